@@ -1,6 +1,6 @@
 // kernels_step.hip -- reset (per-env factorisation), fused / plain step,
 // deterministic episode statistics, and layout gather/scatter kernels.
-#include "fossen_device.h"
+#include "fossen_quad.h"
 
 namespace mg {
 
@@ -173,6 +173,165 @@ hipError_t launch_step(const ClassConst& cc, const StepArgs& a, hipStream_t s) {
       return hipErrorInvalidValue;
   }
 #undef MG_CASE
+}
+
+// ---------------------------------------------------------------------------
+// the same control steps with one env per quad of lanes (fossen_quad.h), all
+// classes in one launch: launches too small to fill the GPU with one env per
+// lane, which last as long as one wave's instruction chain.
+// ---------------------------------------------------------------------------
+
+__device__ __forceinline__ double quad_sum(double x) {
+  x += qperm<MG_QP(1, 0, 3, 2)>(x);
+  return x + qperm<MG_QP(2, 3, 0, 1)>(x);
+}
+
+template <bool LAG, bool EACH>
+__global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, const QuadSegs segs) {
+  int k = 0;
+  while (k + 1 < segs.n && (int)blockIdx.x >= segs.blk_end[k]) ++k;
+  const int blk0 = k > 0 ? segs.blk_end[k - 1] : 0;
+  const ClassConst* __restrict__ cc = segs.cc + k;
+  const int64_t seg_start = segs.start[k], seg_len = segs.len[k];
+  const int lane = threadIdx.x;
+  const QuadLane L = quad_lane(lane);
+  const int c = L.c, ci = c > 1 ? c - 1 : 0;
+  // the four lanes of a quad share every condition below, so a DPP exchange
+  // never reads a lane that is switched off
+  const int64_t local = (int64_t)((int)blockIdx.x - blk0) * kQuadEnvs + (lane >> 2);
+  bool active = local < seg_len && MG_CHECK(a, seg_start + seg_len <= a.Ep, kDbgSegment);
+  const uint32_t j = (uint32_t)(seg_start + (active ? local : 0));
+  const uint32_t j4 = j * 4u;
+  int64_t col = active ? (a.perm ? (int64_t)lane_elem(a.perm, j4) : (int64_t)j) : 0;
+  active = active && MG_CHECK(a, col >= 0 && col < a.dbg.cols, kDbgColumn);
+  const uint32_t c4 = active ? (uint32_t)col * 4u : 0u;
+  const uint32_t s4 = (uint32_t)a.Ep * 4u, e4 = (uint32_t)a.E * 4u;
+  const uint32_t ji = j4 + (uint32_t)ci * s4, jc = j4 + (uint32_t)c * s4;   // internal rows
+  const uint32_t oi = c4 + (uint32_t)ci * e4, oc = c4 + (uint32_t)c * e4;   // caller rows
+
+  QuadThr th;
+  load_quad_thr(cc, c, th);
+  const int n_f = th.lag ? th.n : 0;     // lag states of this class
+  const bool f0 = c < n_f, f1 = c + 4 < n_f;
+  QuadState x;
+  x.p = lane_elem(a.state, ji);
+  x.q = lane_elem(a.state + 3 * a.Ep, jc);
+  x.v = lane_elem(a.state + 7 * a.Ep, ji);
+  x.w = lane_elem(a.state + 10 * a.Ep, ji);
+  x.f[0] = f0 ? lane_elem(a.state + 13 * a.Ep, jc) : 0.0f;
+  x.f[1] = f1 ? lane_elem(a.state + 17 * a.Ep, jc) : 0.0f;
+  bool frozen = lane_elem(a.flags, j) != 0;
+  const QuadStep sc = quad_step_const(cc, a.dt);
+  QuadConst C;
+  QuadMass M;
+  load_quad_const(a.derived, a.Ep, j4, c, sc.h2, C, M);
+  // each control step's throttles are loaded one step ahead
+  const int64_t frame = (int64_t)a.n_max * a.E;
+  float nxt[2];
+  nxt[0] = c < th.n ? lane_elem(a.actions, oc) : 0.0f;
+  nxt[1] = c + 4 < th.n ? lane_elem(a.actions + 4 * a.E, oc) : 0.0f;
+  float tg = 0.0f;
+  if (a.partials && a.targets) tg = lane_elem(a.targets, oi);
+
+  auto quad_finite = [&]() {
+    int ok = isfinite(x.q) && isfinite(x.f[0]) && isfinite(x.f[1]) &&
+             (c == 0 || (isfinite(x.p) && isfinite(x.v) && isfinite(x.w)));
+    ok &= qperm<MG_QP(1, 0, 3, 2)>(ok);
+    ok &= qperm<MG_QP(2, 3, 0, 1)>(ok);
+    return ok != 0;
+  };
+  bool bad = false;     // EACH: went non-finite in this launch
+  for (int t = 0; t < a.n_ctrl; ++t) {
+    const float act[2] = {nxt[0], nxt[1]};
+    if (t + 1 < a.n_ctrl) {
+      const float* af = a.actions + (int64_t)(t + 1) * frame;
+      nxt[0] = c < th.n ? lane_elem(af, oc) : 0.0f;
+      nxt[1] = c + 4 < th.n ? lane_elem(af + 4 * a.E, oc) : 0.0f;
+    }
+    QuadState x0;
+    if constexpr (EACH) x0 = x;
+    if (!frozen) quad_control_step<LAG>(L, C, M, th, sc, act, x, a.substeps);
+    if (a.traj && active) {
+      float* tf = a.traj + (int64_t)t * a.D * a.E;
+      lane_elem(tf + 3 * a.E, oc) = x.q;
+      if (c > 0) {
+        lane_elem(tf, oi) = x.p;
+        lane_elem(tf + 7 * a.E, oi) = x.v;
+        lane_elem(tf + 10 * a.E, oi) = x.w;
+      }
+      if (13 + c < a.D) lane_elem(tf + 13 * a.E, oc) = f0 ? x.f[0] : 0.0f;
+      if (17 + c < a.D) lane_elem(tf + 17 * a.E, oc) = f1 ? x.f[1] : 0.0f;
+    }
+    bool finite = true;
+    if (EACH || a.partials) finite = quad_finite();
+    if (a.partials) {
+      // lane c of the quad takes statistic c: distance sum, its maximum,
+      // kinetic energy, frozen envs
+      const double dd = c > 0 ? (double)x.p - tg : 0.0;
+      const double v = x.v, w = x.w;
+      const double al = (double)M.l * v + (double)M.cl * qperm<kSwapXY>(x.w);
+      const double aa = (double)M.a * w + (double)M.ca * qperm<kSwapXY>(x.v);
+      const double dist = sqrt(quad_sum(mul_nc(dd, dd)));
+      const double ke = 0.5 * quad_sum(c > 0 ? v * al + w * aa : 0.0);
+      const bool good = finite && !frozen;
+      double s = c == 3 ? (active && !good ? 1.0 : 0.0) : (active && good ? (c == 2 ? ke : dist) : 0.0);
+#pragma unroll
+      for (int off = 4; off < 64; off <<= 1) {
+        const double o = __shfl_xor(s, off, 64);
+        s = c == 1 ? fmax(s, o) : s + o;
+      }
+      if (lane < 4)
+        a.partials[((int64_t)t * a.nblk_total + blockIdx.x) * 4 + lane] = s;
+    }
+    if constexpr (EACH) {
+      if (!finite && !frozen) {
+        x = x0;
+        frozen = bad = true;
+      }
+    }
+  }
+  if (!active) return;
+  if (EACH ? !bad : quad_finite()) {
+    lane_elem(a.state + 3 * a.Ep, jc) = x.q;
+    if (c > 0) {
+      lane_elem(a.state, ji) = x.p;
+      lane_elem(a.state + 7 * a.Ep, ji) = x.v;
+      lane_elem(a.state + 10 * a.Ep, ji) = x.w;
+    }
+    if (f0) lane_elem(a.state + 13 * a.Ep, jc) = x.f[0];
+    if (f1) lane_elem(a.state + 17 * a.Ep, jc) = x.f[1];
+  } else {
+    if constexpr (EACH) {
+      // frozen part-way: the state is the input of the step that failed
+      lane_elem(a.state + 3 * a.Ep, jc) = x.q;
+      if (c > 0) {
+        lane_elem(a.state, ji) = x.p;
+        lane_elem(a.state + 7 * a.Ep, ji) = x.v;
+        lane_elem(a.state + 10 * a.Ep, ji) = x.w;
+      }
+      if (f0) lane_elem(a.state + 13 * a.Ep, jc) = x.f[0];
+      if (f1) lane_elem(a.state + 17 * a.Ep, jc) = x.f[1];
+    }
+    if (c == 0)
+      lane_elem(a.flags, j) = (uint8_t)(lane_elem(a.flags, j) | kFlagNonFinite);
+  }
+}
+
+hipError_t launch_step_quad(const QuadSegs& q, const StepArgs& a, bool lag, bool each_step,
+                            hipStream_t s) {
+  const int nblk = q.blk_end[q.n - 1];
+  if (nblk == 0) return hipSuccess;
+  if (a.Ep > kQuadMaxEnvs || a.E > kQuadMaxEnvs) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)nblk), block(kQuadBlock);
+  if (lag && each_step)
+    hipLaunchKernelGGL((k_step_quad<true, true>), grid, block, 0, s, a, q);
+  else if (lag)
+    hipLaunchKernelGGL((k_step_quad<true, false>), grid, block, 0, s, a, q);
+  else if (each_step)
+    hipLaunchKernelGGL((k_step_quad<false, true>), grid, block, 0, s, a, q);
+  else
+    hipLaunchKernelGGL((k_step_quad<false, false>), grid, block, 0, s, a, q);
+  return hipGetLastError();
 }
 
 // second pass: stats[t] = fixed-order combination of the per-block partials

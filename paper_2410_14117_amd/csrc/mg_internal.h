@@ -280,6 +280,27 @@ hipError_t launch_serve_tick(const ServeTickArgs& a, int32_t grid, hipStream_t s
 hipError_t launch_serve_leave(const ServeGatherItem* items, int32_t n_items, ServeTickItem* list,
                               int32_t Dmax, const DebugArgs& dbg, hipStream_t s);
 
+// ---- one env per quad of lanes (fossen_quad.h) ------------------------------
+// The classes' segments of one launch over all of them: block b belongs to the
+// first class k with b < blk_end[k] (kQuadBlock / 4 envs per block).
+constexpr int kQuadBlock = 64;                  // one wave
+constexpr int kQuadEnvs = kQuadBlock / 4;
+// Caller rows and internal rows of the quad kernels are addressed with 32-bit
+// byte offsets (every row of a state or of the constants at once).
+constexpr int64_t kQuadMaxEnvs = (int64_t)1 << 20;
+struct QuadSegs {
+  const ClassConst* cc;        // device [n]
+  int32_t n;
+  int32_t blk_end[MG_MAX_CLASSES];
+  int64_t start[MG_MAX_CLASSES], len[MG_MAX_CLASSES];
+};
+// StepArgs with seg_start, seg_len and blk_off unused (nblk_total: blocks of
+// this launch); each_step: an env whose state is non-finite after a control
+// step is frozen at that step's input, as one launch per control step would,
+// else at the launch's input.
+hipError_t launch_step_quad(const QuadSegs& q, const StepArgs& a, bool lag, bool each_step,
+                            hipStream_t s);
+
 // launchers (kernels_adjoint.hip)
 hipError_t launch_adjoint(bool backward, const ClassConst& cc, const AdjArgs& a, hipStream_t s);
 // every segment's sub-step inputs at once, into the whole-rollout segbuf

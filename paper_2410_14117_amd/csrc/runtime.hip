@@ -49,6 +49,11 @@ float* noalloc_scratch(int device) {
   return g_noalloc_ptr[device];
 }
 
+// Most waves per SIMD of a launch with one env per quad of lanes.
+#ifndef MG_QUAD_WAVES
+#define MG_QUAD_WAVES 1
+#endif
+
 constexpr size_t kMaxCachedGraphs = 64;   // rollout graphs kept per sim
 
 struct GraphKey {
@@ -84,6 +89,9 @@ struct mg_sim {
   std::vector<ClassNominal> nominal;
   std::vector<int64_t> seg_start, seg_len;
   std::vector<int32_t> seg_blk_off;
+  // one env per quad of lanes, all classes in one launch (small sims)
+  bool quad_on = false, any_lag = false;
+  QuadSegs quad{};
 
   float* state = nullptr;      // [D][Ep]
   float* params = nullptr;     // [23][Ep]
@@ -93,6 +101,7 @@ struct mg_sim {
   uint8_t* class_of = nullptr; // [Ep]
   uint8_t* flags = nullptr;    // [Ep] status flags (kFlagNonFinite, kFlagNotSPD)
   ClassNominal* nominal_dev = nullptr;
+  ClassConst* cc_dev = nullptr;      // device copy of cc
   double* partials = nullptr;
   size_t partials_cap = 0;     // doubles
   float* staging = nullptr;    // [max(D,23)][E] for host copies with a permuted layout
@@ -238,8 +247,8 @@ mg_status validate_vehicle(const mg_vehicle& v, int idx, std::string& why, bool&
   return MG_OK;
 }
 
-mg_status ensure_partials(mg_sim* s, int32_t n_ctrl) {
-  const size_t need = (size_t)std::max(n_ctrl, 1) * (size_t)s->nblk_total * 4;
+mg_status ensure_partials(mg_sim* s, int32_t n_ctrl, int32_t nblk) {
+  const size_t need = (size_t)std::max(n_ctrl, 1) * (size_t)nblk * 4;
   if (need <= s->partials_cap) return MG_OK;
   // a graph may hold the old buffer: drop the cache before freeing it
   MG_HIP(s, hipStreamSynchronize(s->stream));
@@ -256,12 +265,7 @@ mg_status ensure_partials(mg_sim* s, int32_t n_ctrl) {
   return MG_OK;
 }
 
-// Enqueue n_ctrl fused control steps (plain = 0) or their plain equivalent
-// (one launch per sub-step), followed by the statistics pass.  Class k >= 1
-// runs on helper stream k-1, forked from and joined back into `st`.
-mg_status enqueue_steps(mg_sim* s, hipStream_t st, const float* actions, int32_t n_ctrl,
-                        const float* targets, float* traj, double* stats, bool plain,
-                        bool one_launch_per_ctrl) {
+StepArgs step_args(mg_sim* s) {
   StepArgs a;
   std::memset(&a, 0, sizeof(a));
   a.state = s->state;
@@ -272,10 +276,45 @@ mg_status enqueue_steps(mg_sim* s, hipStream_t st, const float* actions, int32_t
   a.E = s->E;
   a.perm = s->perm;
   a.n_max = s->n_max;
-  a.targets = targets;
   a.D = s->D;
-  a.nblk_total = s->nblk_total;
   a.dt = (float)s->dt;
+  return a;
+}
+
+// n_ctrl control steps of every class with one env per quad of lanes, frozen
+// as one launch per control step would (each_step) or as one launch.  With
+// statistics the per-wave partials of at most kQuadStatSteps control steps are
+// held at a time (each_step only: with one launch for all of them, all).
+constexpr int32_t kQuadStatSteps = 128;
+mg_status enqueue_quad(mg_sim* s, const float* actions, int32_t n_ctrl, const float* targets,
+                       float* traj, double* stats, bool each_step) {
+  StepArgs a = step_args(s);
+  a.targets = targets;
+  a.nblk_total = s->quad.blk_end[s->n_classes - 1];
+  a.substeps = s->substeps;
+  a.partials = stats ? s->partials : nullptr;
+  const int32_t piece = stats && each_step ? kQuadStatSteps : n_ctrl;
+  for (int32_t t = 0; t < n_ctrl; t += piece) {
+    a.actions = actions + (int64_t)t * s->n_max * s->E;
+    a.traj = traj ? traj + (int64_t)t * s->D * s->E : nullptr;
+    a.n_ctrl = std::min(piece, n_ctrl - t);
+    MG_HIP(s, launch_step_quad(s->quad, a, s->any_lag, each_step, s->stream));
+    if (stats)
+      MG_HIP(s, launch_stats_finalize(s->partials, a.nblk_total, a.n_ctrl, stats + (int64_t)t * 4,
+                                      s->stream));
+  }
+  return MG_OK;
+}
+
+// Enqueue n_ctrl fused control steps (plain = 0) or their plain equivalent
+// (one launch per sub-step), followed by the statistics pass.  Class k >= 1
+// runs on helper stream k-1, forked from and joined back into `st`.
+mg_status enqueue_steps(mg_sim* s, hipStream_t st, const float* actions, int32_t n_ctrl,
+                        const float* targets, float* traj, double* stats, bool plain,
+                        bool one_launch_per_ctrl) {
+  StepArgs a = step_args(s);
+  a.targets = targets;
+  a.nblk_total = s->nblk_total;
   const int64_t frame = (int64_t)s->n_max * s->E;
   const int64_t tframe = (int64_t)s->D * s->E;
   const int64_t pframe = (int64_t)s->nblk_total * 4;
@@ -370,7 +409,11 @@ mg_status step_common(mg_sim* s, const float* actions, int32_t n_ctrl, const flo
   if (!actions) return fail(s, MG_ERR_INVALID, "actions is NULL");
   if (n_ctrl < 1) return fail(s, MG_ERR_INVALID, "n_ctrl must be >= 1");
   DeviceGuard g(s->device);
-  if (stats && (st = ensure_partials(s, n_ctrl))) return st;
+  if (s->quad_on && !plain) {
+    if (stats && (st = ensure_partials(s, n_ctrl, s->quad.blk_end[s->n_classes - 1]))) return st;
+    return enqueue_quad(s, actions, n_ctrl, targets, traj, stats, false);
+  }
+  if (stats && (st = ensure_partials(s, n_ctrl, s->nblk_total))) return st;
   return enqueue_steps(s, s->stream, actions, n_ctrl, targets, traj, stats, plain, false);
 }
 
@@ -588,6 +631,16 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
   }
   s->Ep = std::max<int64_t>(off, kSegAlign);
   s->nblk_total = blk;
+  s->quad.n = cfg->n_classes;
+  int64_t quad_blk = 0;
+  for (int k = 0; k < cfg->n_classes; ++k) {
+    s->any_lag = s->any_lag || s->cc[k].lag;
+    quad_blk += (count[k] + kQuadEnvs - 1) / kQuadEnvs;
+    s->quad.blk_end[k] = (int32_t)std::min<int64_t>(quad_blk, INT32_MAX);
+    s->quad.start[k] = s->seg_start[k];
+    s->quad.len[k] = count[k];
+  }
+  s->quad_on = s->Ep <= kQuadMaxEnvs && quad_blk <= (int64_t)n_cu * 4 * MG_QUAD_WAVES;
   std::vector<int32_t> perm(s->Ep, -1), iperm(E);
   std::vector<uint8_t> cls(s->Ep, 0);
   {
@@ -617,6 +670,7 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
       hipMalloc(&s->derived, Ep * kNumDerived * sizeof(float)) != hipSuccess ||
       hipMalloc(&s->class_of, Ep) != hipSuccess || hipMalloc(&s->flags, Ep) != hipSuccess ||
       hipMalloc(&s->nominal_dev, sizeof(ClassNominal) * s->n_classes) != hipSuccess ||
+      hipMalloc(&s->cc_dev, sizeof(ClassConst) * s->n_classes) != hipSuccess ||
       hipMalloc(&s->staging, (size_t)E * std::max(s->D, kNumParams) * sizeof(float)) != hipSuccess ||
       (!identity && (hipMalloc(&s->perm, Ep * sizeof(int32_t)) != hipSuccess ||
                      hipMalloc(&s->iperm, (size_t)E * sizeof(int32_t)) != hipSuccess))) {
@@ -631,11 +685,14 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
       hipMemcpy(s->class_of, cls.data(), Ep, hipMemcpyHostToDevice) != hipSuccess ||
       hipMemcpy(s->nominal_dev, s->nominal.data(), sizeof(ClassNominal) * s->n_classes,
                 hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(s->cc_dev, s->cc.data(), sizeof(ClassConst) * s->n_classes,
+                hipMemcpyHostToDevice) != hipSuccess ||
       (!identity && (hipMemcpy(s->perm, perm.data(), Ep * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess ||
                      hipMemcpy(s->iperm, iperm.data(), (size_t)E * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess))) {
     (void)hipGetLastError();
     return bail(MG_ERR_DEVICE, "device initialisation failed in mg_create");
   }
+  s->quad.cc = s->cc_dev;
   // the debug build's failed-check word; MG_DEBUG_SHRINK=k (read here, debug
   // build only) makes the kernels treat caller columns >= E - k as out of
   // bounds, so that a test can see the checks fire while every access stays in
@@ -691,7 +748,7 @@ void mg_destroy(mg_sim* s) {
     for (hipEvent_t e : s->ev_fork) (void)hipEventDestroy(e);
     for (hipEvent_t e : s->ev_join) (void)hipEventDestroy(e);
     void* bufs[] = {s->state, s->params, s->derived, s->perm, s->iperm, s->class_of, s->flags,
-                    s->nominal_dev, s->partials, s->staging, s->segbuf, s->task_f, s->task_k,
+                    s->nominal_dev, s->cc_dev, s->partials, s->staging, s->segbuf, s->task_f, s->task_k,
                     s->split_acc, s->dbg.word};
     for (void* b : bufs)
       if (b) (void)hipFree(b);
@@ -931,7 +988,13 @@ mg_status mg_rollout(mg_sim* s, const float* actions, int32_t T, const float* ta
   if (!actions) return fail(s, MG_ERR_INVALID, "actions is NULL");
   if (T < 1) return fail(s, MG_ERR_INVALID, "T must be >= 1");
   DeviceGuard g(s->device);
-  if (stats && (st = ensure_partials(s, T))) return st;
+  if (s->quad_on && !plain) {
+    if (stats && (st = ensure_partials(s, std::min(T, kQuadStatSteps),
+                                       s->quad.blk_end[s->n_classes - 1])))
+      return st;
+    return enqueue_quad(s, actions, T, targets, traj, stats, true);
+  }
+  if (stats && (st = ensure_partials(s, T, s->nblk_total))) return st;
   GraphKey key{T, plain ? 1 : 0, actions, targets, traj, stats};
   auto it = s->graphs.find(key);
   if (it == s->graphs.end()) {

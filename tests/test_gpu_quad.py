@@ -1,0 +1,98 @@
+"""GPU checks of the kernels that spread one env over a quad of lanes (sims of at most one
+wave per SIMD) against the ones with one env per lane: the same envs inside a batch too
+large for the quad kernels, bitwise, at the edges of a wave's 16 envs and of the range."""
+import sys
+import os
+
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+
+from tests.gpu_util import dev, host, say                                  # noqa: E402
+from workloads import (BLUEROV2, BLUEROV2_HEAVY, actions, param_multipliers,   # noqa: E402
+                       random_states, vehicle_variant)
+
+pytestmark = pytest.mark.gpu
+
+BIG = 20000       # more than one quad wave per SIMD of 256 CUs (16384 envs)
+LAG_HEAVY = vehicle_variant(BLUEROV2_HEAVY, thr_map=1, thr_tau=0.05)
+LAG_BLUE = vehicle_variant(BLUEROV2, thr_map=1, thr_tau=0.05)
+THREE = dict(BLUEROV2, thr_pos=BLUEROV2["thr_pos"][:3], thr_dir=BLUEROV2["thr_dir"][:3])
+FLEETS = {"heavy": [LAG_HEAVY], "bluerov2": [BLUEROV2], "three": [THREE],
+          "mixed": [LAG_BLUE, LAG_HEAVY], "lag_and_not": [LAG_HEAVY, BLUEROV2]}
+
+
+@pytest.fixture(scope="module")
+def mgmod():
+    from paper_2410_14117_amd import mg
+    mg.lib()
+    return mg
+
+
+def _inputs(classes, E, T, seed):
+    lagged = max([len(v["thr_pos"]) for v in classes if v["thr_tau"] > 0] or [0])
+    n_max = max(len(v["thr_pos"]) for v in classes)
+    cls = np.random.default_rng(seed).integers(0, len(classes), E).astype(np.int32)
+    x0 = random_states(E, 13 + lagged, seed + 1)
+    for k, v in enumerate(classes):
+        x0[13 + (len(v["thr_pos"]) if v["thr_tau"] > 0 else 0):, cls == k] = 0
+    return cls, x0, 1.2 * actions(T, n_max, E, seed + 2), param_multipliers(E, 0.2, seed + 3)
+
+
+def _run(mg, classes, cls, x0, act, mult, S, mode, E):
+    sim = mg.Sim(classes, E, 0.005, S, env_class=cls[:E])
+    sim.reset(state=dev(x0[:, :E]), param_mult=dev(mult[:, :E]))
+    T = act.shape[0]
+    traj = torch.full((T, x0.shape[0], E), -1.0, device="cuda")
+    stats = torch.empty((T, 4), dtype=torch.float64, device="cuda")
+    fn = sim.rollout if mode == "rollout" else sim.step
+    fn(dev(act[:, :, :E]), traj=traj, stats=stats)
+    out = host(traj), host(stats), host(sim.get_state()), host(sim.get_flags())
+    sim.close()
+    return out
+
+
+@pytest.mark.parametrize("fleet,S,T,mode,sizes", [
+    ("heavy", 4, 3, "step", (1, 15, 16, 17, 16384)),
+    ("bluerov2", 1, 130, "rollout", (33,)),     # more than one piece of the statistics
+    ("three", 2, 3, "step", (49,)),
+    ("mixed", 4, 5, "rollout", (2, 1001)),
+    ("lag_and_not", 2, 4, "step", (1001,)),
+])
+def test_quad_step_equals_one_env_per_lane(mgmod, fleet, S, T, mode, sizes):
+    classes = FLEETS[fleet]
+    cls, x0, act, mult = _inputs(classes, BIG, T, 11)
+    say("quad step", fleet, S, T, mode)
+    big = _run(mgmod, classes, cls, x0, act, mult, S, mode, BIG)
+    for E in sizes:
+        say("  envs", E)
+        traj, stats, xT, flags = _run(mgmod, classes, cls, x0, act, mult, S, mode, E)
+        np.testing.assert_array_equal(traj, big[0][:, :, :E])
+        np.testing.assert_array_equal(xT, big[2][:, :E])
+        assert not flags.any() and not stats[:, 3].any()
+        # FP64 sums of the same FP32 positions in another order
+        d = np.sqrt((traj[:, :3].astype(np.float64) ** 2).sum(1))
+        np.testing.assert_allclose(stats[:, 0], d.sum(1), rtol=1e-12)
+        np.testing.assert_allclose(stats[:, 1], d.max(1), rtol=1e-12)
+
+
+@pytest.mark.parametrize("mode", ["step", "rollout"])
+def test_quad_freeze_equals_one_env_per_lane(mgmod, mode):
+    """An env whose throttles turn NaN part-way, in a launch of several control steps and in a
+    rollout: the same frozen state, flags, counts and later trajectory rows either way."""
+    classes, T = FLEETS["mixed"], 6
+    cls, x0, act, mult = _inputs(classes, BIG, T, 21)
+    act[2, 1, 5] = np.nan
+    act[0, 0, 18] = np.nan
+    say("quad freeze", mode)
+    big = _run(mgmod, classes, cls, x0, act, mult, 2, mode, BIG)
+    traj, stats, xT, flags = _run(mgmod, classes, cls, x0, act, mult, 2, mode, 40)
+    np.testing.assert_array_equal(xT, big[2][:, :40])
+    np.testing.assert_array_equal(flags, big[3][:40])
+    assert list(np.flatnonzero(flags)) == [5, 18]
+    np.testing.assert_array_equal(traj, big[0][:, :, :40])
+    assert list(stats[:, 3]) == [1, 1, 2, 2, 2, 2]
