@@ -348,8 +348,8 @@ mg_status mg_task_counters(mg_sim* sim, int32_t* out);
  * parameter layout); the sim's current parameters are used.
  *
  * mg_adj_forward: T control steps from the sim's current state (which it
- *   advances), one launch per class, storing the state before every
- *   ckpt_every-th control step.
+ *   advances), one launch per class (one for all of them if the sim is small),
+ *   storing the state before every ckpt_every-th control step.
  *   actions  device [T][N_max][E]
  *   ckpt     device [ceil(T / ckpt_every)][D][E]  (written)
  *   traj     device [T][D][E] state after each control step, or NULL
@@ -360,8 +360,9 @@ mg_status mg_task_counters(mg_sim* sim, int32_t* out);
  *   first), so nothing is recomputed and no scratch is used.  Otherwise the sub-step
  *   states it linearises about are held in a scratch buffer the sim owns and
  *   keeps until mg_destroy: the whole rollout's (T * substeps * D * E floats)
- *   when that fits in 4 GiB, there is more than one segment and the allocation
- *   succeeds, every segment then recomputed at once before the sweep;
+ *   when that fits in 4 GiB, there is more than one segment (or the sim is small:
+ *   at most 16 envs per SIMD of the device) and the allocation succeeds, every
+ *   segment then recomputed at once before the sweep;
  *   otherwise one segment's (ckpt_every * substeps * D * E floats), recomputed
  *   just before its sweep.  The gradients are the same, bitwise, either way.
  *   MG_ERR_OOM only when the segment-sized buffer cannot be allocated.

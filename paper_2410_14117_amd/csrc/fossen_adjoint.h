@@ -67,130 +67,126 @@ __device__ __forceinline__ float theta_bar_get(const ThetaBarLds& t, int k) {
 }
 
 // dL/d(x, tau, theta) of xd = rhs_core(x, tau) given xdb = dL/dxd.
-// Accumulates into xb (13 rows; the position rows receive nothing) and thb;
-// writes taub.
+// Writes xb (rows 3..12; the position rows receive nothing) and taub and
+// accumulates into thb.
+//
+// Written on 3-vectors, component i with i1 = i + 1 and i2 = i + 2 (mod 3) and
+// every FMA explicit: the same formulas in the same order serve the kernels
+// that hold one component per lane (fossen_quad_adjoint.h), bit for bit.  With
+// t = 2 q_v x v, k = R^T e3, [a; b] = M nu and [f; m] = M^-1 (g_v, g_w) for the
+// rates' adjoints (g_p, g_q, g_v, g_w):
+//   a' = w x f + v x m,  b' = w x m,  k' = (W-B) f + (h_z m_y, -h_z m_x, 0)
+//   v' = g_p - E_l f - a x m + (M (a', b'))_l + 2 t' x q_v
+//   w' = -E_a m - a x f - b x m + (M (a', b'))_a - q_v g_q0 + q_w g_qv + g_qv x q_v
+//   t' = q_w g_p + g_p x q_v,  E = d_L + 2 d_Q |nu|
+//   q_v' = -w g_q0 + w x g_qv + t x g_p + 2 v x t' + (rows of k)
+//   q_w' = w . g_qv + t . g_p + 2 (q_x k'_y - q_y k'_x)
 template <class T, class TB>
 __host__ __device__ __forceinline__ void rhs_core_vjp(const T* x, const EnvConstT<T>& P,
                                                       const T (&tau)[6], const T* xdb, T* xb,
                                                       T (&taub)[6], TB& thb) {
-  const T qw = x[3], qx = x[4], qy = x[5], qz = x[6];
-  const T u = x[7], v = x[8], w = x[9], p = x[10], q = x[11], r = x[12];
-  // forward intermediates
-  const T x2 = qx + qx, y2 = qy + qy, z2 = qz + qz;
-  const T t0 = fma_t(y2, w, -z2 * v);
-  const T t1 = fma_t(z2, u, -x2 * w);
-  const T t2 = fma_t(x2, v, -y2 * u);
-  const T k0 = fma_t(x2, qz, -y2 * qw);
-  const T k1 = fma_t(y2, qz, x2 * qw);
-  const T k2 = fma_t(-y2, qy, fma_t(-x2, qx, T(1)));
-  const T au = fma_t(P.Muq, q, P.Muu * u), av = fma_t(P.Mvp, p, P.Mvv * v), aw = P.Mww * w;
-  const T bp = fma_t(P.Mpp, p, P.Mvp * v), bq = fma_t(P.Mqq, q, P.Muq * u), br = P.Mrr * r;
-  const T nu[6] = {u, v, w, p, q, r};
-  T e[6];
-#pragma unroll
-  for (int i = 0; i < 6; ++i) e[i] = fma_t(P.dq[i], abs_t(nu[i]), P.dl[i]);
-  const T r0 = fma_t(-e[0], u, fma_t(P.wmb, k0, fma_t(-q, aw, fma_t(r, av, tau[0]))));
-  const T r1 = fma_t(-e[1], v, fma_t(P.wmb, k1, fma_t(-r, au, fma_t(p, aw, tau[1]))));
-  const T r2 = fma_t(-e[2], w, fma_t(P.wmb, k2, fma_t(-p, av, fma_t(q, au, tau[2]))));
-  const T r3 = fma_t(-e[3], p, fma_t(-P.hz, k1,
-               fma_t(r, bq, fma_t(-q, br, fma_t(w, av, fma_t(-v, aw, tau[3]))))));
-  const T r4 = fma_t(-e[4], q, fma_t(P.hz, k0,
-               fma_t(p, br, fma_t(-r, bp, fma_t(u, aw, fma_t(-w, au, tau[4]))))));
-  const T r5 = fma_t(-e[5], r, fma_t(q, bp, fma_t(-p, bq, fma_t(v, au, fma_t(-u, av, tau[5])))));
-  const T nud[6] = {fma_t(P.Iuq, r4, P.Iuu * r0), fma_t(P.Ivp, r3, P.Ivv * r1), P.Iww * r2,
-                    fma_t(P.Ipp, r3, P.Ivp * r1), fma_t(P.Iqq, r4, P.Iuq * r0), P.Irr * r5};
+  // forward intermediates, as rhs_residual forms them
+  const T qw = x[3];
+  const T* q = x + 4;
+  const T* v = x + 7;
+  const T* w = x + 10;
+  T xd[7], res[6], mom[6];
+  momentum(P, v, mom);
+  rhs_residual_m(x, mom, xd, res, P, tau);
+  const T* a = mom;
+  const T* b = mom + 3;
+  const T x2 = q[0] + q[0], y2 = q[1] + q[1], z2 = q[2] + q[2];
+  const T t[3] = {fma_t(y2, v[2], -z2 * v[1]), fma_t(z2, v[0], -x2 * v[2]),
+                  fma_t(x2, v[1], -y2 * v[0])};
+  const T k[3] = {fma_t(x2, q[2], -y2 * qw), fma_t(y2, q[2], x2 * qw),
+                  fma_t(-y2, q[1], fma_t(-x2, q[0], T(1)))};
+  const T nud[6] = {fma_t(P.Iuq, res[4], P.Iuu * res[0]), fma_t(P.Ivp, res[3], P.Ivv * res[1]),
+                    P.Iww * res[2], fma_t(P.Ipp, res[3], P.Ivp * res[1]),
+                    fma_t(P.Iqq, res[4], P.Iuq * res[0]), P.Irr * res[5]};
 
   // nu' = M^-1 r:  rb = M^-1 nudb (M symmetric);  dM_ii gets -rb_i nud_i
-  const T gu = xdb[7], gv = xdb[8], gw = xdb[9], gp = xdb[10], gq = xdb[11], gr = xdb[12];
+  const T* gp = xdb;
+  const T gw = xdb[3];
+  const T* gv = xdb + 4;
+  const T* gn = xdb + 7;
   T rb[6];
-  rb[0] = fma_t(P.Iuq, gq, P.Iuu * gu);
-  rb[4] = fma_t(P.Iqq, gq, P.Iuq * gu);
-  rb[1] = fma_t(P.Ivp, gp, P.Ivv * gv);
-  rb[3] = fma_t(P.Ipp, gp, P.Ivp * gv);
-  rb[2] = mul_nc(P.Iww, gw);
-  rb[5] = mul_nc(P.Irr, gr);
+  rb[0] = fma_t(P.Iuq, gn[4], P.Iuu * gn[0]);
+  rb[1] = fma_t(P.Ivp, gn[3], P.Ivv * gn[1]);
+  rb[2] = mul_nc(P.Iww, gn[2]);
+  rb[3] = fma_t(P.Ipp, gn[3], P.Ivp * gn[1]);
+  rb[4] = fma_t(P.Iqq, gn[4], P.Iuq * gn[0]);
+  rb[5] = mul_nc(P.Irr, gn[5]);
+  const T* f = rb;
+  const T* m = rb + 3;
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
     thb.ma[i] -= rb[i] * nud[i];
     taub[i] = rb[i];
   }
-  // residual rows
-  T nub[6] = {T(0), T(0), T(0), T(0), T(0), T(0)};   // u v w p q r
-  T aub = T(0), avb = T(0), awb = T(0), bpb = T(0), bqb = T(0), brb = T(0);
-  T k0b = T(0), k1b = T(0), k2b = T(0);
-  T eb[6];
-  // r0 = tau0 + r av - q aw + wmb k0 - e0 u
-  nub[5] += av * rb[0]; avb += r * rb[0]; nub[4] -= aw * rb[0]; awb -= q * rb[0];
-  k0b += P.wmb * rb[0]; thb.wmb += k0 * rb[0]; eb[0] = mul_nc(-u, rb[0]); nub[0] -= e[0] * rb[0];
-  // r1 = tau1 + p aw - r au + wmb k1 - e1 v
-  nub[3] += aw * rb[1]; awb += p * rb[1]; nub[5] -= au * rb[1]; aub -= r * rb[1];
-  k1b += P.wmb * rb[1]; thb.wmb += k1 * rb[1]; eb[1] = mul_nc(-v, rb[1]); nub[1] -= e[1] * rb[1];
-  // r2 = tau2 + q au - p av + wmb k2 - e2 w
-  nub[4] += au * rb[2]; aub += q * rb[2]; nub[3] -= av * rb[2]; avb -= p * rb[2];
-  k2b += P.wmb * rb[2]; thb.wmb += k2 * rb[2]; eb[2] = mul_nc(-w, rb[2]); nub[2] -= e[2] * rb[2];
-  // r3 = tau3 - v aw + w av - q br + r bq - hz k1 - e3 p
-  nub[1] -= aw * rb[3]; awb -= v * rb[3]; nub[2] += av * rb[3]; avb += w * rb[3];
-  nub[4] -= br * rb[3]; brb -= q * rb[3]; nub[5] += bq * rb[3]; bqb += r * rb[3];
-  k1b -= P.hz * rb[3]; thb.hz -= k1 * rb[3]; eb[3] = mul_nc(-p, rb[3]); nub[3] -= e[3] * rb[3];
-  // r4 = tau4 - w au + u aw - r bp + p br + hz k0 - e4 q
-  nub[2] -= au * rb[4]; aub -= w * rb[4]; nub[0] += aw * rb[4]; awb += u * rb[4];
-  nub[5] -= bp * rb[4]; bpb -= r * rb[4]; nub[3] += br * rb[4]; brb += p * rb[4];
-  k0b += P.hz * rb[4]; thb.hz += k0 * rb[4]; eb[4] = mul_nc(-q, rb[4]); nub[4] -= e[4] * rb[4];
-  // r5 = tau5 - u av + v au - p bq + q bp - e5 r
-  nub[0] -= av * rb[5]; avb -= u * rb[5]; nub[1] += au * rb[5]; aub += v * rb[5];
-  nub[3] -= bq * rb[5]; bqb -= p * rb[5]; nub[4] += bp * rb[5]; bpb += q * rb[5];
-  eb[5] = mul_nc(-r, rb[5]); nub[5] -= e[5] * rb[5];
-  // e_i = d_L,i + d_Q,i |nu_i|   (d|x|/dx taken as +1 at 0)
+  thb.wmb += k[0] * f[0];
+  thb.wmb += k[1] * f[1];
+  thb.wmb += k[2] * f[2];
+  thb.hz -= k[1] * m[0];
+  thb.hz += k[0] * m[1];
+  T ab[3], bb[3], tb2[3], kb2[3], vb[3], wb[3], qb[3], s[3];
 #pragma unroll
-  for (int i = 0; i < 6; ++i) {
-    thb.dl[i] += eb[i];
-    thb.dq[i] += eb[i] * abs_t(nu[i]);
-    nub[i] += (nu[i] < T(0) ? -P.dq[i] : P.dq[i]) * eb[i];
+  for (int i = 0; i < 3; ++i) {
+    const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
+    // damping: e = d_L + d_Q |nu| (d|x|/dx taken as +1 at 0)
+    const T ebl = mul_nc(-v[i], f[i]), eba = mul_nc(-w[i], m[i]);
+    thb.dl[i] += ebl;
+    thb.dl[3 + i] += eba;
+    thb.dq[i] += ebl * abs_t(v[i]);
+    thb.dq[3 + i] += eba * abs_t(w[i]);
+    const T el = fma_t(P.dq[i], abs_t(v[i]), fma_t(P.dq[i], abs_t(v[i]), P.dl[i]));
+    const T ea = fma_t(P.dq[3 + i], abs_t(w[i]), fma_t(P.dq[3 + i], abs_t(w[i]), P.dl[3 + i]));
+    // [a; b] = M nu
+    ab[i] = fma_t(-v[i2], m[i1], fma_t(v[i1], m[i2], fma_t(-w[i2], f[i1], mul_nc(w[i1], f[i2]))));
+    bb[i] = fma_t(-w[i2], m[i1], mul_nc(w[i1], m[i2]));
+    vb[i] = fma_t(-a[i1], m[i2], fma_t(a[i2], m[i1], fma_t(-el, f[i], gp[i])));
+    wb[i] = fma_t(-b[i1], m[i2], fma_t(b[i2], m[i1],
+            fma_t(-a[i1], f[i2], fma_t(a[i2], f[i1], mul_nc(-ea, m[i])))));
+    // quaternion rows (xd[3..6] = q (x) (0, w)) and t
+    wb[i] = fma_t(-gv[i2], q[i1], fma_t(gv[i1], q[i2], fma_t(qw, gv[i], fma_t(-q[i], gw, wb[i]))));
+    const T tb = fma_t(-gp[i2], q[i1], fma_t(gp[i1], q[i2], mul_nc(qw, gp[i])));
+    tb2[i] = tb + tb;
+    const T kb = mul_nc(P.wmb, f[i]);
+    const T kbi = i == 0 ? fma_t(P.hz, m[1], kb) : (i == 1 ? fma_t(-P.hz, m[0], kb) : kb);
+    kb2[i] = kbi + kbi;
+    qb[i] = fma_t(-w[i2], gv[i1], fma_t(w[i1], gv[i2], mul_nc(-w[i], gw)));
+    qb[i] = fma_t(-t[i2], gp[i1], fma_t(t[i1], gp[i2], qb[i]));
+    s[i] = fma_t(t[i], gp[i], mul_nc(w[i], gv[i]));
   }
-  // [a; b] = M nu
-  nub[0] += P.Muu * aub; nub[4] += P.Muq * aub; thb.ma[0] += u * aub;
-  nub[1] += P.Mvv * avb; nub[3] += P.Mvp * avb; thb.ma[1] += v * avb;
-  nub[2] += P.Mww * awb; thb.ma[2] += w * awb;
-  nub[1] += P.Mvp * bpb; nub[3] += P.Mpp * bpb; thb.ma[3] += p * bpb;
-  nub[0] += P.Muq * bqb; nub[4] += P.Mqq * bqb; thb.ma[4] += q * bqb;
-  nub[5] += P.Mrr * brb; thb.ma[5] += r * brb;
-  // quaternion rows (xd[3..6] = q (x) (0, w))
-  const T g0 = xdb[0], g1 = xdb[1], g2 = xdb[2];
-  const T g3 = xdb[3], g4 = xdb[4], g5 = xdb[5], g6 = xdb[6];
-  T qwb = T(0), qxb = T(0), qyb = T(0), qzb = T(0);
-  qxb -= p * g3; nub[3] -= qx * g3; qyb -= q * g3; nub[4] -= qy * g3; qzb -= r * g3;
-  nub[5] -= qz * g3;
-  qwb += p * g4; nub[3] += qw * g4; qyb += r * g4; nub[5] += qy * g4; qzb -= q * g4;
-  nub[4] -= qz * g4;
-  qwb += q * g5; nub[4] += qw * g5; qzb += p * g5; nub[3] += qz * g5; qxb -= r * g5;
-  nub[5] -= qx * g5;
-  qwb += r * g6; nub[5] += qw * g6; qxb += q * g6; nub[4] += qx * g6; qyb -= p * g6;
-  nub[3] -= qy * g6;
-  // k = R^T e3
-  T x2b = T(0), y2b = T(0), z2b = T(0);
-  x2b += qz * k0b; qzb += x2 * k0b; y2b -= qw * k0b; qwb -= y2 * k0b;
-  y2b += qz * k1b; qzb += y2 * k1b; x2b += qw * k1b; qwb += x2 * k1b;
-  x2b -= qx * k2b; qxb -= x2 * k2b; y2b -= qy * k2b; qyb -= y2 * k2b;
-  // p' = v + qw t + q_v x t,  t = 2 q_v x v
-  T t0b = T(0), t1b = T(0), t2b = T(0);
-  nub[0] += g0; qwb += t0 * g0; t0b += qw * g0; qyb += t2 * g0; t2b += qy * g0;
-  qzb -= t1 * g0; t1b -= qz * g0;
-  nub[1] += g1; qwb += t1 * g1; t1b += qw * g1; qzb += t0 * g1; t0b += qz * g1;
-  qxb -= t2 * g1; t2b -= qx * g1;
-  nub[2] += g2; qwb += t2 * g2; t2b += qw * g2; qxb += t1 * g2; t1b += qx * g2;
-  qyb -= t0 * g2; t0b -= qy * g2;
-  y2b += w * t0b; nub[2] += y2 * t0b; z2b -= v * t0b; nub[1] -= z2 * t0b;
-  z2b += u * t1b; nub[0] += z2 * t1b; x2b -= w * t1b; nub[2] -= x2 * t1b;
-  x2b += v * t2b; nub[1] += x2 * t2b; y2b -= u * t2b; nub[0] -= y2 * t2b;
-  qxb += T(2) * x2b;
-  qyb += T(2) * y2b;
-  qzb += T(2) * z2b;
-  xb[3] += qwb;
-  xb[4] += qxb;
-  xb[5] += qyb;
-  xb[6] += qzb;
 #pragma unroll
-  for (int i = 0; i < 6; ++i) xb[7 + i] += nub[i];
+  for (int i = 0; i < 3; ++i) {
+    thb.ma[i] += v[i] * ab[i];
+    thb.ma[3 + i] += w[i] * bb[i];
+  }
+  vb[0] = fma_t(P.Muq, bb[1], fma_t(P.Muu, ab[0], vb[0]));
+  vb[1] = fma_t(P.Mvp, bb[0], fma_t(P.Mvv, ab[1], vb[1]));
+  vb[2] = fma_t(P.Mww, ab[2], vb[2]);
+  wb[0] = fma_t(P.Mvp, ab[1], fma_t(P.Mpp, bb[0], wb[0]));
+  wb[1] = fma_t(P.Muq, ab[0], fma_t(P.Mqq, bb[1], wb[1]));
+  wb[2] = fma_t(P.Mrr, bb[2], wb[2]);
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
+    vb[i] = fma_t(-tb2[i2], q[i1], fma_t(tb2[i1], q[i2], vb[i]));
+    qb[i] = fma_t(-v[i2], tb2[i1], fma_t(v[i1], tb2[i2], qb[i]));
+  }
+  // k = R^T e3
+  qb[0] = fma_t(-x2, kb2[2], fma_t(qw, kb2[1], fma_t(q[2], kb2[0], qb[0])));
+  qb[1] = fma_t(-y2, kb2[2], fma_t(-qw, kb2[0], fma_t(q[2], kb2[1], qb[1])));
+  qb[2] = fma_t(q[1], kb2[1], fma_t(q[0], kb2[0], qb[2]));
+  s[0] = fma_t(q[0], kb2[1], s[0]);
+  s[1] = fma_t(-q[1], kb2[0], s[1]);
+  xb[3] = (s[0] + s[1]) + s[2];
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    xb[4 + i] = qb[i];
+    xb[7 + i] = vb[i];
+    xb[10 + i] = wb[i];
+  }
 }
 
 // Reverse of rk4_substep: y is the sub-step input (D rows), lam holds dL/d(output)
@@ -249,56 +245,56 @@ __host__ __device__ __forceinline__ void rk4_substep_vjp(const T* y, const EnvCo
   for (int i = 0; i < 4; ++i) qt[i] = fma_t(fac(3 + i, h6), acc[3 + i] + k[3 + i], y[3 + i]);
 
   // renormalisation q = qt / |qt|:  dqt = (lam_q - q (q . lam_q)) / |qt|
-  const T n2 = qt[0] * qt[0] + qt[1] * qt[1] + qt[2] * qt[2] + qt[3] * qt[3];
+  const T n2 = fma_t(qt[3], qt[3], fma_t(qt[2], qt[2], fma_t(qt[0], qt[0], qt[1] * qt[1])));
   const T inv = rsqrt_t(n2);
-  T qo[4], dot = T(0);
+  T qo[4], d[4];
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     qo[i] = qt[i] * inv;
-    dot += qo[i] * lam[3 + i];
+    d[i] = mul_nc(qo[i], lam[3 + i]);
   }
+  const T dot = ((d[0] + d[1]) + d[2]) + d[3];
   T zb[13];
 #pragma unroll
   for (int i = 0; i < 13; ++i) zb[i] = lam[i];
 #pragma unroll
   for (int i = 0; i < 4; ++i) zb[3 + i] = mul_nc(lam[3 + i] - qo[i] * dot, inv);
 
-  // combination z' = y + fac(h6) (k1 + 2 k2 + 2 k3 + k4), then the stages in reverse
+  // combination z' = y + fac(h6) (k1 + 2 k2 + 2 k3 + k4), then the stages in
+  // reverse; the position rows of Xb stay zero
   T yb[13], kb[13], Xb[13], tb1[6], tb2[6], tb3[6], tb4[6];
+  auto scale = [&](T weight) {   // kb = weight fac(h6) zb
 #pragma unroll
-  for (int i = 0; i < 13; ++i) {
-    yb[i] = zb[i];
-    kb[i] = mul_nc(fac(i, h6), zb[i]);
-    Xb[i] = T(0);
-  }
+    for (int i = 0; i < 13; ++i) kb[i] = mul_nc(weight * fac(i, h6), zb[i]);
+  };
+  auto add_stage = [&](T c) {    // X = y + fac(c) k: into yb and kb
+#pragma unroll
+    for (int i = 3; i < 13; ++i) {
+      yb[i] += Xb[i];
+      kb[i] = fma_t(fac(i, c), Xb[i], kb[i]);
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < 13; ++i) yb[i] = zb[i];
+  scale(T(1));
   theta_bar_fence(thb);
   rhs_core_vjp(X4, P, tau4, kb, Xb, tb4, thb);          // X4 = y + fac(dt) k3
-#pragma unroll
-  for (int i = 0; i < 13; ++i) {
-    yb[i] += Xb[i];
-    kb[i] = fma_t(fac(i, dt), Xb[i], T(2) * fac(i, h6) * zb[i]);
-    Xb[i] = T(0);
-  }
+  scale(T(2));
+  add_stage(dt);
   theta_bar_fence(thb);
   rhs_core_vjp(X3, P, tau3, kb, Xb, tb3, thb);          // X3 = y + fac(h2) k2
-#pragma unroll
-  for (int i = 0; i < 13; ++i) {
-    yb[i] += Xb[i];
-    kb[i] = fma_t(fac(i, h2), Xb[i], T(2) * fac(i, h6) * zb[i]);
-    Xb[i] = T(0);
-  }
+  scale(T(2));
+  add_stage(h2);
   theta_bar_fence(thb);
   rhs_core_vjp(X2, P, tau2, kb, Xb, tb2, thb);          // X2 = y + fac(h2) k1
-#pragma unroll
-  for (int i = 0; i < 13; ++i) {
-    yb[i] += Xb[i];
-    kb[i] = fma_t(fac(i, h2), Xb[i], fac(i, h6) * zb[i]);
-    Xb[i] = T(0);
-  }
+  scale(T(1));
+  add_stage(h2);
   theta_bar_fence(thb);
   rhs_core_vjp(y, P, tau1, kb, Xb, tb1, thb);           // X1 = y
 #pragma unroll
-  for (int i = 0; i < 13; ++i) lam[i] = yb[i] + Xb[i];
+  for (int i = 0; i < 3; ++i) lam[i] = yb[i];
+#pragma unroll
+  for (int i = 3; i < 13; ++i) lam[i] = yb[i] + Xb[i];
 
   // stage wrenches tau_i = B f_cmd + sigma_i B (f - f_cmd) and f' = f_cmd + rho (f - f_cmd)
   if constexpr (LAG) {

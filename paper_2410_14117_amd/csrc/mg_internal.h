@@ -293,6 +293,7 @@ struct QuadSegs {
   int32_t n;
   int32_t blk_end[MG_MAX_CLASSES];
   int64_t start[MG_MAX_CLASSES], len[MG_MAX_CLASSES];
+  float zb[MG_MAX_CLASSES];    // z_b of the class (dL/dB through h_z)
 };
 // StepArgs with seg_start, seg_len and blk_off unused (nblk_total: blocks of
 // this launch); each_step: an env whose state is non-finite after a control
@@ -300,6 +301,14 @@ struct QuadSegs {
 // else at the launch's input.
 hipError_t launch_step_quad(const QuadSegs& q, const StepArgs& a, bool lag, bool each_step,
                             hipStream_t s);
+
+// The adjoint's kernels with one env per quad of lanes, all classes in one
+// launch (kernels_adjoint_quad.hip; seg_start, seg_len and zb of AdjArgs unused):
+// the forward, the recomputation of every segment's sub-step inputs into the
+// whole-rollout segbuf, and the reverse sweep (a.recomputed 1 or 2).
+hipError_t launch_adj_quad_fwd(const QuadSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
+hipError_t launch_adj_quad_recompute(const QuadSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
+hipError_t launch_adj_quad_bwd(const QuadSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
 
 // launchers (kernels_adjoint.hip)
 hipError_t launch_adjoint(bool backward, const ClassConst& cc, const AdjArgs& a, hipStream_t s);

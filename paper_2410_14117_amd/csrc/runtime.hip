@@ -49,7 +49,12 @@ float* noalloc_scratch(int device) {
   return g_noalloc_ptr[device];
 }
 
-// Most waves per SIMD of a launch with one env per quad of lanes.
+// Most waves per SIMD of a launch with one env per quad of lanes (step and
+// adjoint).  At two waves per SIMD the quad kernels are level with one env per
+// lane (32 768 envs, forward / backward of 16 control steps: 29.1 / 56.2
+// against 27.8 / 59.3 us for 6 thrusters without lag, 72.8 / 260 against 74.8 /
+// 258 us for 8 with lag and 4 sub-steps; 16 384 envs: 22.1 / 35.9 against 28.0 /
+// 57.9 us and 48.3 / 162 against 74.3 / 252 us).
 #ifndef MG_QUAD_WAVES
 #define MG_QUAD_WAVES 1
 #endif
@@ -445,6 +450,14 @@ AdjArgs adj_args(mg_sim* s, const float* actions, int32_t T, int32_t K) {
   return a;
 }
 
+// Whether the sub-step inputs of the whole rollout are recomputed ahead of the
+// sweep (into whole_floats of scratch, at most cap_floats), every segment side
+// by side.  With one env per lane a single segment is left to the sweep's own
+// recomputation; the quad kernels have no such sweep.
+bool adj_whole(const mg_sim* s, int32_t nseg, size_t whole_floats, size_t cap_floats) {
+  return (s->quad_on || nseg > 1) && nseg <= 65535 && whole_floats <= cap_floats;
+}
+
 // Whether the backward reads its inputs from the forward's trajectory: the
 // caller passed one, and each control step is a single sub-step.
 bool traj_inputs(const mg_sim* s, const float* traj) {
@@ -454,7 +467,9 @@ bool traj_inputs(const mg_sim* s, const float* traj) {
 // The backward's launches: per class, the whole rollout's recomputation into
 // buf (whole) and the reverse sweep, or the sweep that recomputes each segment
 // into buf itself; with traj (one sub-step per control step) only the sweep,
-// reading its inputs from traj.  Allocates nothing.
+// reading its inputs from traj.  Small sims take the kernels with one env per
+// quad of lanes, all classes in one launch, except for the sweep that
+// recomputes its segments itself.  Allocates nothing.
 mg_status adj_backward_launch(mg_sim* s, const float* ckpt, const float* traj,
                               const float* actions, int32_t T, int32_t ckpt_every,
                               const float* dL_dtraj, float* dL_dact, float* dL_dtheta,
@@ -468,6 +483,11 @@ mg_status adj_backward_launch(mg_sim* s, const float* ckpt, const float* traj,
   a.gx0 = dL_dx0;
   a.segbuf = buf;
   a.recomputed = traj ? 2 : (whole ? 1 : 0);
+  if (s->quad_on && a.recomputed) {
+    if (!traj) MG_HIP(s, launch_adj_quad_recompute(s->quad, a, s->any_lag, s->stream));
+    MG_HIP(s, launch_adj_quad_bwd(s->quad, a, s->any_lag, s->stream));
+    return MG_OK;
+  }
   for (int k = 0; k < s->n_classes; ++k) {
     a.seg_start = s->seg_start[k];
     a.seg_len = s->seg_len[k];
@@ -639,6 +659,7 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
     s->quad.blk_end[k] = (int32_t)std::min<int64_t>(quad_blk, INT32_MAX);
     s->quad.start[k] = s->seg_start[k];
     s->quad.len[k] = count[k];
+    s->quad.zb[k] = (float)s->nominal[k].zb;
   }
   s->quad_on = s->Ep <= kQuadMaxEnvs && quad_blk <= (int64_t)n_cu * 4 * MG_QUAD_WAVES;
   std::vector<int32_t> perm(s->Ep, -1), iperm(E);
@@ -1044,6 +1065,10 @@ mg_status mg_adj_forward(mg_sim* s, const float* actions, int32_t T, int32_t ckp
   AdjArgs a = adj_args(s, actions, T, ckpt_every);
   a.ckpt = ckpt;
   a.traj = traj;
+  if (s->quad_on) {
+    MG_HIP(s, launch_adj_quad_fwd(s->quad, a, s->any_lag, s->stream));
+    return MG_OK;
+  }
   for (int k = 0; k < s->n_classes; ++k) {
     a.seg_start = s->seg_start[k];
     a.seg_len = s->seg_len[k];
@@ -1077,7 +1102,7 @@ mg_status mg_adj_backward(mg_sim* s, const float* ckpt, const float* traj, const
   const int32_t nseg = (T + ckpt_every - 1) / ckpt_every;
   const size_t whole_floats = (size_t)T * s->substeps * s->D * (size_t)s->Ep;
   const size_t seg_floats = (size_t)std::min(ckpt_every, T) * s->substeps * s->D * (size_t)s->Ep;
-  bool whole = nseg > 1 && nseg <= 65535 && whole_floats * sizeof(float) <= ((size_t)4 << 30);
+  bool whole = adj_whole(s, nseg, whole_floats, (size_t)1 << 30);
   if (whole && whole_floats > s->segbuf_cap) {
     // the new buffer is allocated before the old one is released, so that a
     // failure leaves the old one in place
@@ -1128,7 +1153,7 @@ mg_status mg_adj_backward_noalloc(mg_sim* s, const float* ckpt, const float* tra
   const int32_t nseg = (T + ckpt_every - 1) / ckpt_every;
   const size_t whole_floats = (size_t)T * s->substeps * s->D * (size_t)s->Ep;
   const size_t seg_floats = (size_t)std::min(ckpt_every, T) * s->substeps * s->D * (size_t)s->Ep;
-  const bool whole = nseg > 1 && nseg <= 65535 && whole_floats <= cap;
+  const bool whole = adj_whole(s, nseg, whole_floats, cap);
   if (!whole && seg_floats > cap)
     return fail(s, MG_ERR_INVALID,
                 "mg_adj_backward_noalloc: one segment's sub-step states (" +

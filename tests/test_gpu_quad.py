@@ -96,3 +96,38 @@ def test_quad_freeze_equals_one_env_per_lane(mgmod, mode):
     assert list(np.flatnonzero(flags)) == [5, 18]
     np.testing.assert_array_equal(traj, big[0][:, :, :40])
     assert list(stats[:, 3]) == [1, 1, 2, 2, 2, 2]
+
+
+def _grads(mg, classes, cls, x0, act, mult, g, S, K, mode, E):
+    sim = mg.Sim(classes, E, 0.005, S, env_class=cls[:E])
+    sim.reset(state=dev(x0[:, :E]), param_mult=dev(mult[:, :E]))
+    a = dev(act[:, :, :E])
+    traj = torch.full((act.shape[0], x0.shape[0], E), -1.0, device="cuda")
+    ckpt, _ = sim.adj_forward(a, K, traj=traj)
+    out = sim.adj_backward(ckpt, a, K, dev(g[:, :, :E]), traj=None if mode == "ckpt" else traj,
+                           noalloc=mode == "noalloc")
+    out = [host(v) for v in (ckpt, traj) + out] + [host(sim.get_state())]
+    sim.close()
+    return out
+
+
+@pytest.mark.parametrize("fleet,S,T,K,mode,sizes", [
+    ("heavy", 3, 5, 2, "ckpt", (1, 17, 16384)),
+    ("heavy", 2, 4, 4, "noalloc", (33,)),       # one segment, recomputed ahead of the sweep
+    ("bluerov2", 1, 7, 3, "traj", (16, 1001)),
+    ("three", 1, 4, 2, "ckpt", (49,)),
+    ("mixed", 2, 5, 2, "ckpt", (2, 1001)),
+    ("lag_and_not", 1, 5, 2, "traj", (1001,)),
+])
+def test_quad_adjoint_equals_one_env_per_lane(mgmod, fleet, S, T, K, mode, sizes):
+    """Checkpoints, trajectory, final state and every gradient, bitwise."""
+    classes = FLEETS[fleet]
+    cls, x0, act, mult = _inputs(classes, BIG, T, 31)
+    g = np.random.default_rng(35).standard_normal((T,) + x0.shape).astype(np.float32)
+    say("quad adjoint", fleet, S, T, K, mode)
+    big = _grads(mgmod, classes, cls, x0, act, mult, g, S, K, "ckpt", BIG)
+    for E in sizes:
+        say("  envs", E)
+        got = _grads(mgmod, classes, cls, x0, act, mult, g, S, K, mode, E)
+        for name, u, w in zip(("ckpt", "traj", "gact", "gtheta", "gx0", "state"), got, big):
+            np.testing.assert_array_equal(u, w[..., :E], err_msg=name)
