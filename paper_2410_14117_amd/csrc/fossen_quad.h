@@ -172,23 +172,27 @@ __device__ __forceinline__ void quad_wrench(const QuadThr& t, const float (&f)[2
 #undef MG_BC
 }
 
-// rhs_residual_m for a quad: kinematic rates kp (position), kq (TWICE q') and
-// the residual (rl, ra) of the state (q, v, w) with momentum (ml, ma) and
-// wrench (tl, ta).
-__device__ __forceinline__ void quad_residual(const QuadLane& L, const QuadConst& C, float q,
-                                              float v, float w, float ml, float ma, float tl,
-                                              float ta, float& kp, float& kq, float& rl,
-                                              float& ra) {
+// Kinematic rates of a quad: kp = R(q) v, kq = q (x) (0, w) (TWICE q').
+__device__ __forceinline__ void quad_kinematics(const QuadLane& L, float q, float v, float w,
+                                                float& kp, float& kq) {
   const float q0 = qperm<kQW>(q), q1 = qperm<kQRot1>(q), q2 = qperm<kQRot2>(q);
   const float v1 = qperm<kRot1>(v), v2 = qperm<kRot2>(v);
-  const float w1 = qperm<kRot1>(w);
   // lane 0 takes these two with a minus (q' of the scalar part); the other
   // lanes' second one is the component i + 2 of w
   const float w0 = qperm<MG_QP(3, 1, 2, 3)>(w) * L.sg, w2 = qperm<kRot2>(w) * L.sg;
   // t = 2 q_v x v
   const float th = fmaf(q1, v2, -(q2 * v1)), t = th + th;
   kp = fmaf(-q2, qperm<kRot1>(t), fmaf(q1, qperm<kRot2>(t), fmaf(q0, t, v)));
-  kq = fmaf(-q2, w1, fmaf(q1, w2, q0 * w0));
+  kq = fmaf(-q2, qperm<kRot1>(w), fmaf(q1, w2, q0 * w0));
+}
+
+// The residual (rl, ra) of rhs_residual_m for a quad: the state (q, v, w) with
+// momentum (ml, ma) and wrench (tl, ta).
+__device__ __forceinline__ void quad_forces(const QuadLane& L, const QuadConst& C, float q,
+                                            float v, float w, float ml, float ma, float tl,
+                                            float ta, float& rl, float& ra) {
+  const float v1 = qperm<kRot1>(v), v2 = qperm<kRot2>(v);
+  const float w1 = qperm<kRot1>(w), w2 = qperm<kRot2>(w) * L.sg;
   // k = R^T e3: x (2 qx) qz - (2 qy) qw, y (2 qy) qz + (2 qx) qw,
   //             z 1 - (2 qx) qx - (2 qy) qy
   const float k = fmaf(qperm<MG_QP(3, 3, 3, 2)>(q), qperm<MG_QP(0, 1, 2, 2)>(q) * L.kf,
@@ -202,6 +206,15 @@ __device__ __forceinline__ void quad_residual(const QuadLane& L, const QuadConst
   ra = fmaf(w2, qperm<kRot1>(ma), ra);
   ra = fmaf(qperm<kSwapXY>(k), C.hz, ra);
   ra = fmaf(-ea, w, ra);
+}
+
+// rhs_residual_m for a quad
+__device__ __forceinline__ void quad_residual(const QuadLane& L, const QuadConst& C, float q,
+                                              float v, float w, float ml, float ma, float tl,
+                                              float ta, float& kp, float& kq, float& rl,
+                                              float& ra) {
+  quad_kinematics(L, q, v, w, kp, kq);
+  quad_forces(L, C, q, v, w, ml, ma, tl, ta, rl, ra);
 }
 
 // (l, a) = base + A r (add_inv)
@@ -311,12 +324,20 @@ __device__ __forceinline__ void quad_substep(const QuadLane& L, const QuadConst&
   x.q = quad_normalise(q);
 }
 
-// begin_control_step and momentum: the command wrench (gl, ga), the lag wrench
-// (dl, da), the lag states at their end-of-control-step value, and M nu.
+// M nu
+__device__ __forceinline__ void quad_momentum(const QuadMass& M, float v, float w, float& ml,
+                                              float& ma) {
+  ml = fmaf(qperm<kSwapXY>(w), M.cl, M.l * v);
+  // the angular rows of M nu are written M_diag w + (coupling v)
+  ma = fmaf(M.a, w, qperm<kSwapXY>(v) * M.ca);
+}
+
+// begin_control_step: the command wrench (gl, ga), the lag wrench (dl, da) and
+// the lag states at their end-of-control-step value, f_cmd + decay (f - f_cmd).
 template <bool LAG>
-__device__ __forceinline__ void quad_begin(const QuadThr& t, const QuadMass& M,
-                                           const float (&act)[2], QuadState& x, float& gl,
-                                           float& ga, float& dl, float& da, float& ml, float& ma) {
+__device__ __forceinline__ void quad_command(const QuadThr& t, const float (&act)[2], float decay,
+                                             QuadState& x, float& gl, float& ga, float& dl,
+                                             float& da) {
   float fcmd[2];
   quad_thrust(t, act, fcmd);
   quad_wrench(t, fcmd, gl, ga);
@@ -325,13 +346,19 @@ __device__ __forceinline__ void quad_begin(const QuadThr& t, const QuadMass& M,
     if (t.lag) {
       const float df[2] = {x.f[0] - fcmd[0], x.f[1] - fcmd[1]};
       quad_wrench(t, df, dl, da);
-      x.f[0] = fmaf(t.rho_s, df[0], fcmd[0]);
-      x.f[1] = fmaf(t.rho_s, df[1], fcmd[1]);
+      x.f[0] = fmaf(decay, df[0], fcmd[0]);
+      x.f[1] = fmaf(decay, df[1], fcmd[1]);
     }
   }
-  ml = fmaf(qperm<kSwapXY>(x.w), M.cl, M.l * x.v);
-  // the angular rows of M nu are written M_diag w + (coupling v)
-  ma = fmaf(M.a, x.w, qperm<kSwapXY>(x.v) * M.ca);
+}
+
+// the same and M nu
+template <bool LAG>
+__device__ __forceinline__ void quad_begin(const QuadThr& t, const QuadMass& M,
+                                           const float (&act)[2], QuadState& x, float& gl,
+                                           float& ga, float& dl, float& da, float& ml, float& ma) {
+  quad_command<LAG>(t, act, t.rho_s, x, gl, ga, dl, da);
+  quad_momentum(M, x.v, x.w, ml, ma);
 }
 
 template <bool LAG>

@@ -22,7 +22,7 @@ struct QuadPlace {
   uint32_t ji, jc, oi, oc;   // 3-vector and quaternion rows, internal and caller
 };
 
-__device__ __forceinline__ QuadPlace quad_place(const QuadSegs& segs, const AdjArgs& a) {
+__device__ __forceinline__ QuadPlace quad_place(const ClassSegs& segs, const AdjArgs& a) {
   QuadPlace p;
   int k = 0;
   while (k + 1 < segs.n && (int)blockIdx.x >= segs.blk_end[k]) ++k;
@@ -82,7 +82,7 @@ __device__ __forceinline__ void quad_load_throttles(const AdjArgs& a, const Quad
 
 template <bool LAG>
 __global__ void __launch_bounds__(kQuadBlock) k_adj_quad_fwd(const AdjArgs a,
-                                                             const QuadSegs segs) {
+                                                             const ClassSegs segs) {
   const QuadPlace p = quad_place(segs, a);
   const ClassConst* __restrict__ cc = segs.cc + p.cls;
   const QuadLane L = quad_lane(threadIdx.x);
@@ -125,7 +125,7 @@ __global__ void __launch_bounds__(kQuadBlock) k_adj_quad_fwd(const AdjArgs a,
 // whole-rollout segbuf.  Position rows are left out: the sweep reads none.
 template <bool LAG>
 __global__ void __launch_bounds__(kQuadBlock) k_adj_quad_recompute(const AdjArgs a,
-                                                                   const QuadSegs segs) {
+                                                                   const ClassSegs segs) {
   const QuadPlace p = quad_place(segs, a);
   const ClassConst* __restrict__ cc = segs.cc + p.cls;
   const QuadLane L = quad_lane(threadIdx.x);
@@ -176,7 +176,7 @@ __global__ void __launch_bounds__(kQuadBlock) k_adj_quad_recompute(const AdjArgs
 // loaded one step ahead, so that a lone wave does not wait for them.
 template <bool LAG, bool TRAJ>
 __global__ void __launch_bounds__(kQuadBlock) __attribute__((amdgpu_waves_per_eu(2)))
-k_adj_quad_bwd(const AdjArgs a, const QuadSegs segs) {
+k_adj_quad_bwd(const AdjArgs a, const ClassSegs segs) {
   const QuadPlace p = quad_place(segs, a);
   const ClassConst* __restrict__ cc = segs.cc + p.cls;
   const QuadLane L = quad_lane(threadIdx.x);
@@ -264,7 +264,7 @@ k_adj_quad_bwd(const AdjArgs a, const QuadSegs segs) {
 // 32-bit offsets of a state's rows
 static bool quad_fits(const AdjArgs& a) { return a.Ep <= kQuadMaxEnvs && a.E <= kQuadMaxEnvs; }
 
-hipError_t launch_adj_quad_fwd(const QuadSegs& q, const AdjArgs& a, bool lag, hipStream_t s) {
+hipError_t launch_adj_quad_fwd(const ClassSegs& q, const AdjArgs& a, bool lag, hipStream_t s) {
   if (!quad_fits(a)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)q.blk_end[q.n - 1]);
   if (lag)
@@ -274,7 +274,7 @@ hipError_t launch_adj_quad_fwd(const QuadSegs& q, const AdjArgs& a, bool lag, hi
   return hipGetLastError();
 }
 
-hipError_t launch_adj_quad_recompute(const QuadSegs& q, const AdjArgs& a, bool lag,
+hipError_t launch_adj_quad_recompute(const ClassSegs& q, const AdjArgs& a, bool lag,
                                      hipStream_t s) {
   const int ny = (a.T + a.ckpt_every - 1) / a.ckpt_every;
   if (!quad_fits(a) || ny > 65535) return hipErrorInvalidValue;
@@ -286,7 +286,7 @@ hipError_t launch_adj_quad_recompute(const QuadSegs& q, const AdjArgs& a, bool l
   return hipGetLastError();
 }
 
-hipError_t launch_adj_quad_bwd(const QuadSegs& q, const AdjArgs& a, bool lag, hipStream_t s) {
+hipError_t launch_adj_quad_bwd(const ClassSegs& q, const AdjArgs& a, bool lag, hipStream_t s) {
   if (!quad_fits(a)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)q.blk_end[q.n - 1]), block(kQuadBlock);
   const bool traj = a.recomputed == 2;

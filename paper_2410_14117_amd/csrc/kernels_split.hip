@@ -8,8 +8,18 @@
 //   f  <- f + dt (f_cmd - f) / tau_thr;  a_prev <- a
 // Since C and g are linear in M and in (W, B), tau_h - C_RB nu - g_RB is the
 // coupled residual tau - C(M) nu - D nu - g of the fused step minus
-// M_A a_prev, so the residual code is shared.  One env per lane.
-#include "fossen_device.h"
+// M_A a_prev, so the residual code is shared.
+//
+// The lag step maps f - f_cmd to kappa (f - f_cmd), kappa = 1 - dt / tau_thr,
+// with the command held over a control step, so its wrench B (f - f_cmd) is
+// formed once per control step and carried, and the lag states are set to
+// their end-of-control-step value f_cmd + kappa^S (f - f_cmd) at its start:
+// nothing in a sub-step depends on the thrusters, so one kernel serves every
+// class and one launch all of them.
+//
+// One env per lane, or per quad of lanes (fossen_quad.h) for launches of at
+// most one wave per SIMD, which last as long as one env's chain.
+#include "fossen_quad.h"
 
 namespace mg {
 
@@ -20,10 +30,10 @@ struct RigidInv {
   float uu, vv, ww, pp, qq, rr, uq, vp;
 };
 
-__device__ __forceinline__ RigidInv rigid_inverse(const float* params, int64_t Ep, int64_t j,
+__device__ __forceinline__ RigidInv rigid_inverse(const float* params, int64_t Ep, uint32_t jo,
                                                   double zg) {
-  const double m = params[j], ix = params[Ep + j], iy = params[2 * Ep + j],
-               iz = params[3 * Ep + j];
+  const double m = lane_elem(params, jo), ix = lane_elem(params + Ep, jo),
+               iy = lane_elem(params + 2 * Ep, jo), iz = lane_elem(params + 3 * Ep, jo);
   const double mzz = mul_nc(mul_nc(m, zg), zg);
   const double mpp = ix + mzz, mqq = iy + mzz, muq = m * zg, mvp = -m * zg;
   const double det_uq = m * mqq - muq * muq, det_vp = m * mpp - mvp * mvp;
@@ -39,113 +49,234 @@ __device__ __forceinline__ RigidInv rigid_inverse(const float* params, int64_t E
   return I;
 }
 
+// Throttles past the class's are zero and so are their columns of B, so the
+// eight-thruster code gives the class's own results.
+__device__ __forceinline__ void load_throttles(int n, const float* af, int64_t E, uint32_t co,
+                                               float (&act)[kMaxThr]) {
+#pragma unroll
+  for (int i = 0; i < kMaxThr; ++i) act[i] = i < n ? lane_elem(af + i * E, co) : 0.0f;
+}
+
 }  // namespace
 
-template <int N, bool LAG>
-__global__ void __launch_bounds__(kBlock) k_split(const SplitArgs a, const ClassConst cc) {
-  constexpr int D = Dims<N, LAG>::D;
-  const int64_t local = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (local >= a.seg_len) return;
-  if (!MG_CHECK(a, a.seg_start + a.seg_len <= a.Ep, kDbgSegment)) return;
-  const int64_t j = a.seg_start + local;
-  const int64_t c = a.perm ? (int64_t)a.perm[j] : j;
+// VALU-bound: 131 instructions per sub-step (211 with 8 thrusters before the lag
+// wrench was carried) and 300-400 per control step.  Three waves per SIMD; held
+// to four it spills inside the loop (4-20 times slower).  Lagged Heavies, 10
+// control steps of 16 sub-steps, before and now: 32 768 envs 74 -> 68 us, 131 072
+// 109 -> 99 us, 524 288 400 -> 358 us.
+template <bool LAG>
+__global__ void __launch_bounds__(kBlock)
+k_split(const SplitArgs a, const ClassSegs segs) {
+  constexpr int D = LAG ? 13 + kMaxThr : 13;
+  int k = 0;
+  while (k + 1 < segs.n && (int)blockIdx.x >= segs.blk_end[k]) ++k;
+  const int blk0 = k > 0 ? segs.blk_end[k - 1] : 0;
+  const ClassConst* __restrict__ cc = segs.cc + k;
+  const int64_t local = (int64_t)((int)blockIdx.x - blk0) * kBlock + threadIdx.x;
+  if (local >= segs.len[k]) return;
+  if (!MG_CHECK(a, segs.start[k] + segs.len[k] <= a.Ep, kDbgSegment)) return;
+  const int64_t j = segs.start[k] + local;
+  const uint32_t jo = (uint32_t)j * 4u;
+  const int64_t c = a.perm ? (int64_t)lane_elem(a.perm, jo) : j;
   if (!MG_CHECK(a, c >= 0 && c < a.dbg.cols, kDbgColumn)) return;
+  const uint32_t co = (uint32_t)c * 4u;
+  const int Dc = 13 + (cc->lag ? cc->n_thr : 0);     // this class's rows
   float x[D], acc[6], ma[6];
 #pragma unroll
-  for (int i = 0; i < D; ++i) x[i] = a.state[i * a.Ep + j];
+  for (int i = 0; i < D; ++i) x[i] = i < 13 || i < Dc ? lane_elem(a.state + i * a.Ep, jo) : 0.0f;
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
-    acc[i] = a.acc[i * a.Ep + j];
-    ma[i] = a.params[(4 + i) * a.Ep + j];
+    acc[i] = lane_elem(a.acc + i * a.Ep, jo);
+    ma[i] = lane_elem(a.params + (4 + i) * a.Ep, jo);
   }
-  const EnvConst P = load_env_const(a.derived, a.Ep, j);
-  const RigidInv I = rigid_inverse(a.params, a.Ep, j, a.zg);
-  const float dt = a.dt, hdt = 0.5f * a.dt, kdt = a.dt * cc.inv_tau;
+  const EnvConst P = load_env_const_off(a.derived, a.Ep, jo);
+  const RigidInv I = rigid_inverse(a.params, a.Ep, jo, a.nominal[k].zg);
+  const float dt = to_vgpr(a.dt), hdt = to_vgpr(0.5f * a.dt), kappa = to_vgpr(cc->kappa);
+  // each control step's throttles are loaded one step ahead: loads and stores
+  // complete in order, so a load behind the trajectory's stores would wait for
+  // them at every control step
+  const int64_t frame = (int64_t)a.n_max * a.E;
+  float nxt[kMaxThr];
+  load_throttles(cc->n_thr, a.actions, a.E, co, nxt);
   for (int t = 0; t < a.n_ctrl; ++t) {
-    const float* af = a.actions + (int64_t)t * a.n_max * a.E + c;
-    float act[N], fcmd[N], gcmd[6];
+    float fcmd[kMaxThr], gcmd[6], dg[6];
+    thrust_command<kMaxThr>(*cc, nxt, fcmd);
+    command_wrench<kMaxThr>(*cc, fcmd, gcmd);
+    if (t + 1 < a.n_ctrl)
+      load_throttles(cc->n_thr, a.actions + (int64_t)(t + 1) * frame, a.E, co, nxt);
 #pragma unroll
-    for (int i = 0; i < N; ++i) act[i] = af[i * a.E];
-    thrust_command<N>(cc, act, fcmd);
-    command_wrench<N>(cc, fcmd, gcmd);
+    for (int i = 0; i < 6; ++i) dg[i] = 0.0f;
+    if constexpr (LAG) {
+      if (cc->lag) begin_control_step<kMaxThr, true>(*cc, x, fcmd, dg, cc->kappa_s);
+    }
     for (int s = 0; s < a.substeps; ++s) {
-      float tau[6];
-      if constexpr (LAG) {
-        float dg[6];
-        lag_wrench<N>(cc, x, fcmd, dg);
+      float tau[6], kin[7], r[6], mom[6];
 #pragma unroll
-        for (int k = 0; k < 6; ++k) tau[k] = gcmd[k] + dg[k];
-      } else {
-#pragma unroll
-        for (int k = 0; k < 6; ++k) tau[k] = gcmd[k];
+      for (int i = 0; i < 6; ++i) {
+        tau[i] = LAG ? gcmd[i] + dg[i] : gcmd[i];
+        if constexpr (LAG) dg[i] = mul_nc(dg[i], kappa);
       }
-      float kin[7], r[6];
-      rhs_residual(x, kin, r, P, tau);
+      momentum(P, x + 7, mom);
+      rhs_residual_m(x, mom, kin, r, P, tau);
 #pragma unroll
-      for (int k = 0; k < 6; ++k) r[k] = fma_t(-ma[k], acc[k], r[k]);
+      for (int i = 0; i < 6; ++i) r[i] = fma_t(-ma[i], acc[i], r[i]);
       acc[0] = fma_t(I.uq, r[4], I.uu * r[0]);
       acc[1] = fma_t(I.vp, r[3], I.vv * r[1]);
-      acc[2] = I.ww * r[2];
+      acc[2] = mul_nc(I.ww, r[2]);
       acc[3] = fma_t(I.pp, r[3], I.vp * r[1]);
       acc[4] = fma_t(I.qq, r[4], I.uq * r[0]);
-      acc[5] = I.rr * r[5];
+      acc[5] = mul_nc(I.rr, r[5]);
 #pragma unroll
-      for (int k = 0; k < 6; ++k) x[7 + k] = fma_t(dt, acc[k], x[7 + k]);
-      // p += dt R(q) v with R(q) v = v + q_w t + q_v x t, t = 2 q_v x v
-      const float qw = x[3], qx = x[4], qy = x[5], qz = x[6];
-      const float u = x[7], v = x[8], w = x[9], p = x[10], q = x[11], rr = x[12];
-      const float t0 = 2.0f * (qy * w - qz * v), t1 = 2.0f * (qz * u - qx * w),
-                  t2 = 2.0f * (qx * v - qy * u);
-      x[0] = fma_t(dt, u + qw * t0 + (qy * t2 - qz * t1), x[0]);
-      x[1] = fma_t(dt, v + qw * t1 + (qz * t0 - qx * t2), x[1]);
-      x[2] = fma_t(dt, w + qw * t2 + (qx * t1 - qy * t0), x[2]);
-      // q += dt/2 q (x) (0, omega), then renormalise
-      const float nw = fma_t(-hdt, qx * p + qy * q + qz * rr, qw);
-      const float nx = fma_t(hdt, qw * p + qy * rr - qz * q, qx);
-      const float ny = fma_t(hdt, qw * q + qz * p - qx * rr, qy);
-      const float nz = fma_t(hdt, qw * rr + qx * q - qy * p, qz);
-      const float inv = rsqrt_t(nw * nw + nx * nx + ny * ny + nz * nz);
-      x[3] = nw * inv;
-      x[4] = nx * inv;
-      x[5] = ny * inv;
-      x[6] = nz * inv;
-      if constexpr (LAG) {
+      for (int i = 0; i < 6; ++i) x[7 + i] = fma_t(dt, acc[i], x[7 + i]);
+      // kinematics at the new velocities: p += dt R(q) v, q += dt/2 q (x) (0, w)
+      rhs_residual_m(x, mom, kin, r, P, tau);
 #pragma unroll
-        for (int i = 0; i < N; ++i) x[13 + i] = fma_t(kdt, fcmd[i] - x[13 + i], x[13 + i]);
-      }
+      for (int i = 0; i < 3; ++i) x[i] = fma_t(dt, kin[i], x[i]);
+#pragma unroll
+      for (int i = 3; i < 7; ++i) x[i] = fma_t(hdt, kin[i], x[i]);
+      const float inv = rsqrt_t(
+          fma_t(x[6], x[6], fma_t(x[5], x[5], fma_t(x[3], x[3], x[4] * x[4]))));
+#pragma unroll
+      for (int i = 3; i < 7; ++i) x[i] *= inv;
     }
     if (a.traj) {
-      float* tf = a.traj + (int64_t)t * a.D * a.E + c;
+      float* tf = a.traj + (int64_t)t * a.D * a.E;
 #pragma unroll
-      for (int i = 0; i < D; ++i) tf[i * a.E] = x[i];
-      for (int i = D; i < a.D; ++i) tf[i * a.E] = 0.0f;
+      for (int i = 0; i < D; ++i)
+        if (i < a.D) lane_elem(tf + i * a.E, co) = x[i];
+      for (int i = D; i < a.D; ++i) lane_elem(tf + i * a.E, co) = 0.0f;
     }
   }
 #pragma unroll
-  for (int i = 0; i < D; ++i) a.state[i * a.Ep + j] = x[i];
+  for (int i = 0; i < D; ++i)
+    if (i < 13 || i < Dc) lane_elem(a.state + i * a.Ep, jo) = x[i];
 #pragma unroll
-  for (int i = 0; i < 6; ++i) a.acc[i * a.Ep + j] = acc[i];
+  for (int i = 0; i < 6; ++i) lane_elem(a.acc + i * a.Ep, jo) = acc[i];
 }
 
-template <int N, bool LAG>
-static hipError_t launch_split_t(const ClassConst& cc, const SplitArgs& a, hipStream_t s) {
-  const int64_t nblk = (a.seg_len + kBlock - 1) / kBlock;
-  if (nblk == 0) return hipSuccess;
-  hipLaunchKernelGGL((k_split<N, LAG>), dim3((unsigned)nblk), dim3(kBlock), 0, s, a, cc);
-  return hipGetLastError();
-}
+#pragma clang fp contract(off)
 
-hipError_t launch_split(const ClassConst& cc, const SplitArgs& a, hipStream_t s) {
-  const bool lag = cc.lag != 0;
-#define MG_CASE(n)                                                               \
-  case n:                                                                        \
-    return lag ? launch_split_t<n, true>(cc, a, s) : launch_split_t<n, false>(cc, a, s);
-  switch (cc.n_thr) {
-    MG_CASE(1) MG_CASE(2) MG_CASE(3) MG_CASE(4) MG_CASE(5) MG_CASE(6) MG_CASE(7) MG_CASE(8)
-    default:
-      return hipErrorInvalidValue;
+// The same with one env per quad of lanes, bitwise: launches of at most one
+// wave per SIMD (16 384 envs: 71 -> 43 us, 1000 envs: 69 -> 36 us as above; at
+// two waves per SIMD it would be level with one env per lane).
+template <bool LAG>
+__global__ void __launch_bounds__(kQuadBlock) k_split_quad(const SplitArgs a,
+                                                           const ClassSegs segs) {
+  int k = 0;
+  while (k + 1 < segs.n && (int)blockIdx.x >= segs.blk_end[k]) ++k;
+  const int blk0 = k > 0 ? segs.blk_end[k - 1] : 0;
+  const ClassConst* __restrict__ cc = segs.cc + k;
+  const QuadLane L = quad_lane(threadIdx.x);
+  const int c = L.c, ci = c > 1 ? c - 1 : 0;
+  // the four lanes of a quad share every condition below
+  const int64_t local = (int64_t)((int)blockIdx.x - blk0) * kQuadEnvs + (threadIdx.x >> 2);
+  bool active = local < segs.len[k] &&
+                MG_CHECK(a, segs.start[k] + segs.len[k] <= a.Ep, kDbgSegment);
+  const uint32_t j4 = (uint32_t)(segs.start[k] + (active ? local : 0)) * 4u;
+  const int64_t col = active ? (a.perm ? (int64_t)lane_elem(a.perm, j4) : (int64_t)(j4 / 4u)) : 0;
+  active = active && MG_CHECK(a, col >= 0 && col < a.dbg.cols, kDbgColumn);
+  const uint32_t c4 = active ? (uint32_t)col * 4u : 0u;
+  const uint32_t s4 = (uint32_t)a.Ep * 4u, e4 = (uint32_t)a.E * 4u;
+  const uint32_t ji = j4 + (uint32_t)ci * s4, jc = j4 + (uint32_t)c * s4;   // internal rows
+  const uint32_t oi = c4 + (uint32_t)ci * e4, oc = c4 + (uint32_t)c * e4;   // caller rows
+  QuadThr th;
+  load_quad_thr(cc, c, th);
+  const int n_f = th.lag ? th.n : 0;
+  const bool f0 = c < n_f, f1 = c + 4 < n_f;
+  QuadState x;
+  x.p = lane_elem(a.state, ji);
+  x.q = lane_elem(a.state + 3 * a.Ep, jc);
+  x.v = lane_elem(a.state + 7 * a.Ep, ji);
+  x.w = lane_elem(a.state + 10 * a.Ep, ji);
+  x.f[0] = f0 ? lane_elem(a.state + 13 * a.Ep, jc) : 0.0f;
+  x.f[1] = f1 ? lane_elem(a.state + 17 * a.Ep, jc) : 0.0f;
+  float al = lane_elem(a.acc, ji), aa = lane_elem(a.acc + 3 * a.Ep, ji);
+  const float mal = lane_elem(a.params + 4 * a.Ep, ji), maa = lane_elem(a.params + 7 * a.Ep, ji);
+  QuadConst C;
+  QuadMass M;
+  load_quad_const(a.derived, a.Ep, j4, c, 1.0f, C, M);
+  const RigidInv I = rigid_inverse(a.params, a.Ep, j4, a.nominal[k].zg);
+  const float il = c == 1 ? I.uu : (c == 2 ? I.vv : I.ww);
+  const float ia = c == 1 ? I.pp : (c == 2 ? I.qq : I.rr);
+  const float icl = c == 1 ? I.uq : (c == 2 ? I.vp : 0.0f);
+  const float ica = c == 1 ? I.vp : (c == 2 ? I.uq : 0.0f);
+  const float dt = to_vgpr(a.dt), hdt = to_vgpr(0.5f * a.dt), kappa = to_vgpr(cc->kappa);
+  const int64_t frame = (int64_t)a.n_max * a.E;
+  float nxt[2];   // throttles, loaded one control step ahead
+  nxt[0] = c < th.n ? lane_elem(a.actions, oc) : 0.0f;
+  nxt[1] = c + 4 < th.n ? lane_elem(a.actions + 4 * a.E, oc) : 0.0f;
+  for (int t = 0; t < a.n_ctrl; ++t) {
+    const float act[2] = {nxt[0], nxt[1]};
+    if (t + 1 < a.n_ctrl) {
+      const float* af = a.actions + (int64_t)(t + 1) * frame;
+      nxt[0] = c < th.n ? lane_elem(af, oc) : 0.0f;
+      nxt[1] = c + 4 < th.n ? lane_elem(af + 4 * a.E, oc) : 0.0f;
+    }
+    float gl, ga, dl, da;
+    quad_command<LAG>(th, act, cc->kappa_s, x, gl, ga, dl, da);
+    for (int s = 0; s < a.substeps; ++s) {
+      const float tl = LAG ? gl + dl : gl, ta = LAG ? ga + da : ga;
+      if constexpr (LAG) {
+        dl *= kappa;
+        da *= kappa;
+      }
+      float ml, ma, rl, ra, kp, kq;
+      quad_momentum(M, x.v, x.w, ml, ma);
+      quad_forces(L, C, x.q, x.v, x.w, ml, ma, tl, ta, rl, ra);
+      rl = fmaf(-mal, al, rl);
+      ra = fmaf(-maa, aa, ra);
+      al = fmaf(qperm<kSwapXY>(ra), icl, il * rl);
+      aa = fmaf(ia, ra, qperm<kSwapXY>(rl) * ica);
+      x.v = fmaf(dt, al, x.v);
+      x.w = fmaf(dt, aa, x.w);
+      quad_kinematics(L, x.q, x.v, x.w, kp, kq);
+      x.p = fmaf(dt, kp, x.p);
+      x.q = quad_normalise(fmaf(hdt, kq, x.q));
+    }
+    if (a.traj && active) {
+      float* tf = a.traj + (int64_t)t * a.D * a.E;
+      lane_elem(tf + 3 * a.E, oc) = x.q;
+      if (c > 0) {
+        lane_elem(tf, oi) = x.p;
+        lane_elem(tf + 7 * a.E, oi) = x.v;
+        lane_elem(tf + 10 * a.E, oi) = x.w;
+      }
+      if (13 + c < a.D) lane_elem(tf + 13 * a.E, oc) = f0 ? x.f[0] : 0.0f;
+      if (17 + c < a.D) lane_elem(tf + 17 * a.E, oc) = f1 ? x.f[1] : 0.0f;
+    }
   }
-#undef MG_CASE
+  if (!active) return;
+  lane_elem(a.state + 3 * a.Ep, jc) = x.q;
+  if (c > 0) {
+    lane_elem(a.state, ji) = x.p;
+    lane_elem(a.state + 7 * a.Ep, ji) = x.v;
+    lane_elem(a.state + 10 * a.Ep, ji) = x.w;
+    lane_elem(a.acc, ji) = al;
+    lane_elem(a.acc + 3 * a.Ep, ji) = aa;
+  }
+  if (f0) lane_elem(a.state + 13 * a.Ep, jc) = x.f[0];
+  if (f1) lane_elem(a.state + 17 * a.Ep, jc) = x.f[1];
+}
+
+#pragma clang fp contract(fast)
+
+hipError_t launch_split(const ClassSegs& segs, const SplitArgs& a, bool lag, bool quad,
+                        hipStream_t s) {
+  const int nblk = segs.blk_end[segs.n - 1];
+  if (nblk == 0) return hipSuccess;
+  // 32-bit lane offsets: one row, or (quad) every row at once
+  const int64_t most = quad ? kQuadMaxEnvs : (int64_t)1 << 30;
+  if (a.Ep > most || a.E > most) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)nblk);
+  if (quad && lag)
+    hipLaunchKernelGGL((k_split_quad<true>), grid, dim3(kQuadBlock), 0, s, a, segs);
+  else if (quad)
+    hipLaunchKernelGGL((k_split_quad<false>), grid, dim3(kQuadBlock), 0, s, a, segs);
+  else if (lag)
+    hipLaunchKernelGGL((k_split<true>), grid, dim3(kBlock), 0, s, a, segs);
+  else
+    hipLaunchKernelGGL((k_split<false>), grid, dim3(kBlock), 0, s, a, segs);
+  return hipGetLastError();
 }
 
 }  // namespace mg

@@ -187,7 +187,7 @@ __device__ __forceinline__ double quad_sum(double x) {
 }
 
 template <bool LAG, bool EACH>
-__global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, const QuadSegs segs) {
+__global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, const ClassSegs segs) {
   int k = 0;
   while (k + 1 < segs.n && (int)blockIdx.x >= segs.blk_end[k]) ++k;
   const int blk0 = k > 0 ? segs.blk_end[k - 1] : 0;
@@ -317,7 +317,7 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
   }
 }
 
-hipError_t launch_step_quad(const QuadSegs& q, const StepArgs& a, bool lag, bool each_step,
+hipError_t launch_step_quad(const ClassSegs& q, const StepArgs& a, bool lag, bool each_step,
                             hipStream_t s) {
   const int nblk = q.blk_end[q.n - 1];
   if (nblk == 0) return hipSuccess;

@@ -47,6 +47,9 @@ struct ClassConst {
   int32_t thr_map;       // 0 linear, 1 quadratic
   int32_t lag;
   float rho_s;           // rho^S for the owner's S sub-steps per control step
+  // the same for the split scheme's semi-implicit Euler step of the lag: one
+  // sub-step maps f - f_cmd to kappa (f - f_cmd), kappa = 1 - z
+  float kappa, kappa_s;
 };
 
 // Class constants for sub-steps of dt, S sub-steps per control step.  The
@@ -100,6 +103,17 @@ __device__ __forceinline__ bool dbg_check(const DebugArgs& d, bool ok, uint32_t 
 #define MG_CHECK(args, ok, bit) true
 #define MG_SET_DBG(args, value) ((void)0)
 #endif
+
+// The classes' segments of one launch over all of them: block b belongs to the
+// first class k with b < blk_end[k] (kBlock envs per block with one env per
+// lane, kQuadEnvs with one env per quad of lanes).
+struct ClassSegs {
+  const ClassConst* cc;        // device [n]
+  int32_t n;
+  int32_t blk_end[MG_MAX_CLASSES];
+  int64_t start[MG_MAX_CLASSES], len[MG_MAX_CLASSES];
+  float zb[MG_MAX_CLASSES];    // z_b of the class (dL/dB through h_z)
+};
 
 struct StepArgs {
   float* state;                // internal [D][Ep]
@@ -184,12 +198,11 @@ struct SplitArgs {
   float* acc;                  // internal [6][Ep] previous sub-step's acceleration
   int64_t Ep, E;
   const int32_t* perm;
-  int64_t seg_start, seg_len;
+  const ClassNominal* nominal; // device [n_classes]
   const float* actions;        // caller [n_ctrl][n_max][E]
   int32_t n_max, D, n_ctrl, substeps;
   float* traj;                 // caller [n_ctrl][D][E] or NULL
   float dt;
-  double zg;                   // this class's CG height below the CO
   MG_DBG_FIELD
 };
 
@@ -281,34 +294,26 @@ hipError_t launch_serve_leave(const ServeGatherItem* items, int32_t n_items, Ser
                               int32_t Dmax, const DebugArgs& dbg, hipStream_t s);
 
 // ---- one env per quad of lanes (fossen_quad.h) ------------------------------
-// The classes' segments of one launch over all of them: block b belongs to the
-// first class k with b < blk_end[k] (kQuadBlock / 4 envs per block).
 constexpr int kQuadBlock = 64;                  // one wave
-constexpr int kQuadEnvs = kQuadBlock / 4;
+constexpr int kQuadEnvs = kQuadBlock / 4;       // envs per block
 // Caller rows and internal rows of the quad kernels are addressed with 32-bit
 // byte offsets (every row of a state or of the constants at once).
 constexpr int64_t kQuadMaxEnvs = (int64_t)1 << 20;
-struct QuadSegs {
-  const ClassConst* cc;        // device [n]
-  int32_t n;
-  int32_t blk_end[MG_MAX_CLASSES];
-  int64_t start[MG_MAX_CLASSES], len[MG_MAX_CLASSES];
-  float zb[MG_MAX_CLASSES];    // z_b of the class (dL/dB through h_z)
-};
+
 // StepArgs with seg_start, seg_len and blk_off unused (nblk_total: blocks of
 // this launch); each_step: an env whose state is non-finite after a control
 // step is frozen at that step's input, as one launch per control step would,
 // else at the launch's input.
-hipError_t launch_step_quad(const QuadSegs& q, const StepArgs& a, bool lag, bool each_step,
+hipError_t launch_step_quad(const ClassSegs& q, const StepArgs& a, bool lag, bool each_step,
                             hipStream_t s);
 
 // The adjoint's kernels with one env per quad of lanes, all classes in one
 // launch (kernels_adjoint_quad.hip; seg_start, seg_len and zb of AdjArgs unused):
 // the forward, the recomputation of every segment's sub-step inputs into the
 // whole-rollout segbuf, and the reverse sweep (a.recomputed 1 or 2).
-hipError_t launch_adj_quad_fwd(const QuadSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
-hipError_t launch_adj_quad_recompute(const QuadSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
-hipError_t launch_adj_quad_bwd(const QuadSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
+hipError_t launch_adj_quad_fwd(const ClassSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
+hipError_t launch_adj_quad_recompute(const ClassSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
+hipError_t launch_adj_quad_bwd(const ClassSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
 
 // launchers (kernels_adjoint.hip)
 hipError_t launch_adjoint(bool backward, const ClassConst& cc, const AdjArgs& a, hipStream_t s);
@@ -321,7 +326,9 @@ hipError_t launch_stats_finalize(const double* partials, int32_t nblk, int32_t n
                                  double* stats, hipStream_t s);
 hipError_t launch_reset(const ResetArgs& a, hipStream_t s);
 hipError_t launch_task(const ClassConst& cc, const TaskConst& tc, const TaskArgs& a, hipStream_t s);
-hipError_t launch_split(const ClassConst& cc, const SplitArgs& a, hipStream_t s);
+// all classes in one launch, one env per lane or (quad) per quad of lanes
+hipError_t launch_split(const ClassSegs& segs, const SplitArgs& a, bool lag, bool quad,
+                        hipStream_t s);
 // out[r][perm[j]] = in[r][j] for rows r < rows (internal -> caller order)
 // status flags to caller order int32 [E]; flags &= mask for n envs
 hipError_t launch_flags_out(const uint8_t* flags, int32_t* out, int64_t E, const int32_t* perm,

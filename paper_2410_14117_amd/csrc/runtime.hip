@@ -96,7 +96,8 @@ struct mg_sim {
   std::vector<int32_t> seg_blk_off;
   // one env per quad of lanes, all classes in one launch (small sims)
   bool quad_on = false, any_lag = false;
-  QuadSegs quad{};
+  ClassSegs quad{};
+  ClassSegs lanes{};           // all classes in one launch, one env per lane
 
   float* state = nullptr;      // [D][Ep]
   float* params = nullptr;     // [23][Ep]
@@ -145,6 +146,8 @@ ClassConst mg::make_class_const(const mg_vehicle& v, double dt, int substeps) {
   c.sigma4 = (float)(1.0 - z + z * z / 2 - z * z * z / 4);
   c.rho = (float)rho;
   c.rho_s = (float)std::pow(rho, (double)substeps);
+  c.kappa = (float)(1.0 - z);
+  c.kappa_s = (float)std::pow(1.0 - z, (double)substeps);
   c.n_thr = v.n_thr;
   c.thr_map = v.thr_map;
   c.lag = v.thr_tau > 0.0 ? 1 : 0;
@@ -661,6 +664,9 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
     s->quad.len[k] = count[k];
     s->quad.zb[k] = (float)s->nominal[k].zb;
   }
+  s->lanes = s->quad;
+  for (int k = 0; k < cfg->n_classes; ++k)
+    s->lanes.blk_end[k] = k + 1 < cfg->n_classes ? s->seg_blk_off[k + 1] : blk;
   s->quad_on = s->Ep <= kQuadMaxEnvs && quad_blk <= (int64_t)n_cu * 4 * MG_QUAD_WAVES;
   std::vector<int32_t> perm(s->Ep, -1), iperm(E);
   std::vector<uint8_t> cls(s->Ep, 0);
@@ -713,7 +719,7 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
     (void)hipGetLastError();
     return bail(MG_ERR_DEVICE, "device initialisation failed in mg_create");
   }
-  s->quad.cc = s->cc_dev;
+  s->quad.cc = s->lanes.cc = s->cc_dev;
   // the debug build's failed-check word; MG_DEBUG_SHRINK=k (read here, debug
   // build only) makes the kernels treat caller columns >= E - k as out of
   // bounds, so that a test can see the checks fire while every access stays in
@@ -898,21 +904,8 @@ mg_status mg_step_split(mg_sim* s, const float* actions, int32_t n_ctrl, float* 
   a.substeps = s->substeps;
   a.traj = traj;
   a.dt = (float)s->dt;
-  hipStream_t st0 = s->stream;
-  for (int k = 1; k < s->n_classes; ++k) {
-    MG_HIP(s, hipEventRecord(s->ev_fork[k - 1], st0));
-    MG_HIP(s, hipStreamWaitEvent(s->aux[k - 1], s->ev_fork[k - 1], 0));
-  }
-  for (int k = 0; k < s->n_classes; ++k) {
-    a.seg_start = s->seg_start[k];
-    a.seg_len = s->seg_len[k];
-    a.zg = s->nominal[k].zg;
-    MG_HIP(s, launch_split(s->cc[k], a, k == 0 ? st0 : s->aux[k - 1]));
-  }
-  for (int k = 1; k < s->n_classes; ++k) {
-    MG_HIP(s, hipEventRecord(s->ev_join[k - 1], s->aux[k - 1]));
-    MG_HIP(s, hipStreamWaitEvent(st0, s->ev_join[k - 1], 0));
-  }
+  a.nominal = s->nominal_dev;
+  MG_HIP(s, launch_split(s->quad_on ? s->quad : s->lanes, a, s->any_lag, s->quad_on, s->stream));
   return MG_OK;
 }
 

@@ -340,7 +340,7 @@ class Sim:
 
     def step_split(self, actions, traj=None):
         """actions [n_ctrl][N_max][E]: n_ctrl control steps of the split scheme of Sec. II
-        in one launch per class (see mg_step_split)."""
+        in one launch (see mg_step_split)."""
         import torch
         n_ctrl = int(actions.shape[0])
         E, D, N = self.n_envs, self.state_dim, self.action_dim

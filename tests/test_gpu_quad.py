@@ -12,7 +12,7 @@ torch = pytest.importorskip("torch")
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 sys.path.insert(0, ROOT)
 
-from tests.gpu_util import dev, host, say                                  # noqa: E402
+from tests.gpu_util import TOL_ONE_STEP, dev, host, rel_err, say                                  # noqa: E402
 from workloads import (BLUEROV2, BLUEROV2_HEAVY, actions, param_multipliers,   # noqa: E402
                        random_states, vehicle_variant)
 
@@ -131,3 +131,38 @@ def test_quad_adjoint_equals_one_env_per_lane(mgmod, fleet, S, T, K, mode, sizes
         got = _grads(mgmod, classes, cls, x0, act, mult, g, S, K, mode, E)
         for name, u, w in zip(("ckpt", "traj", "gact", "gtheta", "gx0", "state"), got, big):
             np.testing.assert_array_equal(u, w[..., :E], err_msg=name)
+
+
+@pytest.mark.parametrize("fleet,S,T,sizes", [
+    ("heavy", 4, 3, (1, 17, 16384)),
+    ("bluerov2", 1, 5, (33,)),
+    ("three", 2, 3, (49,)),
+    ("lag_and_not", 3, 4, (2, 1001)),
+])
+def test_split_of_all_classes_in_one_launch(mgmod, oracle, fleet, S, T, sizes):
+    """The split scheme with one env per lane and one per quad of lanes: bitwise equal over two
+    calls (the second from carried accelerations), and within the one-step tolerance of the
+    oracle for each class's own thrusters."""
+    classes = [dict(v, added_mass=[0.4 * m for m in v["added_mass"]]) for v in FLEETS[fleet]]
+    cls, x0, act, mult = _inputs(classes, BIG, 2 * T, 41)
+    say("split", fleet, S, T)
+
+    def run(E):
+        sim = mgmod.Sim(classes, E, 0.005, S, env_class=cls[:E])
+        sim.reset(state=dev(x0[:, :E]), param_mult=dev(mult[:, :E]))
+        traj = torch.full((2 * T, x0.shape[0], E), -1.0, device="cuda")
+        sim.step_split(dev(act[:T, :, :E]), traj=traj[:T])
+        sim.step_split(dev(act[T:, :, :E]), traj=traj[T:])
+        out = host(traj), host(sim.get_state())
+        sim.close()
+        return out
+
+    big = run(BIG)
+    for E in sizes:
+        say("  envs", E)
+        for u, w in zip(run(E), big):
+            np.testing.assert_array_equal(u, w[..., :E])
+    sub = np.r_[0:8, BIG - 5:BIG]
+    ref = oracle.split_rollout(classes, x0[:, sub], act[:1][:, :, sub], S, 0.005,
+                               env_class=cls[sub], mult=mult[:, sub], want_traj=True)
+    assert rel_err(big[0][0][:, sub], ref["traj"][0]) <= TOL_ONE_STEP
