@@ -203,7 +203,8 @@ mg_status mg_get_flags(mg_sim* sim, int32_t* out, int32_t out_on_device);
 int32_t mg_debug_build(void);
 mg_status mg_debug_word(mg_sim* sim, uint32_t* word, int32_t clear);
 
-/* Advances every env by n_ctrl control steps in ONE fused launch per class:
+/* Advances every env by n_ctrl control steps in ONE fused launch (one per class
+ * where some classes have a thruster lag and some have none):
  * each control step reads one throttle frame, holds it for `substeps` RK4
  * sub-steps, and the state stays in registers across all n_ctrl * substeps
  * sub-steps (Sec. II: several sub-simulation steps per simulation step).
@@ -238,11 +239,12 @@ mg_status mg_step_plain(mg_sim* sim, const float* actions, int32_t n_ctrl, const
                         float* traj, double* stats);
 /* A sequence of T Gym-style steps (Sec. III) of every env with its
  * throttles (Eq. (3)) given up front, each of `substeps` sub-steps (Sec. II):
- * T control steps as T launches per class (plain != 0: T * substeps
- * launches), replayed from a HIP graph that is captured on first use and
- * cached for this exact argument tuple (at most 64 tuples per sim; the 65th
- * empties the cache, after waiting for the sim's stream).  Arguments as
- * mg_step with n_ctrl = T. */
+ * T control steps in one launch, with the results of T mg_step calls.  With
+ * plain != 0 (T * substeps launches per class), or where some classes have a
+ * thruster lag and some have none (T launches per class), the launches are
+ * replayed from a HIP graph that is captured on first use and cached for this
+ * exact argument tuple (at most 64 tuples per sim; the 65th empties the cache,
+ * after waiting for the sim's stream).  Arguments as mg_step with n_ctrl = T. */
 mg_status mg_rollout(mg_sim* sim, const float* actions, int32_t T, const float* targets,
                      float* traj, double* stats, int32_t plain);
 /* Reads back eta and nu of Eq. (1) (Sec. II) with the thruster states: copies

@@ -198,6 +198,12 @@ __device__ __forceinline__ T* pin_sgpr(T* p) {
   asm volatile("" : "+s"(v));
   return reinterpret_cast<T*>(v);
 }
+// The same for a row stride: the rows' offsets are then formed where the pinned
+// value is used instead of being held in scalar registers from another use on.
+__device__ __forceinline__ int64_t pin_sgpr(int64_t v) {
+  asm volatile("" : "+s"(v));
+  return v;
+}
 template <class T>
 __device__ __forceinline__ __attribute__((address_space(1))) T& lane_elem(T* row, uint32_t off) {
   using G = __attribute__((address_space(1))) char;
@@ -231,6 +237,47 @@ __device__ __forceinline__ EnvConst load_env_const_off(const float* __restrict__
   P.wmb = lane_elem(der + kWmB * Ep, off);
   P.hz = lane_elem(der + kHz * Ep, off);
   return P;
+}
+
+// One class's constants as scalars, for a kernel that takes its class from its
+// block: read through the constant address space (nothing writes them while a
+// sim exists), which makes them scalar loads; through a plain pointer the
+// compiler must allow for the kernel's own stores and reads them anew into
+// vector registers at every control step.
+__device__ __forceinline__ ClassConst scalar_class_const(const ClassConst* p) {
+  using W = const __attribute__((address_space(4))) uint32_t;
+  constexpr int kWords = sizeof(ClassConst) / sizeof(uint32_t);
+  struct Words {
+    uint32_t w[kWords];
+  } v;
+  W* src = (W*)(reinterpret_cast<uint64_t>(p));
+#pragma unroll
+  for (int i = 0; i < kWords; ++i) v.w[i] = src[i];
+  return __builtin_bit_cast(ClassConst, v);
+}
+
+// A block's class in a launch over all of them, and its index within it.
+__device__ __forceinline__ int block_class(const ClassSegs& segs, int& block) {
+  int k = 0, first = 0;
+  while (k + 1 < segs.n && (int)blockIdx.x >= segs.blk_end[k]) first = segs.blk_end[k++];
+  block = (int)blockIdx.x - __builtin_amdgcn_readfirstlane(first);
+  return __builtin_amdgcn_readfirstlane(k);   // uniform, also to the compiler
+}
+
+// The throttles of a class of n <= N thrusters; rows past n hold some other
+// throttle until mask_throttles makes them zeros.  With their columns of B,
+// which are zero too, N-thruster code then gives that class's results.  Two
+// steps, so that no load is waited for before the next one is issued.
+template <int N>
+__device__ __forceinline__ void load_throttles(int n, const float* af, int64_t E, uint32_t co,
+                                               float (&act)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) act[i] = lane_elem(i < n ? af + i * E : af, co);
+}
+template <int N>
+__device__ __forceinline__ void mask_throttles(int n, float (&act)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) act[i] = i < n ? act[i] : 0.0f;
 }
 
 template <int N, bool LAG>

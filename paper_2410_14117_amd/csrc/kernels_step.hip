@@ -36,6 +36,19 @@ __device__ __forceinline__ void block_stats(double s_dist, double m_dist, double
   __syncthreads();
 }
 
+// 1/2 nu^T M nu = 1/2 (v . a + w . b), every FMA explicit, so that the kernels
+// that form it agree bitwise
+__device__ __forceinline__ double kinetic_energy(const EnvConst& P, const float* x) {
+  const double u = x[7], v = x[8], w = x[9], p = x[10], q = x[11], r = x[12];
+  const double au = fma((double)P.Muu, u, mul_nc((double)P.Muq, q));
+  const double av = fma((double)P.Mvv, v, mul_nc((double)P.Mvp, p));
+  const double aw = mul_nc((double)P.Mww, w);
+  const double bp = fma((double)P.Mvp, v, mul_nc((double)P.Mpp, p));
+  const double bq = fma((double)P.Muq, u, mul_nc((double)P.Mqq, q));
+  const double br = mul_nc((double)P.Mrr, r);
+  return 0.5 * fma(r, br, fma(q, bq, fma(p, bp, fma(w, aw, fma(u, au, mul_nc(v, av))))));
+}
+
 // ---------------------------------------------------------------------------
 // the step kernel: n_ctrl control steps x substeps RK4 sub-steps per launch,
 // state and per-env constants in registers throughout; one env per lane.
@@ -114,17 +127,9 @@ __global__ void __launch_bounds__(kBlock) MG_STEP_ATTR k_step(const StepArgs a, 
             tz = lane_elem(a.targets + 2 * a.E, co);
           }
           const double dx = (double)x[0] - tx, dy = (double)x[1] - ty, dz = (double)x[2] - tz;
-          s_dist = sqrt(dx * dx + dy * dy + dz * dz);
+          s_dist = sqrt(fma(dz, dz, fma(dx, dx, mul_nc(dy, dy))));
           m_dist = s_dist;
-          // 1/2 nu^T M nu = 1/2 (v . a + w . b)
-          const double u = x[7], v = x[8], w = x[9], p = x[10], q = x[11], r = x[12];
-          const double au = (double)P.Muu * u + (double)P.Muq * q;
-          const double av = (double)P.Mvv * v + (double)P.Mvp * p;
-          const double aw = (double)P.Mww * w;
-          const double bp = (double)P.Mvp * v + (double)P.Mpp * p;
-          const double bq = (double)P.Muq * u + (double)P.Mqq * q;
-          const double br = (double)P.Mrr * r;
-          s_ke = 0.5 * (u * au + v * av + w * aw + p * bp + q * bq + r * br);
+          s_ke = kinetic_energy(P, x);
         } else {
           n_bad = 1.0;
         }
@@ -145,6 +150,157 @@ __global__ void __launch_bounds__(kBlock) MG_STEP_ATTR k_step(const StepArgs a, 
       // the launch-input state stays in place
       lane_elem(a.flags, (uint32_t)j) =
           (uint8_t)(lane_elem(a.flags, (uint32_t)j) | kFlagNonFinite);
+    }
+  }
+}
+
+// The control steps of all classes in one launch: one tail of blocks for all of
+// them, no fork and join between class streams, and whole rollouts in one launch
+// (a.each).  All classes have a lag or none has; N is the most thrusters of any.
+// The class constants and the row pointers are formed anew at each use (the
+// pins): held in scalar registers across the control steps they spill, which
+// took 20 us of a control step of 2^20 envs.  168 VGPRs, no spills.  Per control
+// step, before (a launch per class and control step, forked and joined or
+// replayed from a graph) and now: 10^5 envs of two classes, 4 sub-steps, one call
+// per control step 43.7 -> 12.2 us, rollouts 17.1 -> 7.9; 2^20 envs, 16 sub-steps
+// 180 -> 174 and 175 -> 155; 2^20 envs of one class, rollouts 158 -> 154.  A
+// single class's mg_step stays with k_step, which is 2-8 % faster there.
+template <int N, bool LAG>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
+k_step_classes(const StepArgs a, const ClassSegs segs) {
+  constexpr int D = Dims<N, LAG>::D;
+  int block;
+  const int k = block_class(segs, block);
+  const ClassConst* ccp = segs.cc + k;
+  auto class_const = [&]() { return scalar_class_const(pin_sgpr(ccp)); };
+  const int64_t seg_start = segs.start[k], seg_len = segs.len[k];
+  const int n = class_const().n_thr;
+  const int Dc = LAG ? 13 + n : 13;    // the class's rows
+  const int64_t local = (int64_t)block * kBlock + threadIdx.x;
+  bool active = local < seg_len && MG_CHECK(a, seg_start + seg_len <= a.Ep, kDbgSegment);
+  const int64_t j = seg_start + (active ? local : 0);
+  const uint32_t jo = (uint32_t)j * 4u;
+  int64_t c = active ? (a.perm ? (int64_t)lane_elem(a.perm, jo) : j) : 0;
+  active = active && MG_CHECK(a, c >= 0 && c < a.dbg.cols, kDbgColumn);
+  c = active ? c : 0;
+  const uint32_t co = (uint32_t)c * 4u;
+
+  float x[D];
+  auto load_state = [&]() {
+    const float* st = pin_sgpr(a.state);
+    const int64_t ld = pin_sgpr(a.Ep);
+#pragma unroll
+    for (int i = 0; i < D; ++i) x[i] = lane_elem(i < 13 || i < Dc ? st + i * ld : st, jo);
+  };
+  auto mask_state = [&]() {
+#pragma unroll
+    for (int i = 13; i < D; ++i) x[i] = i < Dc ? x[i] : 0.0f;
+  };
+  auto store_state = [&]() {
+    float* st = pin_sgpr(a.state);
+    const int64_t ld = pin_sgpr(a.Ep);
+#pragma unroll
+    for (int i = 0; i < 13; ++i) lane_elem(st + i * ld, jo) = x[i];
+    if (Dc == D) {
+#pragma unroll
+      for (int i = 13; i < D; ++i) lane_elem(st + i * ld, jo) = x[i];
+    } else {
+#pragma unroll
+      for (int i = 13; i < D; ++i)
+        if (i < Dc) lane_elem(st + i * ld, jo) = x[i];
+    }
+  };
+  auto all_finite = [&]() {
+    bool finite = true;
+#pragma unroll
+    for (int i = 0; i < D; ++i) finite = finite && isfinite(x[i]);
+    return finite;
+  };
+  auto set_nonfinite = [&]() {
+    lane_elem(a.flags, (uint32_t)j) =
+        (uint8_t)(lane_elem(a.flags, (uint32_t)j) | kFlagNonFinite);
+  };
+  EnvConst P;
+  // an env whose flags are set is frozen: it is not stepped; an env whose
+  // state is non-finite at the end of the launch (a.each: of a control step)
+  // gets its input state back and is flagged, so that it is frozen from the
+  // next launch (control step) on: bad_at is that step
+  bool frozen = false;
+  int bad_at = a.n_ctrl;
+  // each control step's throttles are loaded one step ahead: loads and stores
+  // complete in order, so a load behind the trajectory's stores would wait for
+  // them
+  float nxt[N];
+  if (active) {
+    load_state();
+    P = load_env_const_off(a.derived, pin_sgpr(a.Ep), jo);
+    frozen = lane_elem(a.flags, (uint32_t)j) != 0;
+    load_throttles<N>(n, a.actions, pin_sgpr(a.E), co, nxt);
+    mask_state();
+  }
+  const StepConstT<float> sc = make_step_const(class_const(), a.dt);
+  const HalfInvT<float> A = half_step_inverse(P, sc.h2);
+  for (int t = 0; t < a.n_ctrl; ++t) {
+    double s_dist = 0.0, m_dist = 0.0, s_ke = 0.0, n_bad = 0.0;
+    if (active) {
+      const ClassConst cc = class_const();
+      float fcmd[N], gcmd[6];
+      mask_throttles<N>(n, nxt);
+      thrust_command<N>(cc, nxt, fcmd);
+      command_wrench<N>(cc, fcmd, gcmd);
+      if (t + 1 < a.n_ctrl)
+        load_throttles<N>(n, pin_sgpr(a.actions + (int64_t)(t + 1) * a.n_max * a.E),
+                          pin_sgpr(a.E), co, nxt);
+      if (!frozen)
+        control_step<N, LAG>(x, P, A, cc, fcmd, gcmd, sc, a.substeps, cc.rho_s);
+      if (a.traj && bad_at == a.n_ctrl) {
+        float* tf = pin_sgpr(a.traj + (int64_t)t * a.D * a.E);
+        const int64_t ld = pin_sgpr(a.E);
+#pragma unroll
+        for (int i = 0; i < D; ++i) lane_elem(tf + i * ld, co) = x[i];   // D == a.D
+      }
+      const bool finite = (a.partials || a.each) ? all_finite() : true;
+      if (a.partials) {
+        if (finite && !frozen) {
+          float tx = 0.f, ty = 0.f, tz = 0.f;
+          if (a.targets) {
+            tx = lane_elem(a.targets, co);
+            ty = lane_elem(a.targets + a.E, co);
+            tz = lane_elem(a.targets + 2 * a.E, co);
+          }
+          const double dx = (double)x[0] - tx, dy = (double)x[1] - ty, dz = (double)x[2] - tz;
+          s_dist = sqrt(fma(dz, dz, fma(dx, dx, mul_nc(dy, dy))));
+          m_dist = s_dist;
+          s_ke = kinetic_energy(P, x);
+        } else {
+          n_bad = 1.0;
+        }
+      }
+      if (a.each) {
+        if (!finite) {
+          bad_at = min(bad_at, t);
+          frozen = true;
+        } else if (!frozen) {
+          store_state();
+        }
+      }
+    }
+    if (a.partials)
+      block_stats(s_dist, m_dist, s_ke, n_bad,
+                  a.partials + ((int64_t)t * a.nblk_total + blockIdx.x) * 4);
+  }
+  if (!active) return;
+  if (!a.each && all_finite()) {
+    store_state();
+  } else if (!a.each || bad_at < a.n_ctrl) {
+    set_nonfinite();        // the input state stays in place
+    if (!a.traj) return;
+    load_state();
+    mask_state();
+    for (int t = bad_at + 1; t < a.n_ctrl; ++t) {
+      float* tf = a.traj + (int64_t)t * a.D * a.E + c;
+#pragma unroll
+      for (int i = 0; i < D; ++i) tf[i * a.E] = x[i];
     }
   }
 }
@@ -173,6 +329,29 @@ hipError_t launch_step(const ClassConst& cc, const StepArgs& a, hipStream_t s) {
       return hipErrorInvalidValue;
   }
 #undef MG_CASE
+}
+
+hipError_t launch_step_classes(const ClassSegs& segs, const StepArgs& a, bool lag,
+                               hipStream_t s) {
+  const int nblk = segs.blk_end[segs.n - 1];
+  if (nblk == 0) return hipSuccess;
+  if (a.Ep > ((int64_t)1 << 30) || a.E > ((int64_t)1 << 30)) return hipErrorInvalidValue;
+  if (a.D != 13 + (lag ? a.n_max : 0)) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)nblk), block(kBlock);
+#define MG_CASE(n)                                                                      \
+  case n:                                                                               \
+    if (lag)                                                                            \
+      hipLaunchKernelGGL((k_step_classes<n, true>), grid, block, 0, s, a, segs);        \
+    else                                                                                \
+      hipLaunchKernelGGL((k_step_classes<n, false>), grid, block, 0, s, a, segs);       \
+    break;
+  switch (a.n_max) {
+    MG_CASE(1) MG_CASE(2) MG_CASE(3) MG_CASE(4) MG_CASE(5) MG_CASE(6) MG_CASE(7) MG_CASE(8)
+    default:
+      return hipErrorInvalidValue;
+  }
+#undef MG_CASE
+  return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
@@ -284,7 +463,7 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
         a.partials[((int64_t)t * a.nblk_total + blockIdx.x) * 4 + lane] = s;
     }
     if constexpr (EACH) {
-      if (!finite && !frozen) {
+      if (!finite) {
         x = x0;
         frozen = bad = true;
       }

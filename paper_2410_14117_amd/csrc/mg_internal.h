@@ -132,6 +132,9 @@ struct StepArgs {
   int32_t nblk_total, blk_off;
   int32_t n_ctrl, substeps;
   float dt;
+  int32_t each;                // k_step_classes: state written back, or the env frozen, after each
+                               // control step (as one launch per control step would), else
+                               // after the last
   MG_DBG_FIELD
 };
 
@@ -322,6 +325,8 @@ hipError_t launch_adj_recompute(const ClassConst& cc, const AdjArgs& a, hipStrea
 
 // launchers (kernels_step.hip)
 hipError_t launch_step(const ClassConst& cc, const StepArgs& a, hipStream_t s);
+// all classes in one launch (seg_start, seg_len and blk_off unused), not plain
+hipError_t launch_step_classes(const ClassSegs& segs, const StepArgs& a, bool lag, hipStream_t s);
 hipError_t launch_stats_finalize(const double* partials, int32_t nblk, int32_t n_ctrl,
                                  double* stats, hipStream_t s);
 hipError_t launch_reset(const ResetArgs& a, hipStream_t s);

@@ -97,7 +97,10 @@ struct mg_sim {
   // one env per quad of lanes, all classes in one launch (small sims)
   bool quad_on = false, any_lag = false;
   ClassSegs quad{};
-  ClassSegs lanes{};           // all classes in one launch, one env per lane
+  // all classes in one launch, one env per lane (steps and rollouts: if all
+  // classes have a lag or none has)
+  bool lanes_on = true;
+  ClassSegs lanes{};
 
   float* state = nullptr;      // [D][Ep]
   float* params = nullptr;     // [23][Ep]
@@ -314,9 +317,32 @@ mg_status enqueue_quad(mg_sim* s, const float* actions, int32_t n_ctrl, const fl
   return MG_OK;
 }
 
+// n_ctrl control steps of every class in one launch, one env per lane, frozen as
+// one launch per control step would (each_step) or as one launch.
+mg_status enqueue_lanes(mg_sim* s, const float* actions, int32_t n_ctrl, const float* targets,
+                        float* traj, double* stats, bool each_step) {
+  StepArgs a = step_args(s);
+  a.actions = actions;
+  a.targets = targets;
+  a.traj = traj;
+  a.partials = stats ? s->partials : nullptr;
+  a.nblk_total = s->nblk_total;
+  a.n_ctrl = n_ctrl;
+  a.substeps = s->substeps;
+  a.each = each_step ? 1 : 0;
+  if (s->n_classes == 1 && !each_step) {
+    a.seg_len = s->seg_len[0];
+    MG_HIP(s, launch_step(s->cc[0], a, s->stream));
+  } else {
+    MG_HIP(s, launch_step_classes(s->lanes, a, s->any_lag, s->stream));
+  }
+  if (stats) MG_HIP(s, launch_stats_finalize(s->partials, s->nblk_total, n_ctrl, stats, s->stream));
+  return MG_OK;
+}
+
 // Enqueue n_ctrl fused control steps (plain = 0) or their plain equivalent
-// (one launch per sub-step), followed by the statistics pass.  Class k >= 1
-// runs on helper stream k-1, forked from and joined back into `st`.
+// (one launch per sub-step) class by class, followed by the statistics pass.
+// Class k >= 1 runs on helper stream k-1, forked from and joined back into `st`.
 mg_status enqueue_steps(mg_sim* s, hipStream_t st, const float* actions, int32_t n_ctrl,
                         const float* targets, float* traj, double* stats, bool plain,
                         bool one_launch_per_ctrl) {
@@ -422,6 +448,8 @@ mg_status step_common(mg_sim* s, const float* actions, int32_t n_ctrl, const flo
     return enqueue_quad(s, actions, n_ctrl, targets, traj, stats, false);
   }
   if (stats && (st = ensure_partials(s, n_ctrl, s->nblk_total))) return st;
+  if (s->lanes_on && !plain)
+    return enqueue_lanes(s, actions, n_ctrl, targets, traj, stats, false);
   return enqueue_steps(s, s->stream, actions, n_ctrl, targets, traj, stats, plain, false);
 }
 
@@ -664,6 +692,8 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
     s->quad.len[k] = count[k];
     s->quad.zb[k] = (float)s->nominal[k].zb;
   }
+  for (int k = 0; k < cfg->n_classes; ++k)
+    s->lanes_on = s->lanes_on && (s->cc[k].lag != 0) == s->any_lag;
   s->lanes = s->quad;
   for (int k = 0; k < cfg->n_classes; ++k)
     s->lanes.blk_end[k] = k + 1 < cfg->n_classes ? s->seg_blk_off[k + 1] : blk;
@@ -1009,6 +1039,7 @@ mg_status mg_rollout(mg_sim* s, const float* actions, int32_t T, const float* ta
     return enqueue_quad(s, actions, T, targets, traj, stats, true);
   }
   if (stats && (st = ensure_partials(s, T, s->nblk_total))) return st;
+  if (s->lanes_on && !plain) return enqueue_lanes(s, actions, T, targets, traj, stats, true);
   GraphKey key{T, plain ? 1 : 0, actions, targets, traj, stats};
   auto it = s->graphs.find(key);
   if (it == s->graphs.end()) {

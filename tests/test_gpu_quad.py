@@ -1,6 +1,7 @@
-"""GPU checks of the kernels that spread one env over a quad of lanes (sims of at most one
-wave per SIMD) against the ones with one env per lane: the same envs inside a batch too
-large for the quad kernels, bitwise, at the edges of a wave's 16 envs and of the range."""
+"""GPU checks of the kernels that take all classes in one launch: those with one env over a
+quad of lanes (sims of at most one wave per SIMD) against the ones with one env per lane, the
+same envs inside a batch too large for the quad kernels, bitwise, at the edges of a wave's 16
+envs and of the range; and a rollout in one launch against its steps."""
 import sys
 import os
 
@@ -166,3 +167,33 @@ def test_split_of_all_classes_in_one_launch(mgmod, oracle, fleet, S, T, sizes):
     ref = oracle.split_rollout(classes, x0[:, sub], act[:1][:, :, sub], S, 0.005,
                                env_class=cls[sub], mult=mult[:, sub], want_traj=True)
     assert rel_err(big[0][0][:, sub], ref["traj"][0]) <= TOL_ONE_STEP
+
+
+@pytest.mark.parametrize("fleet,E", [("heavy", 16385), ("mixed", 20000), ("bluerov2", 16640),
+                                     ("lag_and_not", 20000)])
+def test_rollout_of_all_classes_in_one_launch(mgmod, fleet, E):
+    """One env per lane: a rollout equals as many single steps (of the same classes one at a
+    time if the sim has one class), bitwise, with envs that go non-finite part-way, at the
+    first and the last control step, and one that is not steppable from the start."""
+    classes, T, S = FLEETS[fleet], 4, 2
+    cls, x0, act, mult = _inputs(classes, E, T, 51)
+    act[0, 0, 7] = act[1, 1, 100] = act[T - 1, 0, E - 1] = np.nan
+    mult[4:7, 300] = -9.0          # mass matrix not positive definite
+    say("rollout in one launch", fleet, E)
+    out = []
+    for mode in ("rollout", "step"):
+        sim = mgmod.Sim(classes, E, 0.005, S, env_class=cls)
+        sim.reset(state=dev(x0), param_mult=dev(mult))
+        traj = torch.full((T, x0.shape[0], E), -1.0, device="cuda")
+        stats = torch.empty((T, 4), dtype=torch.float64, device="cuda")
+        if mode == "rollout":
+            sim.rollout(dev(act), traj=traj, stats=stats)
+        else:
+            for t in range(T):
+                sim.step(dev(act[t:t + 1]), traj=traj[t:t + 1], stats=stats[t:t + 1])
+        out.append([host(v) for v in (traj, stats, sim.get_state(), sim.get_flags())])
+        sim.close()
+    for u, w in zip(*out):
+        np.testing.assert_array_equal(u, w)
+    assert sorted(np.flatnonzero(out[0][3])) == sorted({7, 100, 300, E - 1})
+    assert list(out[0][1][:, 3]) == [2, 3, 3, 4]
