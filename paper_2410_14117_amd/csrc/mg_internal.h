@@ -178,8 +178,7 @@ struct TaskArgs {
   int32_t* task_k;             // internal [Ep] control steps since the episode began
   int64_t Ep, E;
   const int32_t* perm;         // internal -> caller, NULL = identity
-  int64_t seg_start, seg_len;
-  const ClassNominal* nominal; // device, this class's entry
+  const ClassNominal* nominal; // device [n_classes]
   const float* actions;        // caller [n_max][E], or NULL: observe only
   int32_t n_max, D, substeps;
   float dt;
@@ -330,7 +329,9 @@ hipError_t launch_step_classes(const ClassSegs& segs, const StepArgs& a, bool la
 hipError_t launch_stats_finalize(const double* partials, int32_t nblk, int32_t n_ctrl,
                                  double* stats, hipStream_t s);
 hipError_t launch_reset(const ResetArgs& a, hipStream_t s);
-hipError_t launch_task(const ClassConst& cc, const TaskConst& tc, const TaskArgs& a, hipStream_t s);
+// all classes in one launch, one env per lane or (quad) per quad of lanes
+hipError_t launch_task(const ClassSegs& segs, const TaskConst& tc, const TaskArgs& a, bool lag,
+                       bool quad, hipStream_t s);
 // all classes in one launch, one env per lane or (quad) per quad of lanes
 hipError_t launch_split(const ClassSegs& segs, const SplitArgs& a, bool lag, bool quad,
                         hipStream_t s);

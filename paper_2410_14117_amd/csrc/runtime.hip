@@ -540,11 +540,10 @@ mg_status copy_in(mg_sim* s, const float* src, int32_t rows, float* dst) {
   return MG_OK;
 }
 
-// One task launch per class (forked / joined like the step): a Gym step when
-// actions is given, else the observation alone.
+// A Gym step of all classes in one launch when actions is given, else the
+// observation alone.
 mg_status enqueue_task(mg_sim* s, const float* actions, float* obs, float* err, int32_t* done,
                        const float* reset_state, const float* reset_mult) {
-  hipStream_t st = s->stream;
   TaskArgs a;
   std::memset(&a, 0, sizeof(a));
   a.state = s->state;
@@ -567,20 +566,9 @@ mg_status enqueue_task(mg_sim* s, const float* actions, float* obs, float* err, 
   a.done = done;
   a.reset_state = reset_state;
   a.reset_mult = reset_mult;
-  for (int k = 1; k < s->n_classes; ++k) {
-    MG_HIP(s, hipEventRecord(s->ev_fork[k - 1], st));
-    MG_HIP(s, hipStreamWaitEvent(s->aux[k - 1], s->ev_fork[k - 1], 0));
-  }
-  for (int k = 0; k < s->n_classes; ++k) {
-    a.seg_start = s->seg_start[k];
-    a.seg_len = s->seg_len[k];
-    a.nominal = s->nominal_dev + k;
-    MG_HIP(s, launch_task(s->cc[k], s->task, a, k == 0 ? st : s->aux[k - 1]));
-  }
-  for (int k = 1; k < s->n_classes; ++k) {
-    MG_HIP(s, hipEventRecord(s->ev_join[k - 1], s->aux[k - 1]));
-    MG_HIP(s, hipStreamWaitEvent(st, s->ev_join[k - 1], 0));
-  }
+  a.nominal = s->nominal_dev;
+  MG_HIP(s, launch_task(s->quad_on ? s->quad : s->lanes, s->task, a, s->any_lag, s->quad_on,
+                        s->stream));
   return MG_OK;
 }
 

@@ -197,3 +197,48 @@ def test_rollout_of_all_classes_in_one_launch(mgmod, fleet, E):
         np.testing.assert_array_equal(u, w)
     assert sorted(np.flatnonzero(out[0][3])) == sorted({7, 100, 300, E - 1})
     assert list(out[0][1][:, 3]) == [2, 3, 3, 4]
+
+
+@pytest.mark.parametrize("fleet,task,m,sizes", [
+    ("heavy", "helix", 4, (1, 17, 16384)),
+    ("bluerov2", "lemniscate", 1, (33,)),
+    ("three", "circle", 16, (49,)),
+    ("mixed", "circle", 5, (2, 1001)),
+    ("lag_and_not", "station", 3, (1001,)),
+])
+def test_task_quad_equals_one_env_per_lane(mgmod, fleet, task, m, sizes):
+    """Task steps with one env per quad of lanes and per lane: observations, errors, done flags
+    and everything a restart writes, bitwise; episodes end by their length, by the error bound
+    and by a non-finite state."""
+    classes, T = FLEETS[fleet], 5
+    cls, x0, act, mult = _inputs(classes, BIG, T, 61)
+    act[1, 0, 0] = act[1, 0, 20] = np.nan
+    rng = np.random.default_rng(65)
+    x1 = random_states(BIG, x0.shape[0], 66)
+    center, phase, yaw = (rng.standard_normal(n).astype(np.float32)
+                          for n in ((3, BIG), (BIG,), (BIG,)))
+    say("task", fleet, task, m)
+
+    def run(E):
+        sim = mgmod.Sim(classes, E, 0.005, 3, env_class=cls[:E])
+        sim.reset(state=dev(x0[:, :E]), param_mult=dev(mult[:, :E]))
+        sim.task_configure(dict(task=task, lookahead=m, radius=1.0, omega=0.5, climb_rate=0.1,
+                                episode_steps=4, max_error=2.5),
+                           dev(center[:, :E]), dev(phase[:E]), dev(yaw[:E]))
+        out = [host(sim.task_observe())]
+        for t in range(T):
+            kw = dict(reset_state=dev(x1[:, :E]), reset_mult=dev(mult[::-1, :E].copy())) \
+                if t % 2 else {}
+            out += [host(v) for v in sim.task_step(dev(act[t, :, :E]), **kw)]
+        out += [host(sim.get_state()), host(sim.get_params()), host(sim.get_flags()),
+                host(sim.task_counters())]
+        sim.close()
+        return out
+
+    big = run(BIG)
+    dones = np.stack(big[3::3][:T])
+    assert (dones == 1).any() and (dones == 2).any() and (dones == 0).any()
+    for E in sizes:
+        say("  envs", E)
+        for i, (u, w) in enumerate(zip(run(E), big)):
+            np.testing.assert_array_equal(u, w[..., :E], err_msg=str(i))
