@@ -228,25 +228,36 @@ def vehicle_struct(preset):
     return v
 
 
+_torch = None
+
+
+def _import_torch():
+    """torch, imported on first use (the server's host calls need none of it)."""
+    global _torch
+    if _torch is None:
+        import torch
+        _torch = torch
+    return _torch
+
+
 def _ptr(t, dtype, shape, name):
-    """Device pointer of a contiguous CUDA tensor with the given dtype/shape (None -> NULL)."""
+    """Device pointer of a contiguous CUDA tensor with the given dtype and shape, a tuple
+    (None -> NULL)."""
     if t is None:
         return None
-    import torch
-    if not isinstance(t, torch.Tensor) or t.device.type != "cuda":
+    if not isinstance(t, (_torch or _import_torch()).Tensor) or not t.is_cuda:
         raise TypeError(f"{name} must be a device tensor")
     if t.dtype != dtype:
         raise TypeError(f"{name} must be {dtype}, got {t.dtype}")
     if not t.is_contiguous():
         raise ValueError(f"{name} must be contiguous")
-    if tuple(t.shape) != tuple(shape):
-        raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {tuple(shape)}")
+    if t.shape != shape:
+        raise ValueError(f"{name} has shape {tuple(t.shape)}, expected {shape}")
     return t.data_ptr()
 
 
 def _current_stream():
-    import torch
-    return torch.cuda.current_stream().cuda_stream
+    return _import_torch().cuda.current_stream().cuda_stream
 
 
 class Sim:
@@ -278,6 +289,7 @@ class Sim:
             raise MgError(st, L.mg_last_error(None).decode())
         self._h = h
         self.device = int(device)
+        self._dev = _import_torch().device("cuda", self.device)
         self.n_envs = int(n_envs)
         self.state_dim = L.mg_state_dim(h)
         self.action_dim = L.mg_action_dim(h)
@@ -290,7 +302,10 @@ class Sim:
             raise MgError(st, lib().mg_last_error(self._h).decode())
 
     def _bind_stream(self):
-        self._check(lib().mg_set_stream(self._h, _current_stream()))
+        # the current device's current stream, as torch.cuda.current_stream() gives it,
+        # without the Stream object: 0.2 instead of 2.9 us of a call's 4-9
+        c = _torch._C
+        self._check(_lib.mg_set_stream(self._h, c._cuda_getCurrentRawStream(c._cuda_getDevice())))
 
     @property
     def handle(self):
@@ -309,7 +324,7 @@ class Sim:
 
     # -- calls -----------------------------------------------------------------------------
     def reset(self, env_ids=None, state=None, param_mult=None):
-        import torch
+        torch = _torch
         n = self.n_envs if env_ids is None else int(env_ids.numel())
         ids = _ptr(env_ids, torch.int64, (n,), "env_ids")
         s = _ptr(state, torch.float32, (self.state_dim, n), "state")
@@ -318,19 +333,19 @@ class Sim:
         self._check(lib().mg_reset(self._h, ids, n if env_ids is not None else 0, s, m))
 
     def set_params(self, params):
-        import torch
+        torch = _torch
         p = _ptr(params, torch.float32, (NUM_PARAMS, self.n_envs), "params")
         self._bind_stream()
         self._check(lib().mg_set_params(self._h, p))
 
     def set_state(self, state):
-        import torch
+        torch = _torch
         s = _ptr(state, torch.float32, (self.state_dim, self.n_envs), "state")
         self._bind_stream()
         self._check(lib().mg_set_state(self._h, s))
 
     def _step_args(self, actions, n_ctrl, targets, traj, stats):
-        import torch
+        torch = _torch
         E, D, N = self.n_envs, self.state_dim, self.action_dim
         a = _ptr(actions, torch.float32, (n_ctrl, N, E), "actions")
         tg = _ptr(targets, torch.float32, (3, E), "targets")
@@ -341,7 +356,7 @@ class Sim:
     def step_split(self, actions, traj=None):
         """actions [n_ctrl][N_max][E]: n_ctrl control steps of the split scheme of Sec. II
         in one launch (see mg_step_split)."""
-        import torch
+        torch = _torch
         n_ctrl = int(actions.shape[0])
         E, D, N = self.n_envs, self.state_dim, self.action_dim
         a = _ptr(actions, torch.float32, (n_ctrl, N, E), "actions")
@@ -352,7 +367,7 @@ class Sim:
     # -- Gym-style tasks ---------------------------------------------------------------------
     def task_configure(self, task, center, phase, yaw=None):
         """task: dict (see task_struct); center [3][E], phase [E], yaw [E] device tensors."""
-        import torch
+        torch = _torch
         E = self.n_envs
         self._task = task_struct(task)
         self._bind_stream()
@@ -362,10 +377,10 @@ class Sim:
         self.obs_dim = lib().mg_task_obs_dim(self._h)
 
     def task_observe(self, obs=None):
-        import torch
+        torch = _torch
         if obs is None:
             obs = torch.empty((self.obs_dim, self.n_envs), dtype=torch.float32,
-                              device=f"cuda:{self.device}")
+                              device=self._dev)
         p = _ptr(obs, torch.float32, (self.obs_dim, self.n_envs), "obs")
         self._bind_stream()
         self._check(lib().mg_task_observe(self._h, p))
@@ -374,8 +389,8 @@ class Sim:
     def task_step(self, actions, obs=None, err=None, done=None, reset_state=None,
                   reset_mult=None):
         """actions [N_max][E]; returns (obs [obs_dim][E], err [E], done [E] int32)."""
-        import torch
-        E, dev = self.n_envs, f"cuda:{self.device}"
+        torch = _torch
+        E, dev = self.n_envs, self._dev
         if obs is None:
             obs = torch.empty((self.obs_dim, E), dtype=torch.float32, device=dev)
         if err is None:
@@ -393,9 +408,9 @@ class Sim:
         return obs, err, done
 
     def task_counters(self, out=None):
-        import torch
+        torch = _torch
         if out is None:
-            out = torch.empty((self.n_envs,), dtype=torch.int32, device=f"cuda:{self.device}")
+            out = torch.empty((self.n_envs,), dtype=torch.int32, device=self._dev)
         p = _ptr(out, torch.int32, (self.n_envs,), "out")
         self._bind_stream()
         self._check(lib().mg_task_counters(self._h, p))
@@ -418,20 +433,20 @@ class Sim:
         self._check(lib().mg_rollout(self._h, a, T, tg, tr, st, 1 if plain else 0))
 
     def get_state(self, out=None):
-        import torch
+        torch = _torch
         if out is None:
             out = torch.empty((self.state_dim, self.n_envs), dtype=torch.float32,
-                              device=f"cuda:{self.device}")
+                              device=self._dev)
         p = _ptr(out, torch.float32, (self.state_dim, self.n_envs), "out")
         self._bind_stream()
         self._check(lib().mg_get_state(self._h, p, 1))
         return out
 
     def get_params(self, out=None):
-        import torch
+        torch = _torch
         if out is None:
             out = torch.empty((NUM_PARAMS, self.n_envs), dtype=torch.float32,
-                              device=f"cuda:{self.device}")
+                              device=self._dev)
         p = _ptr(out, torch.float32, (NUM_PARAMS, self.n_envs), "out")
         self._bind_stream()
         self._check(lib().mg_get_params(self._h, p, 1))
@@ -443,8 +458,8 @@ class Sim:
     def get_flags(self):
         """Per-env status flags (int32 [E] device tensor): 1 = state went non-finite, 2 = mass
         matrix not positive definite; a flagged env is frozen."""
-        import torch
-        out = torch.empty((self.n_envs,), dtype=torch.int32, device=f"cuda:{self.device}")
+        torch = _torch
+        out = torch.empty((self.n_envs,), dtype=torch.int32, device=self._dev)
         self._bind_stream()
         self._check(lib().mg_get_flags(self._h, out.data_ptr(), 1))
         return out
@@ -461,13 +476,13 @@ class Sim:
     def adj_forward(self, actions, ckpt_every, ckpt=None, traj=None):
         """Rollout of T = actions.shape[0] control steps from the current state, saving a
         checkpoint before every ckpt_every-th step.  Returns (ckpt, traj)."""
-        import torch
+        torch = _torch
         T, E, D, N = int(actions.shape[0]), self.n_envs, self.state_dim, self.action_dim
         K = int(ckpt_every)
         if K < 1:
             raise ValueError("ckpt_every must be >= 1")
         nseg = (T + K - 1) // K
-        dev = f"cuda:{self.device}"
+        dev = self._dev
         if ckpt is None:
             ckpt = torch.empty((nseg, D, E), dtype=torch.float32, device=dev)
         a = _ptr(actions, torch.float32, (T, N, E), "actions")
@@ -484,11 +499,11 @@ class Sim:
         noalloc: call mg_adj_backward_noalloc (static scratch, no device allocation);
         traj: the trajectory adj_forward wrote (with one sub-step per control step the
         backward then reads its inputs from it instead of recomputing them)."""
-        import torch
+        torch = _torch
         T, E, D, N = int(actions.shape[0]), self.n_envs, self.state_dim, self.action_dim
         K = int(ckpt_every)
         nseg = (T + K - 1) // K
-        dev = f"cuda:{self.device}"
+        dev = self._dev
         if out is None:
             gact = torch.empty((T, N, E), dtype=torch.float32, device=dev)
             gth = torch.empty((NUM_THETA, E), dtype=torch.float32, device=dev)
