@@ -163,13 +163,19 @@ __device__ __forceinline__ bool set_env_params(const ClassNominal& nom, const fl
                                                int64_t stride, bool absolute, float* params,
                                                float* derived, int64_t Ep, int64_t j) {
   double prm[kNumParams];
+  float v[kNumParams];
+  // every load before the first store: the compiler may not move a load up past
+  // a store, and would wait for each parameter in turn
+  if (in) {
+#pragma unroll
+    for (int i = 0; i < kNumParams; ++i) v[i] = in[i * stride];
+  }
+#pragma unroll
+  for (int i = 0; i < kNumParams; ++i) prm[i] = nom.p[i];
 #pragma unroll
   for (int i = 0; i < kNumParams; ++i) {
-    double pi = nom.p[i];
-    if (in) {
-      const double v = in[i * stride];
-      pi = absolute ? v : pi * v;
-    }
+    double pi = prm[i];
+    if (in) pi = absolute ? (double)v[i] : pi * v[i];
     const float pf = (float)pi;
     prm[i] = (double)pf;
     params[i * Ep + j] = pf;

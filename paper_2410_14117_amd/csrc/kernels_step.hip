@@ -553,66 +553,99 @@ hipError_t launch_stats_finalize(const double* partials, int32_t nblk, int32_t n
 // factorisation of M = M_RB + M_A (FP64, rounded once), and the state
 // ---------------------------------------------------------------------------
 
+// Bandwidth-bound: 23 + D floats in, 53 + D out per env; 2^20 Heavies 132 -> 105 us
+// (4.7 TB/s, a large copy's rate) since every load precedes the first store.  A
+// reset of every env goes through them in internal order, so that it is the
+// reads that are scattered where the classes are interleaved, not the writes,
+// of which there are more.
 __global__ void __launch_bounds__(256) k_reset(const ResetArgs a) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= a.n) return;
-  const int64_t id = a.ids ? a.ids[k] : k;
-  if (id < 0 || id >= a.E) return;   // out-of-range ids are skipped (documented)
-  if (!MG_CHECK(a, id < a.dbg.cols, kDbgColumn)) return;
-  const int64_t j = a.iperm ? (int64_t)a.iperm[id] : id;
-  if (!MG_CHECK(a, j >= 0 && j < a.Ep, kDbgInternal)) return;
+  const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  int64_t k = t, j;       // column of the inputs, internal index
+  if (!a.ids && a.perm) {
+    if (t >= a.Ep) return;
+    k = a.perm[t];
+    j = t;
+    if (k < 0) return;    // padding
+    if (!MG_CHECK(a, k < a.dbg.cols, kDbgColumn)) return;
+  } else {
+    if (t >= a.n) return;
+    const int64_t id = a.ids ? a.ids[k] : k;
+    if (id < 0 || id >= a.E) return;   // out-of-range ids are skipped (documented)
+    if (!MG_CHECK(a, id < a.dbg.cols, kDbgColumn)) return;
+    j = a.iperm ? (int64_t)a.iperm[id] : id;
+    if (!MG_CHECK(a, j >= 0 && j < a.Ep, kDbgInternal)) return;
+  }
   const ClassNominal& nom = a.nominal[a.class_of[j]];
+  // the state is loaded before set_env_params, whose stores no load may pass
+  constexpr int kMaxD = 13 + kMaxThr;
+  float x[kMaxD];
+  if (a.write_state) {
+    const int Dc = 13 + (nom.lag ? nom.n_thr : 0);
+#pragma unroll
+    for (int i = 0; i < kMaxD; ++i) {
+      x[i] = i == 3 ? 1.0f : 0.0f;
+      if (a.state_in && i < a.D) x[i] = a.state_in[i * a.n + k];
+    }
+#pragma unroll
+    for (int i = 13; i < kMaxD; ++i) x[i] = i < Dc ? x[i] : 0.0f;
+  }
   const bool spd = set_env_params(nom, a.param_in ? a.param_in + k : nullptr, a.n,
                                   a.param_absolute != 0, a.params, a.derived, a.Ep, j);
   if (a.flags) {
     const uint8_t keep = a.write_state ? 0 : (uint8_t)(a.flags[j] & kFlagNonFinite);
     a.flags[j] = (uint8_t)(keep | (spd ? 0 : kFlagNotSPD));
   }
-  if (a.write_state && a.task_k) a.task_k[j] = 0;
-  if (a.write_state && a.split_acc)
+  if (!a.write_state) return;
+  if (a.task_k) a.task_k[j] = 0;
+  if (a.split_acc)
     for (int i = 0; i < 6; ++i) a.split_acc[i * a.Ep + j] = 0.0f;
-
-  if (a.write_state) {
-    const int Dc = 13 + (nom.lag ? nom.n_thr : 0);
-    for (int i = 0; i < a.D; ++i) {
-      float xi;
-      if (i >= Dc) xi = 0.0f;
-      else if (a.state_in) xi = a.state_in[i * a.n + k];
-      else xi = (i == 3) ? 1.0f : 0.0f;
-      a.state[i * a.Ep + j] = xi;
-    }
-  }
+#pragma unroll
+  for (int i = 0; i < kMaxD; ++i)
+    if (i < a.D) a.state[i * a.Ep + j] = x[i];
 }
 
 hipError_t launch_reset(const ResetArgs& a, hipStream_t s) {
   if (a.n <= 0) return hipSuccess;
-  const int64_t nblk = (a.n + 255) / 256;
+  const int64_t nblk = ((!a.ids && a.perm ? a.Ep : a.n) + 255) / 256;
   hipLaunchKernelGGL(k_reset, dim3((unsigned)nblk), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// internal <-> caller order
+// internal <-> caller order (blockIdx.y: kGatherRows rows at a time, so that their
+// loads are in flight together)
 // ---------------------------------------------------------------------------
 
-__global__ void k_gather_out(const float* __restrict__ in, int64_t Ep, float* __restrict__ out,
-                             int64_t E, int32_t rows, const int32_t* __restrict__ perm,
-                             int64_t n_internal) {
-  const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= n_internal) return;
-  const int64_t c = perm ? (int64_t)perm[j] : j;
-  if (c < 0 || c >= E) return;
-  for (int r = 0; r < rows; ++r) out[r * E + c] = in[r * Ep + j];
+constexpr int kGatherRows = 8;
+
+// One caller env per thread (iperm: caller -> internal): interleaved classes are
+// read as a few consecutive streams and written as one.
+__global__ void __launch_bounds__(256) k_gather_out(const float* __restrict__ in, int64_t Ep,
+                                                    float* __restrict__ out, int64_t E,
+                                                    int32_t rows,
+                                                    const int32_t* __restrict__ iperm) {
+  const int64_t c = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (c >= E) return;
+  const int64_t j = iperm ? (int64_t)iperm[c] : c;
+  const int r0 = blockIdx.y * kGatherRows;
+#pragma unroll
+  for (int r = r0; r < r0 + kGatherRows; ++r)
+    if (r < rows) out[r * E + c] = in[r * Ep + j];
 }
 
-__global__ void k_scatter_in(const float* __restrict__ in, int64_t E, float* __restrict__ out,
-                             int64_t Ep, int32_t rows, const int32_t* __restrict__ perm,
-                             int64_t n_internal) {
+__global__ void __launch_bounds__(256) k_scatter_in(const float* __restrict__ in, int64_t E,
+                                                    float* __restrict__ out, int64_t Ep,
+                                                    int32_t rows,
+                                                    const int32_t* __restrict__ perm,
+                                                    int64_t n_internal) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (j >= n_internal) return;
   const int64_t c = perm ? (int64_t)perm[j] : j;
   if (c < 0 || c >= E) return;
-  for (int r = 0; r < rows; ++r) out[r * Ep + j] = in[r * E + c];
+  const int r0 = blockIdx.y * kGatherRows;
+#pragma unroll
+  for (int r = r0; r < r0 + kGatherRows; ++r)
+    if (r < rows) out[r * Ep + j] = in[r * E + c];
 }
 
 // status flags, internal bytes -> caller int32
@@ -646,19 +679,22 @@ hipError_t launch_flags_mask(uint8_t* flags, int64_t n, uint8_t mask, hipStream_
   return hipGetLastError();
 }
 
+static dim3 gather_grid(int64_t n, int32_t rows) {
+  return dim3((unsigned)((n + 255) / 256), (unsigned)((rows + kGatherRows - 1) / kGatherRows));
+}
+
 hipError_t launch_gather_out(const float* in, int64_t Ep, float* out, int64_t E, int32_t rows,
-                             const int32_t* perm, int64_t n_internal, hipStream_t s) {
-  if (n_internal <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_gather_out, dim3((unsigned)((n_internal + 255) / 256)), dim3(256), 0, s,
-                     in, Ep, out, E, rows, perm, n_internal);
+                             const int32_t* iperm, hipStream_t s) {
+  hipLaunchKernelGGL(k_gather_out, gather_grid(E, rows), dim3(256), 0, s, in, Ep, out, E, rows,
+                     iperm);
   return hipGetLastError();
 }
 
 hipError_t launch_scatter_in(const float* in, int64_t E, float* out, int64_t Ep, int32_t rows,
                              const int32_t* perm, int64_t n_internal, hipStream_t s) {
   if (n_internal <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_scatter_in, dim3((unsigned)((n_internal + 255) / 256)), dim3(256), 0, s,
-                     in, E, out, Ep, rows, perm, n_internal);
+  hipLaunchKernelGGL(k_scatter_in, gather_grid(n_internal, rows), dim3(256), 0, s, in, E, out, Ep,
+                     rows, perm, n_internal);
   return hipGetLastError();
 }
 

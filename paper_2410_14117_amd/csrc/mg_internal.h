@@ -147,6 +147,7 @@ struct ResetArgs {
   int64_t Ep, E;
   int32_t D;
   const int32_t* iperm;        // caller -> internal, NULL = identity
+  const int32_t* perm;         // internal -> caller (-1: padding), NULL = identity
   const uint8_t* class_of;     // internal [Ep] class of each env
   const ClassNominal* nominal; // device [n_classes]
   const int64_t* ids;          // caller ids [n] or NULL (= 0..n-1)
@@ -335,13 +336,13 @@ hipError_t launch_task(const ClassSegs& segs, const TaskConst& tc, const TaskArg
 // all classes in one launch, one env per lane or (quad) per quad of lanes
 hipError_t launch_split(const ClassSegs& segs, const SplitArgs& a, bool lag, bool quad,
                         hipStream_t s);
-// out[r][perm[j]] = in[r][j] for rows r < rows (internal -> caller order)
 // status flags to caller order int32 [E]; flags &= mask for n envs
 hipError_t launch_flags_out(const uint8_t* flags, int32_t* out, int64_t E, const int32_t* perm,
                             int64_t n_internal, hipStream_t s);
 hipError_t launch_flags_mask(uint8_t* flags, int64_t n, uint8_t mask, hipStream_t s);
+// out[r][e] = in[r][iperm[e]] for rows r < rows (internal -> caller order)
 hipError_t launch_gather_out(const float* in, int64_t Ep, float* out, int64_t E, int32_t rows,
-                             const int32_t* perm, int64_t n_internal, hipStream_t s);
+                             const int32_t* iperm, hipStream_t s);
 // out[r][j] = in[r][perm[j]] (caller -> internal order), padding lanes untouched
 hipError_t launch_scatter_in(const float* in, int64_t E, float* out, int64_t Ep, int32_t rows,
                              const int32_t* perm, int64_t n_internal, hipStream_t s);

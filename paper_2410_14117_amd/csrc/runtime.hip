@@ -404,6 +404,7 @@ mg_status reset_impl(mg_sim* s, const int64_t* ids, int64_t n, const float* stat
   r.E = s->E;
   r.D = s->D;
   r.iperm = s->iperm;
+  r.perm = s->perm;
   r.class_of = s->class_of;
   r.nominal = s->nominal_dev;
   r.ids = ids;
@@ -426,7 +427,7 @@ mg_status copy_out(mg_sim* s, const float* src, int32_t rows, float* out, int32_
     MG_HIP(s, hipMemcpy2DAsync(dst, s->E * sizeof(float), src, s->Ep * sizeof(float),
                                s->E * sizeof(float), rows, hipMemcpyDeviceToDevice, s->stream));
   } else {
-    MG_HIP(s, launch_gather_out(src, s->Ep, dst, s->E, rows, s->perm, s->Ep, s->stream));
+    MG_HIP(s, launch_gather_out(src, s->Ep, dst, s->E, rows, s->iperm, s->stream));
   }
   if (!on_device) {
     MG_HIP(s, hipMemcpyAsync(out, s->staging, (size_t)rows * s->E * sizeof(float),
