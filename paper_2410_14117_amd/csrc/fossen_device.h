@@ -262,11 +262,11 @@ __device__ __forceinline__ ClassConst scalar_class_const(const ClassConst* p) {
   return __builtin_bit_cast(ClassConst, v);
 }
 
-// A block's class in a launch over all of them, and its index within it.
-__device__ __forceinline__ int block_class(const ClassSegs& segs, int& block) {
+// The class of block b in a launch over all of them, and its index within it.
+__device__ __forceinline__ int block_class(const ClassSegs& segs, int b, int& block) {
   int k = 0, first = 0;
-  while (k + 1 < segs.n && (int)blockIdx.x >= segs.blk_end[k]) first = segs.blk_end[k++];
-  block = (int)blockIdx.x - __builtin_amdgcn_readfirstlane(first);
+  while (k + 1 < segs.n && b >= segs.blk_end[k]) first = segs.blk_end[k++];
+  block = b - __builtin_amdgcn_readfirstlane(first);
   return __builtin_amdgcn_readfirstlane(k);   // uniform, also to the compiler
 }
 

@@ -10,8 +10,8 @@
 // 3-vector (position, linear and angular velocity, momenta, residuals), so one
 // instruction serves a whole vector and a cross product reads its rotated
 // operands through DPP quad permutations.  Lane 0 carries finite don't-care
-// values in the 3-vectors that no other lane reads.  About 215 instructions
-// per sub-step, 2.1 times fewer; the total over the chip grows (four lanes do
+// values in the 3-vectors that no other lane reads.  241 instructions per
+// sub-step, 1.9 times fewer; the total over the chip grows (four lanes do
 // the work of one 1.9 times), which is why large launches keep one env per lane.
 //
 // Every value is formed by the same operations in the same order as in
@@ -142,6 +142,36 @@ __device__ __forceinline__ void load_quad_thr(const ClassConst* cc, int c, QuadT
   t.lag = cc->lag;
 }
 
+// The lane's two thrusters, c and c + 4 of n, in rows of stride s4 bytes: offsets
+// of loads (of row 0 past n, masked when the values are used, so that nothing
+// branches and no load is waited for before the next one is issued).
+struct QuadPair {
+  uint32_t o0, o1;
+  bool m0, m1;
+};
+__device__ __forceinline__ QuadPair quad_pair(int c, int n, uint32_t col, uint32_t s4) {
+  QuadPair r;
+  r.m0 = c < n;
+  r.m1 = c + 4 < n;
+  r.o0 = col + (r.m0 ? (uint32_t)c * s4 : 0u);
+  r.o1 = col + (r.m1 ? (uint32_t)(c + 4) * s4 : 0u);
+  return r;
+}
+__device__ __forceinline__ void quad_load_pair(const QuadPair& r, const float* rows,
+                                               float (&v)[2]) {
+  v[0] = lane_elem(rows, r.o0);
+  v[1] = lane_elem(rows, r.o1);
+}
+__device__ __forceinline__ void quad_mask_pair(const QuadPair& r, float (&v)[2]) {
+  v[0] = r.m0 ? v[0] : 0.0f;
+  v[1] = r.m1 ? v[1] : 0.0f;
+}
+__device__ __forceinline__ void quad_store_pair(const QuadPair& r, float* rows,
+                                                const float (&v)[2]) {
+  if (r.m0) lane_elem(rows, r.o0) = v[0];
+  if (r.m1) lane_elem(rows, r.o1) = v[1];
+}
+
 // clamp and thrust map of the lane's two throttles (thrust_command)
 __device__ __forceinline__ void quad_thrust(const QuadThr& t, const float (&a)[2],
                                             float (&fcmd)[2]) {
@@ -153,7 +183,8 @@ __device__ __forceinline__ void quad_thrust(const QuadThr& t, const float (&a)[2
   }
 }
 
-// (l, a) = B f, thrusters in order (command_wrench, lag_wrench)
+// (l, a) = B f, thrusters in order (command_wrench, lag_wrench); those past the
+// class's own are zeros with zero columns
 __device__ __forceinline__ void quad_wrench(const QuadThr& t, const float (&f)[2], float& l,
                                             float& a) {
 #define MG_BC(i) \
@@ -162,7 +193,7 @@ __device__ __forceinline__ void quad_wrench(const QuadThr& t, const float (&f)[2
   l = t.bl[0] * f0;
   a = t.ba[0] * f0;
 #define MG_ACC(i)                 \
-  if (t.n > i) {                  \
+  {                               \
     const float fi = MG_BC(i);    \
     l = fmaf(t.bl[i], fi, l);     \
     a = fmaf(t.ba[i], fi, a);     \

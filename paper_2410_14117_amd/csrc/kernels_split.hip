@@ -68,11 +68,10 @@ template <bool LAG>
 __global__ void __launch_bounds__(kBlock)
 k_split(const SplitArgs a, const ClassSegs segs) {
   constexpr int D = LAG ? 13 + kMaxThr : 13;
-  int k = 0;
-  while (k + 1 < segs.n && (int)blockIdx.x >= segs.blk_end[k]) ++k;
-  const int blk0 = k > 0 ? segs.blk_end[k - 1] : 0;
+  int block;
+  const int k = block_class(segs, blockIdx.x, block);
   const ClassConst* __restrict__ cc = segs.cc + k;
-  const int64_t local = (int64_t)((int)blockIdx.x - blk0) * kBlock + threadIdx.x;
+  const int64_t local = (int64_t)block * kBlock + threadIdx.x;
   if (local >= segs.len[k]) return;
   if (!MG_CHECK(a, segs.start[k] + segs.len[k] <= a.Ep, kDbgSegment)) return;
   const int64_t j = segs.start[k] + local;
@@ -162,14 +161,13 @@ k_split(const SplitArgs a, const ClassSegs segs) {
 template <bool LAG>
 __global__ void __launch_bounds__(kQuadBlock) k_split_quad(const SplitArgs a,
                                                            const ClassSegs segs) {
-  int k = 0;
-  while (k + 1 < segs.n && (int)blockIdx.x >= segs.blk_end[k]) ++k;
-  const int blk0 = k > 0 ? segs.blk_end[k - 1] : 0;
+  int block;
+  const int k = block_class(segs, blockIdx.x, block);
   const ClassConst* __restrict__ cc = segs.cc + k;
   const QuadLane L = quad_lane(threadIdx.x);
   const int c = L.c, ci = c > 1 ? c - 1 : 0;
   // the four lanes of a quad share every condition below
-  const int64_t local = (int64_t)((int)blockIdx.x - blk0) * kQuadEnvs + (threadIdx.x >> 2);
+  const int64_t local = (int64_t)block * kQuadEnvs + (threadIdx.x >> 2);
   bool active = local < segs.len[k] &&
                 MG_CHECK(a, segs.start[k] + segs.len[k] <= a.Ep, kDbgSegment);
   const uint32_t j4 = (uint32_t)(segs.start[k] + (active ? local : 0)) * 4u;
@@ -182,14 +180,15 @@ __global__ void __launch_bounds__(kQuadBlock) k_split_quad(const SplitArgs a,
   QuadThr th;
   load_quad_thr(cc, c, th);
   const int n_f = th.lag ? th.n : 0;
-  const bool f0 = c < n_f, f1 = c + 4 < n_f;
+  const QuadPair fs = quad_pair(c, n_f, j4, s4);     // lag states, internal rows
+  const QuadPair thr_in = quad_pair(c, th.n, c4, e4);  // throttles, caller rows
   QuadState x;
   x.p = lane_elem(a.state, ji);
   x.q = lane_elem(a.state + 3 * a.Ep, jc);
   x.v = lane_elem(a.state + 7 * a.Ep, ji);
   x.w = lane_elem(a.state + 10 * a.Ep, ji);
-  x.f[0] = f0 ? lane_elem(a.state + 13 * a.Ep, jc) : 0.0f;
-  x.f[1] = f1 ? lane_elem(a.state + 17 * a.Ep, jc) : 0.0f;
+  x.f[0] = x.f[1] = 0.0f;
+  if constexpr (LAG) quad_load_pair(fs, a.state + 13 * a.Ep, x.f);
   float al = lane_elem(a.acc, ji), aa = lane_elem(a.acc + 3 * a.Ep, ji);
   const float mal = lane_elem(a.params + 4 * a.Ep, ji), maa = lane_elem(a.params + 7 * a.Ep, ji);
   QuadConst C;
@@ -203,15 +202,12 @@ __global__ void __launch_bounds__(kQuadBlock) k_split_quad(const SplitArgs a,
   const float dt = to_vgpr(a.dt), hdt = to_vgpr(0.5f * a.dt), kappa = to_vgpr(cc->kappa);
   const int64_t frame = (int64_t)a.n_max * a.E;
   float nxt[2];   // throttles, loaded one control step ahead
-  nxt[0] = c < th.n ? lane_elem(a.actions, oc) : 0.0f;
-  nxt[1] = c + 4 < th.n ? lane_elem(a.actions + 4 * a.E, oc) : 0.0f;
+  quad_load_pair(thr_in, a.actions, nxt);
+  if constexpr (LAG) quad_mask_pair(fs, x.f);
   for (int t = 0; t < a.n_ctrl; ++t) {
-    const float act[2] = {nxt[0], nxt[1]};
-    if (t + 1 < a.n_ctrl) {
-      const float* af = a.actions + (int64_t)(t + 1) * frame;
-      nxt[0] = c < th.n ? lane_elem(af, oc) : 0.0f;
-      nxt[1] = c + 4 < th.n ? lane_elem(af + 4 * a.E, oc) : 0.0f;
-    }
+    float act[2] = {nxt[0], nxt[1]};
+    quad_mask_pair(thr_in, act);
+    if (t + 1 < a.n_ctrl) quad_load_pair(thr_in, a.actions + (int64_t)(t + 1) * frame, nxt);
     float gl, ga, dl, da;
     quad_command<LAG>(th, act, cc->kappa_s, x, gl, ga, dl, da);
     for (int s = 0; s < a.substeps; ++s) {
@@ -241,8 +237,10 @@ __global__ void __launch_bounds__(kQuadBlock) k_split_quad(const SplitArgs a,
         lane_elem(tf + 7 * a.E, oi) = x.v;
         lane_elem(tf + 10 * a.E, oi) = x.w;
       }
-      if (13 + c < a.D) lane_elem(tf + 13 * a.E, oc) = f0 ? x.f[0] : 0.0f;
-      if (17 + c < a.D) lane_elem(tf + 17 * a.E, oc) = f1 ? x.f[1] : 0.0f;
+      if constexpr (LAG) {   // zeros past the class's own
+        if (13 + c < a.D) lane_elem(tf + 13 * a.E, oc) = x.f[0];
+        if (17 + c < a.D) lane_elem(tf + 17 * a.E, oc) = x.f[1];
+      }
     }
   }
   if (!active) return;
@@ -254,8 +252,7 @@ __global__ void __launch_bounds__(kQuadBlock) k_split_quad(const SplitArgs a,
     lane_elem(a.acc, ji) = al;
     lane_elem(a.acc + 3 * a.Ep, ji) = aa;
   }
-  if (f0) lane_elem(a.state + 13 * a.Ep, jc) = x.f[0];
-  if (f1) lane_elem(a.state + 17 * a.Ep, jc) = x.f[1];
+  if constexpr (LAG) quad_store_pair(fs, a.state + 13 * a.Ep, x.f);
 }
 
 #pragma clang fp contract(fast)

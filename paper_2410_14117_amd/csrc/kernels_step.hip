@@ -170,7 +170,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))
 k_step_classes(const StepArgs a, const ClassSegs segs) {
   constexpr int D = Dims<N, LAG>::D;
   int block;
-  const int k = block_class(segs, block);
+  const int k = block_class(segs, blockIdx.x, block);
   const ClassConst* ccp = segs.cc + k;
   auto class_const = [&]() { return scalar_class_const(pin_sgpr(ccp)); };
   const int64_t seg_start = segs.start[k], seg_len = segs.len[k];
@@ -391,14 +391,15 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
   QuadThr th;
   load_quad_thr(cc, c, th);
   const int n_f = th.lag ? th.n : 0;     // lag states of this class
-  const bool f0 = c < n_f, f1 = c + 4 < n_f;
+  const QuadPair fs = quad_pair(c, n_f, j4, s4);   // lag states, internal rows
+  const QuadPair ta = quad_pair(c, th.n, c4, e4);  // throttles, caller rows
   QuadState x;
   x.p = lane_elem(a.state, ji);
   x.q = lane_elem(a.state + 3 * a.Ep, jc);
   x.v = lane_elem(a.state + 7 * a.Ep, ji);
   x.w = lane_elem(a.state + 10 * a.Ep, ji);
-  x.f[0] = f0 ? lane_elem(a.state + 13 * a.Ep, jc) : 0.0f;
-  x.f[1] = f1 ? lane_elem(a.state + 17 * a.Ep, jc) : 0.0f;
+  x.f[0] = x.f[1] = 0.0f;
+  if constexpr (LAG) quad_load_pair(fs, a.state + 13 * a.Ep, x.f);
   bool frozen = lane_elem(a.flags, j) != 0;
   const QuadStep sc = quad_step_const(cc, a.dt);
   QuadConst C;
@@ -407,10 +408,10 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
   // each control step's throttles are loaded one step ahead
   const int64_t frame = (int64_t)a.n_max * a.E;
   float nxt[2];
-  nxt[0] = c < th.n ? lane_elem(a.actions, oc) : 0.0f;
-  nxt[1] = c + 4 < th.n ? lane_elem(a.actions + 4 * a.E, oc) : 0.0f;
+  quad_load_pair(ta, a.actions, nxt);
   float tg = 0.0f;
   if (a.partials && a.targets) tg = lane_elem(a.targets, oi);
+  if constexpr (LAG) quad_mask_pair(fs, x.f);
 
   auto quad_finite = [&]() {
     int ok = isfinite(x.q) && isfinite(x.f[0]) && isfinite(x.f[1]) &&
@@ -421,12 +422,9 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
   };
   bool bad = false;     // EACH: went non-finite in this launch
   for (int t = 0; t < a.n_ctrl; ++t) {
-    const float act[2] = {nxt[0], nxt[1]};
-    if (t + 1 < a.n_ctrl) {
-      const float* af = a.actions + (int64_t)(t + 1) * frame;
-      nxt[0] = c < th.n ? lane_elem(af, oc) : 0.0f;
-      nxt[1] = c + 4 < th.n ? lane_elem(af + 4 * a.E, oc) : 0.0f;
-    }
+    float act[2] = {nxt[0], nxt[1]};
+    quad_mask_pair(ta, act);
+    if (t + 1 < a.n_ctrl) quad_load_pair(ta, a.actions + (int64_t)(t + 1) * frame, nxt);
     QuadState x0;
     if constexpr (EACH) x0 = x;
     if (!frozen) quad_control_step<LAG>(L, C, M, th, sc, act, x, a.substeps);
@@ -438,8 +436,10 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
         lane_elem(tf + 7 * a.E, oi) = x.v;
         lane_elem(tf + 10 * a.E, oi) = x.w;
       }
-      if (13 + c < a.D) lane_elem(tf + 13 * a.E, oc) = f0 ? x.f[0] : 0.0f;
-      if (17 + c < a.D) lane_elem(tf + 17 * a.E, oc) = f1 ? x.f[1] : 0.0f;
+      if constexpr (LAG) {   // zeros past the class's own
+        if (13 + c < a.D) lane_elem(tf + 13 * a.E, oc) = x.f[0];
+        if (17 + c < a.D) lane_elem(tf + 17 * a.E, oc) = x.f[1];
+      }
     }
     bool finite = true;
     if (EACH || a.partials) finite = quad_finite();
@@ -477,8 +477,7 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
       lane_elem(a.state + 7 * a.Ep, ji) = x.v;
       lane_elem(a.state + 10 * a.Ep, ji) = x.w;
     }
-    if (f0) lane_elem(a.state + 13 * a.Ep, jc) = x.f[0];
-    if (f1) lane_elem(a.state + 17 * a.Ep, jc) = x.f[1];
+    if constexpr (LAG) quad_store_pair(fs, a.state + 13 * a.Ep, x.f);
   } else {
     if constexpr (EACH) {
       // frozen part-way: the state is the input of the step that failed
@@ -488,8 +487,7 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
         lane_elem(a.state + 7 * a.Ep, ji) = x.v;
         lane_elem(a.state + 10 * a.Ep, ji) = x.w;
       }
-      if (f0) lane_elem(a.state + 13 * a.Ep, jc) = x.f[0];
-      if (f1) lane_elem(a.state + 17 * a.Ep, jc) = x.f[1];
+      if constexpr (LAG) quad_store_pair(fs, a.state + 13 * a.Ep, x.f);
     }
     if (c == 0)
       lane_elem(a.flags, j) = (uint8_t)(lane_elem(a.flags, j) | kFlagNonFinite);

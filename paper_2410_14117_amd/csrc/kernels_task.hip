@@ -134,7 +134,7 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))
 k_task(const TaskArgs a, const ClassSegs segs, const TaskConst tc) {
   constexpr int D = Dims<N, LAG>::D;
   int block;
-  const int cls = block_class(segs, block);
+  const int cls = block_class(segs, blockIdx.x, block);
   const ClassConst* ccp = segs.cc + cls;
   const int64_t local = (int64_t)block * kBlock + threadIdx.x;
   if (local >= segs.len[cls]) return;
@@ -234,7 +234,7 @@ template <bool LAG>
 __global__ void __launch_bounds__(kQuadBlock) k_task_quad(const TaskArgs a, const ClassSegs segs,
                                                           const TaskConst tc) {
   int block;
-  const int cls = block_class(segs, block);
+  const int cls = block_class(segs, blockIdx.x, block);
   const ClassConst* __restrict__ cc = segs.cc + cls;
   const QuadLane L = quad_lane(threadIdx.x);
   const int c = L.c, ci = c > 1 ? c - 1 : 0;
@@ -253,14 +253,15 @@ __global__ void __launch_bounds__(kQuadBlock) k_task_quad(const TaskArgs a, cons
   QuadThr th;
   load_quad_thr(cc, c, th);
   const int n_f = th.lag ? th.n : 0;
-  const bool f0 = c < n_f, f1 = c + 4 < n_f;
+  const QuadPair fs = quad_pair(c, n_f, j4, s4);     // lag states, internal rows
+  const QuadPair thr_in = quad_pair(c, th.n, c4, e4);  // throttles, caller rows
   QuadState x;
   x.p = lane_elem(a.state, ji);
   x.q = lane_elem(a.state + 3 * a.Ep, jc);
   x.v = lane_elem(a.state + 7 * a.Ep, ji);
   x.w = lane_elem(a.state + 10 * a.Ep, ji);
-  x.f[0] = f0 ? lane_elem(a.state + 13 * a.Ep, jc) : 0.0f;
-  x.f[1] = f1 ? lane_elem(a.state + 17 * a.Ep, jc) : 0.0f;
+  x.f[0] = x.f[1] = 0.0f;
+  if constexpr (LAG) quad_load_pair(fs, a.state + 13 * a.Ep, x.f);
   int32_t k = lane_elem(a.task_k, j4);
   const double cen[3] = {lane_elem(a.task_f, j4), lane_elem(a.task_f + a.Ep, j4),
                          lane_elem(a.task_f + 2 * a.Ep, j4)};
@@ -268,12 +269,13 @@ __global__ void __launch_bounds__(kQuadBlock) k_task_quad(const TaskArgs a, cons
   const double yaw = lane_elem(a.task_f + 4 * a.Ep, j4);
   if (a.actions) {
     float act[2];
-    act[0] = c < th.n ? lane_elem(a.actions, oc) : 0.0f;
-    act[1] = c + 4 < th.n ? lane_elem(a.actions + 4 * a.E, oc) : 0.0f;
+    quad_load_pair(thr_in, a.actions, act);
     const QuadStep sc = quad_step_const(cc, a.dt);
     QuadConst C;
     QuadMass M;
     load_quad_const(a.derived, a.Ep, j4, c, sc.h2, C, M);
+    quad_mask_pair(thr_in, act);
+    if constexpr (LAG) quad_mask_pair(fs, x.f);
     quad_control_step<LAG>(L, C, M, th, sc, act, x, a.substeps);
     k += 1;
   }
@@ -306,8 +308,10 @@ __global__ void __launch_bounds__(kQuadBlock) k_task_quad(const TaskArgs a, cons
         x.q = lane_elem(a.reset_state + 3 * a.E, oc);
         x.v = lane_elem(a.reset_state + 7 * a.E, oi);
         x.w = lane_elem(a.reset_state + 10 * a.E, oi);
-        if (f0) x.f[0] = lane_elem(a.reset_state + 13 * a.E, oc);
-        if (f1) x.f[1] = lane_elem(a.reset_state + 17 * a.E, oc);
+        if constexpr (LAG) {
+          quad_load_pair(quad_pair(c, n_f, c4, e4), a.reset_state + 13 * a.E, x.f);
+          quad_mask_pair(fs, x.f);
+        }
       }
       k = 0;
       curve_sincos(tc, 0.0, phase, sn, cs);
@@ -328,8 +332,7 @@ __global__ void __launch_bounds__(kQuadBlock) k_task_quad(const TaskArgs a, cons
       } else {
         lane_elem(a.task_k, j4) = k;
       }
-      if (f0) lane_elem(a.state + 13 * a.Ep, jc) = x.f[0];
-      if (f1) lane_elem(a.state + 17 * a.Ep, jc) = x.f[1];
+      if constexpr (LAG) quad_store_pair(fs, a.state + 13 * a.Ep, x.f);
     }
   }
   position(p);

@@ -49,12 +49,11 @@ float* noalloc_scratch(int device) {
   return g_noalloc_ptr[device];
 }
 
-// Most waves per SIMD of a launch with one env per quad of lanes (step and
-// adjoint).  At two waves per SIMD the quad kernels are level with one env per
-// lane (32 768 envs, forward / backward of 16 control steps: 29.1 / 56.2
-// against 27.8 / 59.3 us for 6 thrusters without lag, 72.8 / 260 against 74.8 /
-// 258 us for 8 with lag and 4 sub-steps; 16 384 envs: 22.1 / 35.9 against 28.0 /
-// 57.9 us and 48.3 / 162 against 74.3 / 252 us).
+// Most waves per SIMD of a launch with one env per quad of lanes.  At two waves
+// per SIMD the quad kernels are level with one env per lane: 32 768 envs, one
+// launch of 16 control steps, adjoint forward / backward 29.1 / 56.2 against
+// 27.8 / 59.3 us without lag, 72.8 / 260 against 74.8 / 258 us with; the step's
+// 59.5 against 61.7 us for 4 control steps of 16 sub-steps.
 #ifndef MG_QUAD_WAVES
 #define MG_QUAD_WAVES 1
 #endif
@@ -110,7 +109,7 @@ struct mg_sim {
   uint8_t* class_of = nullptr; // [Ep]
   uint8_t* flags = nullptr;    // [Ep] status flags (kFlagNonFinite, kFlagNotSPD)
   ClassNominal* nominal_dev = nullptr;
-  ClassConst* cc_dev = nullptr;      // device copy of cc
+  ClassConst* cc_dev = nullptr;      // device copy of cc, behind nominal_dev's entries
   double* partials = nullptr;
   size_t partials_cap = 0;     // doubles
   float* staging = nullptr;    // [max(D,23)][E] for host copies with a permuted layout
@@ -711,12 +710,17 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
     return code;
   };
   const size_t Ep = (size_t)s->Ep;
+  // the classes' nominal parameters and, behind them, their constants: one buffer
+  const size_t nominal_bytes = sizeof(ClassNominal) * s->n_classes;
+  std::vector<char> class_tables(nominal_bytes + sizeof(ClassConst) * s->n_classes);
+  std::memcpy(class_tables.data(), s->nominal.data(), nominal_bytes);
+  std::memcpy(class_tables.data() + nominal_bytes, s->cc.data(),
+              sizeof(ClassConst) * s->n_classes);
   if (hipMalloc(&s->state, Ep * s->D * sizeof(float)) != hipSuccess ||
       hipMalloc(&s->params, Ep * kNumParams * sizeof(float)) != hipSuccess ||
       hipMalloc(&s->derived, Ep * kNumDerived * sizeof(float)) != hipSuccess ||
       hipMalloc(&s->class_of, Ep) != hipSuccess || hipMalloc(&s->flags, Ep) != hipSuccess ||
-      hipMalloc(&s->nominal_dev, sizeof(ClassNominal) * s->n_classes) != hipSuccess ||
-      hipMalloc(&s->cc_dev, sizeof(ClassConst) * s->n_classes) != hipSuccess ||
+      hipMalloc(&s->nominal_dev, class_tables.size()) != hipSuccess ||
       hipMalloc(&s->staging, (size_t)E * std::max(s->D, kNumParams) * sizeof(float)) != hipSuccess ||
       (!identity && (hipMalloc(&s->perm, Ep * sizeof(int32_t)) != hipSuccess ||
                      hipMalloc(&s->iperm, (size_t)E * sizeof(int32_t)) != hipSuccess))) {
@@ -729,15 +733,15 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
       hipMemset(s->derived, 0, Ep * kNumDerived * sizeof(float)) != hipSuccess ||
       hipMemset(s->flags, 0, Ep) != hipSuccess ||
       hipMemcpy(s->class_of, cls.data(), Ep, hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(s->nominal_dev, s->nominal.data(), sizeof(ClassNominal) * s->n_classes,
-                hipMemcpyHostToDevice) != hipSuccess ||
-      hipMemcpy(s->cc_dev, s->cc.data(), sizeof(ClassConst) * s->n_classes,
-                hipMemcpyHostToDevice) != hipSuccess ||
+      hipMemcpy(s->nominal_dev, class_tables.data(), class_tables.size(), hipMemcpyHostToDevice) !=
+          hipSuccess ||
       (!identity && (hipMemcpy(s->perm, perm.data(), Ep * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess ||
                      hipMemcpy(s->iperm, iperm.data(), (size_t)E * sizeof(int32_t), hipMemcpyHostToDevice) != hipSuccess))) {
     (void)hipGetLastError();
     return bail(MG_ERR_DEVICE, "device initialisation failed in mg_create");
   }
+  s->cc_dev = reinterpret_cast<ClassConst*>(reinterpret_cast<char*>(s->nominal_dev) +
+                                            nominal_bytes);
   s->quad.cc = s->lanes.cc = s->cc_dev;
   // the debug build's failed-check word; MG_DEBUG_SHRINK=k (read here, debug
   // build only) makes the kernels treat caller columns >= E - k as out of
@@ -794,7 +798,7 @@ void mg_destroy(mg_sim* s) {
     for (hipEvent_t e : s->ev_fork) (void)hipEventDestroy(e);
     for (hipEvent_t e : s->ev_join) (void)hipEventDestroy(e);
     void* bufs[] = {s->state, s->params, s->derived, s->perm, s->iperm, s->class_of, s->flags,
-                    s->nominal_dev, s->cc_dev, s->partials, s->staging, s->segbuf, s->task_f, s->task_k,
+                    s->nominal_dev, s->partials, s->staging, s->segbuf, s->task_f, s->task_k,
                     s->split_acc, s->dbg.word};
     for (void* b : bufs)
       if (b) (void)hipFree(b);

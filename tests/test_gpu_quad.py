@@ -113,15 +113,17 @@ def _grads(mg, classes, cls, x0, act, mult, g, S, K, mode, E):
 
 
 @pytest.mark.parametrize("fleet,S,T,K,mode,sizes", [
-    ("heavy", 3, 5, 2, "ckpt", (1, 17, 16384)),
+    ("heavy", 3, 5, 2, "ckpt", (1, 17, 4096, 4097, 8192, 8193, 16384)),
     ("heavy", 2, 4, 4, "noalloc", (33,)),       # one segment, recomputed ahead of the sweep
-    ("bluerov2", 1, 7, 3, "traj", (16, 1001)),
-    ("three", 1, 4, 2, "ckpt", (49,)),
-    ("mixed", 2, 5, 2, "ckpt", (2, 1001)),
-    ("lag_and_not", 1, 5, 2, "traj", (1001,)),
+    ("bluerov2", 1, 7, 3, "traj", (16, 1001, 5001, 9000)),
+    ("three", 1, 1, 2, "ckpt", (49, 5000)),     # a single sub-step
+    ("mixed", 2, 5, 2, "ckpt", (2, 1001, 4100)),
+    ("lag_and_not", 1, 5, 2, "traj", (1001, 6000, 10000)),
 ])
 def test_quad_adjoint_equals_one_env_per_lane(mgmod, fleet, S, T, K, mode, sizes):
-    """Checkpoints, trajectory, final state and every gradient, bitwise."""
+    """Checkpoints, trajectory, final state and every gradient, bitwise; on 256 compute units
+    the sweep takes three waves per 16 envs up to 4096 envs, blocks of two such groups up to
+    8192 and one wave beyond."""
     classes = FLEETS[fleet]
     cls, x0, act, mult = _inputs(classes, BIG, T, 31)
     g = np.random.default_rng(35).standard_normal((T,) + x0.shape).astype(np.float32)
