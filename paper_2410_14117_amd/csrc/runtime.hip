@@ -617,11 +617,15 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
   }
   const int64_t E = cfg->n_envs;
   std::vector<int64_t> count(cfg->n_classes, 0);
+  bool in_order = true;   // the envs come class by class
   if (cfg->env_class) {
+    int32_t last = 0;
     for (int64_t e = 0; e < E; ++e) {
       const int32_t c = cfg->env_class[e];
       if (c < 0 || c >= cfg->n_classes) return fail(nullptr, MG_ERR_INVALID, "env_class out of range");
       ++count[c];
+      in_order = in_order && c >= last;
+      last = c;
     }
   } else {
     count[0] = E;
@@ -686,22 +690,27 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
   for (int k = 0; k < cfg->n_classes; ++k)
     s->lanes.blk_end[k] = k + 1 < cfg->n_classes ? s->seg_blk_off[k + 1] : blk;
   s->quad_on = s->Ep <= kQuadMaxEnvs && quad_blk <= (int64_t)n_cu * 4 * MG_QUAD_WAVES;
-  std::vector<int32_t> perm(s->Ep, -1), iperm(E);
-  std::vector<uint8_t> cls(s->Ep, 0);
-  {
+  // caller and internal order are the same if the envs come class by class and
+  // no segment but the last needs padding
+  bool identity = in_order;
+  for (int64_t k = 0, first = 0; k < cfg->n_classes; first += count[k++])
+    identity = identity && (count[k] == 0 || s->seg_start[k] == first);
+  std::vector<int32_t> perm, iperm;
+  if (!identity) {
+    perm.assign(s->Ep, -1);
+    iperm.resize(E);
     std::vector<int64_t> fill(s->seg_start);
     for (int64_t e = 0; e < E; ++e) {
-      const int32_t c = cfg->env_class ? cfg->env_class[e] : 0;
-      const int64_t j = fill[c]++;
+      const int64_t j = fill[cfg->env_class[e]]++;
       perm[j] = (int32_t)e;
       iperm[e] = (int32_t)j;
     }
-    for (int k = 0; k < cfg->n_classes; ++k)
-      for (int64_t j = s->seg_start[k]; j < s->seg_start[k] + ((count[k] + kSegAlign - 1) / kSegAlign) * kSegAlign; ++j)
-        cls[j] = (uint8_t)k;
   }
-  bool identity = true;
-  for (int64_t e = 0; e < E && identity; ++e) identity = iperm[e] == e;
+  std::vector<uint8_t> cls(s->Ep, 0);
+  for (int k = 0; k < cfg->n_classes; ++k)
+    if (count[k])
+      std::memset(cls.data() + s->seg_start[k], k,
+                  (count[k] + kSegAlign - 1) / kSegAlign * kSegAlign);
 
   DeviceGuard g(s->device);
   auto bail = [&](mg_status code, const std::string& msg) {
