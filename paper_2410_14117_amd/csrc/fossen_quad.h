@@ -402,6 +402,39 @@ __device__ __forceinline__ void quad_control_step(const QuadLane& L, const QuadC
   for (int i = 0; i < S; ++i) quad_substep<LAG>(L, C, s, x, ml, ma, gl, ga, dl, da);
 }
 
+__device__ __forceinline__ double quad_sum(double x) {
+  x += qperm<MG_QP(1, 0, 3, 2)>(x);
+  return x + qperm<MG_QP(2, 3, 0, 1)>(x);
+}
+
+// A wave's part of the episode statistics, in every quad: lane c takes statistic
+// c, the sum of the distances to the targets (lane c's component tg), their
+// maximum, the kinetic energy and the count of frozen envs; good: active and not
+// frozen.  Quads of a row of 16 lanes by DPP rotations, rows through LDS.
+__device__ __forceinline__ double quad_stats(int c, const QuadMass& M, float p, float v, float w,
+                                             float tg, bool active, bool good) {
+  const double dd = c > 0 ? (double)p - tg : 0.0;
+  const double vd = v, wd = w;
+  const double al = (double)M.l * vd + (double)M.cl * qperm<kSwapXY>(w);
+  const double aa = (double)M.a * wd + (double)M.ca * qperm<kSwapXY>(v);
+  const double dist = sqrt(quad_sum(dd * dd));
+  const double ke = 0.5 * quad_sum(c > 0 ? vd * al + wd * aa : 0.0);
+  double s = c == 3 ? (active && !good ? 1.0 : 0.0) : (good ? (c == 2 ? ke : dist) : 0.0);
+  auto join = [&](double o) { s = c == 1 ? fmax(s, o) : s + o; };
+  join(qperm<0x124>(s));   // row_ror:4
+  join(qperm<0x128>(s));   // row_ror:8
+  join(__shfl_xor(s, 16, 64));
+  join(__shfl_xor(s, 32, 64));
+  return s;
+}
+
+// An LDS-only barrier: loads in flight stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
 #pragma clang fp contract(fast)
 
 }  // namespace mg

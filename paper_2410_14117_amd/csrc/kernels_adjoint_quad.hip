@@ -1,12 +1,13 @@
-// kernels_adjoint_quad.hip -- the adjoint's kernels with one env per quad of
-// lanes and all classes in one launch (fossen_quad_adjoint.h), for sims too
-// small to fill the GPU with one env per lane: a launch then lasts as long as
-// one env's chain of sub-steps, at 2.1 ns an instruction for a lone wave.  Results
-// are bitwise those of kernels_adjoint.hip.  16 control steps, one env per lane and
-// here, forward / backward: 1000 envs without lag, one sub-step 27.6 / 55.7 ->
-// 16.1 / 19.5 us; 8192 28.8 / 56.6 -> 17.5 / 23.5; 16 384 28.0 / 57.9 -> 19.8 / 32.8;
-// with lag and four sub-steps, 1000 envs 72 / 244 -> 39 / 88, 8192 74 / 251 ->
-// 42 / 103, 16 384 74 / 252 -> 44 / 149.
+// kernels_adjoint_quad.hip -- the adjoint's recomputation and reverse sweep with
+// one env per quad of lanes and all classes in one launch (fossen_quad_adjoint.h),
+// for sims too small to fill the GPU with one env per lane (their forward is
+// k_roll_quad): a launch then lasts as long as one env's chain of sub-steps, at
+// 2.1 ns an instruction for a lone wave.  Results are bitwise those of
+// kernels_adjoint.hip.  16 control steps, one env per lane and here, forward /
+// backward: 1000 envs without lag, one sub-step 27.6 / 55.7 -> 12.1 / 19.7 us; 8192
+// 28.8 / 56.6 -> 14.0 / 23.0; 16 384 28.0 / 57.9 -> 17.0 / 33.1; with lag and four
+// sub-steps, 1000 envs 72 / 244 -> 33 / 87, 8192 74 / 251 -> 37 / 102, 16 384
+// 74 / 252 -> 40 / 149.
 #include "fossen_quad_adjoint.h"
 
 namespace mg {
@@ -89,50 +90,6 @@ __device__ __forceinline__ void quad_load_throttles(const AdjArgs& a, const Quad
 }
 
 }  // namespace
-
-template <bool LAG>
-__global__ void __launch_bounds__(kQuadBlock) k_adj_quad_fwd(const AdjArgs a,
-                                                             const ClassSegs segs) {
-  const QuadPlace p = quad_place(segs, a, blockIdx.x);
-  const ClassConst* __restrict__ cc = segs.cc + p.cls;
-  const QuadLane L = quad_lane(threadIdx.x);
-  QuadThr th;
-  load_quad_thr(cc, p.c, th);
-  QuadState x;
-  x.p = lane_elem(a.state, p.ji);
-  quad_load_state<LAG>(a.state, a.Ep, p.ji, p.jc, p.jf, x);
-  const QuadStep sc = quad_step_const(cc, a.dt);
-  QuadConst C;
-  QuadMass M;
-  load_quad_const(a.derived, a.Ep, p.j4, p.c, sc.h2, C, M);
-  float nxt[2];
-  quad_load_throttles(a, p, 0, nxt);
-  if constexpr (LAG) quad_mask_pair(p.jf, x.f);
-  float* ck = a.ckpt;
-  int until = 0;   // control steps to the next checkpoint
-  for (int t = 0; t < a.T; ++t) {
-    float act[2] = {nxt[0], nxt[1]};
-    quad_mask_pair(p.oa, act);
-    if (t + 1 < a.T) quad_load_throttles(a, p, t + 1, nxt);
-    if (until == 0) {
-      if (p.active) quad_store_caller<LAG>(ck, a, p, x.p, x.q, x.v, x.w, x.f);
-      ck += a.D * a.E;
-      until = a.ckpt_every;
-    }
-    --until;
-    quad_control_step<LAG>(L, C, M, th, sc, act, x, a.substeps);
-    if (p.active && a.traj)
-      quad_store_caller<LAG>(a.traj + (int64_t)t * a.D * a.E, a, p, x.p, x.q, x.v, x.w, x.f);
-  }
-  if (!p.active) return;
-  lane_elem(a.state + 3 * a.Ep, p.jc) = x.q;
-  if (p.c > 0) {
-    lane_elem(a.state, p.ji) = x.p;
-    lane_elem(a.state + 7 * a.Ep, p.ji) = x.v;
-    lane_elem(a.state + 10 * a.Ep, p.ji) = x.w;
-  }
-  if constexpr (LAG) quad_store_pair(p.jf, a.state + 13 * a.Ep, x.f);
-}
 
 // Every segment's sub-step inputs at once (blockIdx.y = segment) into the
 // whole-rollout segbuf.  Position rows are left out: the sweep reads none.
@@ -320,13 +277,6 @@ k_adj_quad_bwd(const AdjArgs a, const ClassSegs segs) {
 // sub-step, 400-500 in wave 1's, 250-300 in wave 2's.
 constexpr int kTrioIn = 17, kTrioTheta = 5, kTrioOut = 4;   // columns
 constexpr int kTrioColumns = 2 * kTrioIn + 3 * kTrioTheta + 2 * kTrioOut;
-
-// An LDS-only barrier: loads in flight stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // PAIR: two groups of 16 envs to a block of eight waves, one block to a CU, for
 // launches of more groups than CUs.  A block's waves go to the CU's four SIMDs in
@@ -527,16 +477,6 @@ k_adj_quad_bwd_trio(const AdjArgs a, const ClassSegs segs) {
 
 // 32-bit offsets of a state's rows
 static bool quad_fits(const AdjArgs& a) { return a.Ep <= kQuadMaxEnvs && a.E <= kQuadMaxEnvs; }
-
-hipError_t launch_adj_quad_fwd(const ClassSegs& q, const AdjArgs& a, bool lag, hipStream_t s) {
-  if (!quad_fits(a)) return hipErrorInvalidValue;
-  const dim3 grid((unsigned)q.blk_end[q.n - 1]);
-  if (lag)
-    hipLaunchKernelGGL((k_adj_quad_fwd<true>), grid, dim3(kQuadBlock), 0, s, a, q);
-  else
-    hipLaunchKernelGGL((k_adj_quad_fwd<false>), grid, dim3(kQuadBlock), 0, s, a, q);
-  return hipGetLastError();
-}
 
 hipError_t launch_adj_quad_recompute(const ClassSegs& q, const AdjArgs& a, bool lag,
                                      hipStream_t s) {

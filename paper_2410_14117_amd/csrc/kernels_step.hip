@@ -360,16 +360,11 @@ hipError_t launch_step_classes(const ClassSegs& segs, const StepArgs& a, bool la
 // lane, which last as long as one wave's instruction chain.
 // ---------------------------------------------------------------------------
 
-__device__ __forceinline__ double quad_sum(double x) {
-  x += qperm<MG_QP(1, 0, 3, 2)>(x);
-  return x + qperm<MG_QP(2, 3, 0, 1)>(x);
-}
-
-template <bool LAG, bool EACH>
+// one control step
+template <bool LAG>
 __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, const ClassSegs segs) {
-  int k = 0;
-  while (k + 1 < segs.n && (int)blockIdx.x >= segs.blk_end[k]) ++k;
-  const int blk0 = k > 0 ? segs.blk_end[k - 1] : 0;
+  int block;
+  const int k = block_class(segs, blockIdx.x, block);
   const ClassConst* __restrict__ cc = segs.cc + k;
   const int64_t seg_start = segs.start[k], seg_len = segs.len[k];
   const int lane = threadIdx.x;
@@ -377,7 +372,7 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
   const int c = L.c, ci = c > 1 ? c - 1 : 0;
   // the four lanes of a quad share every condition below, so a DPP exchange
   // never reads a lane that is switched off
-  const int64_t local = (int64_t)((int)blockIdx.x - blk0) * kQuadEnvs + (lane >> 2);
+  const int64_t local = (int64_t)block * kQuadEnvs + (lane >> 2);
   bool active = local < seg_len && MG_CHECK(a, seg_start + seg_len <= a.Ep, kDbgSegment);
   const uint32_t j = (uint32_t)(seg_start + (active ? local : 0));
   const uint32_t j4 = j * 4u;
@@ -405,72 +400,35 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
   QuadConst C;
   QuadMass M;
   load_quad_const(a.derived, a.Ep, j4, c, sc.h2, C, M);
-  // each control step's throttles are loaded one step ahead
-  const int64_t frame = (int64_t)a.n_max * a.E;
-  float nxt[2];
-  quad_load_pair(ta, a.actions, nxt);
+  float act[2];
+  quad_load_pair(ta, a.actions, act);
   float tg = 0.0f;
   if (a.partials && a.targets) tg = lane_elem(a.targets, oi);
   if constexpr (LAG) quad_mask_pair(fs, x.f);
-
-  auto quad_finite = [&]() {
-    int ok = isfinite(x.q) && isfinite(x.f[0]) && isfinite(x.f[1]) &&
-             (c == 0 || (isfinite(x.p) && isfinite(x.v) && isfinite(x.w)));
-    ok &= qperm<MG_QP(1, 0, 3, 2)>(ok);
-    ok &= qperm<MG_QP(2, 3, 0, 1)>(ok);
-    return ok != 0;
-  };
-  bool bad = false;     // EACH: went non-finite in this launch
-  for (int t = 0; t < a.n_ctrl; ++t) {
-    float act[2] = {nxt[0], nxt[1]};
-    quad_mask_pair(ta, act);
-    if (t + 1 < a.n_ctrl) quad_load_pair(ta, a.actions + (int64_t)(t + 1) * frame, nxt);
-    QuadState x0;
-    if constexpr (EACH) x0 = x;
-    if (!frozen) quad_control_step<LAG>(L, C, M, th, sc, act, x, a.substeps);
-    if (a.traj && active) {
-      float* tf = a.traj + (int64_t)t * a.D * a.E;
-      lane_elem(tf + 3 * a.E, oc) = x.q;
-      if (c > 0) {
-        lane_elem(tf, oi) = x.p;
-        lane_elem(tf + 7 * a.E, oi) = x.v;
-        lane_elem(tf + 10 * a.E, oi) = x.w;
-      }
-      if constexpr (LAG) {   // zeros past the class's own
-        if (13 + c < a.D) lane_elem(tf + 13 * a.E, oc) = x.f[0];
-        if (17 + c < a.D) lane_elem(tf + 17 * a.E, oc) = x.f[1];
-      }
+  quad_mask_pair(ta, act);
+  if (!frozen) quad_control_step<LAG>(L, C, M, th, sc, act, x, a.substeps);
+  if (a.traj && active) {
+    lane_elem(a.traj + 3 * a.E, oc) = x.q;
+    if (c > 0) {
+      lane_elem(a.traj, oi) = x.p;
+      lane_elem(a.traj + 7 * a.E, oi) = x.v;
+      lane_elem(a.traj + 10 * a.E, oi) = x.w;
     }
-    bool finite = true;
-    if (EACH || a.partials) finite = quad_finite();
-    if (a.partials) {
-      // lane c of the quad takes statistic c: distance sum, its maximum,
-      // kinetic energy, frozen envs
-      const double dd = c > 0 ? (double)x.p - tg : 0.0;
-      const double v = x.v, w = x.w;
-      const double al = (double)M.l * v + (double)M.cl * qperm<kSwapXY>(x.w);
-      const double aa = (double)M.a * w + (double)M.ca * qperm<kSwapXY>(x.v);
-      const double dist = sqrt(quad_sum(mul_nc(dd, dd)));
-      const double ke = 0.5 * quad_sum(c > 0 ? v * al + w * aa : 0.0);
-      const bool good = finite && !frozen;
-      double s = c == 3 ? (active && !good ? 1.0 : 0.0) : (active && good ? (c == 2 ? ke : dist) : 0.0);
-#pragma unroll
-      for (int off = 4; off < 64; off <<= 1) {
-        const double o = __shfl_xor(s, off, 64);
-        s = c == 1 ? fmax(s, o) : s + o;
-      }
-      if (lane < 4)
-        a.partials[((int64_t)t * a.nblk_total + blockIdx.x) * 4 + lane] = s;
-    }
-    if constexpr (EACH) {
-      if (!finite) {
-        x = x0;
-        frozen = bad = true;
-      }
+    if constexpr (LAG) {   // zeros past the class's own
+      if (13 + c < a.D) lane_elem(a.traj + 13 * a.E, oc) = x.f[0];
+      if (17 + c < a.D) lane_elem(a.traj + 17 * a.E, oc) = x.f[1];
     }
   }
+  int finite = isfinite(x.q) && isfinite(x.f[0]) && isfinite(x.f[1]) &&
+               (c == 0 || (isfinite(x.p) && isfinite(x.v) && isfinite(x.w)));
+  finite &= qperm<MG_QP(1, 0, 3, 2)>(finite);
+  finite &= qperm<MG_QP(2, 3, 0, 1)>(finite);
+  if (a.partials) {
+    const double s = quad_stats(c, M, x.p, x.v, x.w, tg, active, active && finite && !frozen);
+    if (lane < 4) a.partials[(int64_t)blockIdx.x * 4 + lane] = s;
+  }
   if (!active) return;
-  if (EACH ? !bad : quad_finite()) {
+  if (finite) {
     lane_elem(a.state + 3 * a.Ep, jc) = x.q;
     if (c > 0) {
       lane_elem(a.state, ji) = x.p;
@@ -478,20 +436,202 @@ __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, cons
       lane_elem(a.state + 10 * a.Ep, ji) = x.w;
     }
     if constexpr (LAG) quad_store_pair(fs, a.state + 13 * a.Ep, x.f);
-  } else {
-    if constexpr (EACH) {
-      // frozen part-way: the state is the input of the step that failed
-      lane_elem(a.state + 3 * a.Ep, jc) = x.q;
-      if (c > 0) {
-        lane_elem(a.state, ji) = x.p;
-        lane_elem(a.state + 7 * a.Ep, ji) = x.v;
-        lane_elem(a.state + 10 * a.Ep, ji) = x.w;
-      }
-      if constexpr (LAG) quad_store_pair(fs, a.state + 13 * a.Ep, x.f);
-    }
-    if (c == 0)
-      lane_elem(a.flags, j) = (uint8_t)(lane_elem(a.flags, j) | kFlagNonFinite);
+  } else if (c == 0) {   // the input state stays in place
+    lane_elem(a.flags, j) = (uint8_t)(lane_elem(a.flags, j) | kFlagNonFinite);
   }
+}
+
+// Several control steps in two waves per 16 envs.  Only the rigid-body state is
+// serial through the sub-steps; the commands and lag states of the control steps
+// ahead, and the rows and statistics of those behind, are not.  Wave 0 takes the
+// sub-steps; in phase t, while it takes control step t, wave 1 writes what step
+// t - 1 left and forms the wrenches of step t + 1, through LDS; n_ctrl + 1 phases
+// for both waves alike.  The values are those of k_step_quad, bitwise.  4096
+// Heavies, 200 control steps of 4 sub-steps with trajectory and statistics: 551 us
+// in one wave, 403 here, where the sub-steps are 0.50 us each; the adjoint's
+// forward of 16 control steps, 8192 envs, 17.5 -> 14.0 us (one sub-step, no lag)
+// and 42 -> 37 us (four, lag).
+// MODE: frozen as one launch, frozen as one launch per control step, or the
+// adjoint's forward (nothing frozen; checkpoints).
+enum { kRollLaunch, kRollEach, kRollAdjoint };
+
+template <bool LAG, int MODE>
+__global__ void __launch_bounds__(2 * kQuadBlock) k_roll_quad(const StepArgs a,
+                                                              const ClassSegs segs, float* ckpt,
+                                                              int ckpt_every) {
+  __shared__ float4 cmd[2][kQuadBlock];   // command wrench and lag wrench of a control step
+  __shared__ float4 out[2][kQuadBlock];   // position, quaternion, velocities after it
+  __shared__ int status[2][kQuadBlock];   // 1: frozen before it, 2: non-finite after it
+  const int lane = threadIdx.x & (kQuadBlock - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kQuadBlock);
+  int block;
+  const int k = block_class(segs, blockIdx.x, block);
+  const ClassConst* __restrict__ cc = segs.cc + k;
+  const QuadLane L = quad_lane(lane);
+  const int c = L.c, ci = c > 1 ? c - 1 : 0;
+  // the four lanes of a quad share every condition below
+  const int64_t local = (int64_t)block * kQuadEnvs + (lane >> 2);
+  bool active = local < segs.len[k] &&
+                MG_CHECK(a, segs.start[k] + segs.len[k] <= a.Ep, kDbgSegment);
+  const uint32_t j = (uint32_t)(segs.start[k] + (active ? local : 0)), j4 = j * 4u;
+  const int64_t col = active ? (a.perm ? (int64_t)lane_elem(a.perm, j4) : (int64_t)j) : 0;
+  active = active && MG_CHECK(a, col >= 0 && col < a.dbg.cols, kDbgColumn);
+  const uint32_t c4 = active ? (uint32_t)col * 4u : 0u;
+  const uint32_t s4 = (uint32_t)a.Ep * 4u, e4 = (uint32_t)a.E * 4u;
+  const uint32_t ji = j4 + (uint32_t)ci * s4, jc = j4 + (uint32_t)c * s4;   // internal rows
+  const uint32_t oi = c4 + (uint32_t)ci * e4, oc = c4 + (uint32_t)c * e4;   // caller rows
+  const QuadStep sc = quad_step_const(cc, a.dt);
+  QuadConst C;
+  QuadMass M;
+  load_quad_const(a.derived, a.Ep, j4, c, sc.h2, C, M);
+  bool frozen = MODE != kRollAdjoint && lane_elem(a.flags, j) != 0;
+  QuadState x;
+  x.p = lane_elem(a.state, ji);
+  x.q = lane_elem(a.state + 3 * a.Ep, jc);
+  x.v = lane_elem(a.state + 7 * a.Ep, ji);
+  x.w = lane_elem(a.state + 10 * a.Ep, ji);
+  x.f[0] = x.f[1] = 0.0f;
+  const int n = a.n_ctrl;
+  if (wave == 0) {
+    bool bad = false;
+    for (int t = 0; t < n; ++t) {
+      lds_barrier();
+      const float4 u = cmd[t & 1][lane];
+      const QuadState x0 = x;
+      const int was = frozen ? 1 : 0;
+      if (!frozen) {
+        float dl = u.z, da = u.w, ml, ma;
+        quad_momentum(M, x.v, x.w, ml, ma);
+        for (int i = 0; i < a.substeps; ++i)
+          quad_substep<LAG>(L, C, sc, x, ml, ma, u.x, u.y, dl, da);
+      }
+      out[t & 1][lane] = make_float4(x.p, x.q, x.v, x.w);
+      if constexpr (MODE != kRollAdjoint) {
+        // a thruster state that is not finite has made the velocities so
+        int ok = 1;
+        if (MODE == kRollEach || t == n - 1) {
+          ok = isfinite(x.q) && (c == 0 || (isfinite(x.p) && isfinite(x.v) && isfinite(x.w)));
+          ok &= qperm<MG_QP(1, 0, 3, 2)>(ok);
+          ok &= qperm<MG_QP(2, 3, 0, 1)>(ok);
+        }
+        status[t & 1][lane] = was | (ok ? 0 : 2);
+        if (!ok) {
+          bad = true;
+          if constexpr (MODE == kRollEach) {
+            x = x0;
+            frozen = true;
+          }
+        }
+      }
+    }
+    lds_barrier();
+    if (!active) return;
+    if (bad && c == 0)
+      lane_elem(a.flags, j) = (uint8_t)(lane_elem(a.flags, j) | kFlagNonFinite);
+    if (bad && MODE == kRollLaunch) return;   // the launch-input state stays in place
+    lane_elem(a.state + 3 * a.Ep, jc) = x.q;
+    if (c > 0) {
+      lane_elem(a.state, ji) = x.p;
+      lane_elem(a.state + 7 * a.Ep, ji) = x.v;
+      lane_elem(a.state + 10 * a.Ep, ji) = x.w;
+    }
+    return;
+  }
+  QuadThr th;
+  load_quad_thr(cc, c, th);
+  const QuadPair fs = quad_pair(c, th.lag ? th.n : 0, j4, s4);   // lag states, internal rows
+  const QuadPair ta = quad_pair(c, th.n, c4, e4);                // throttles, caller rows
+  if constexpr (LAG) quad_load_pair(fs, a.state + 13 * a.Ep, x.f);
+  const int64_t frame = (int64_t)a.n_max * a.E;
+  float nxt[2];   // throttles, loaded one control step ahead of their use
+  quad_load_pair(ta, a.actions, nxt);
+  float tg = 0.0f;
+  if (a.partials && a.targets) tg = lane_elem(a.targets, oi);
+  if constexpr (LAG) quad_mask_pair(fs, x.f);
+  // lag states before the control step that wave 0 has finished, after it, after
+  // the next, and of an env that is frozen
+  float f0[2] = {0.0f, 0.0f}, f1[2] = {0.0f, 0.0f}, ff[2] = {x.f[0], x.f[1]};
+  int last = frozen ? 1 : 0;
+  auto prepare = [&](int t) {
+    float act[2] = {nxt[0], nxt[1]};
+    quad_mask_pair(ta, act);
+    if (t + 1 < n) quad_load_pair(ta, a.actions + (int64_t)(t + 1) * frame, nxt);
+    f0[0] = f1[0];
+    f0[1] = f1[1];
+    f1[0] = x.f[0];
+    f1[1] = x.f[1];
+    float gl, ga, dl, da;
+    quad_command<LAG>(th, act, th.rho_s, x, gl, ga, dl, da);
+    cmd[t & 1][lane] = make_float4(gl, ga, dl, da);
+  };
+  auto store = [&](float* rows, const float4& u, const float (&f)[2]) {
+    if (!active) return;
+    lane_elem(rows + 3 * a.E, oc) = u.y;
+    if (c > 0) {
+      lane_elem(rows, oi) = u.x;
+      lane_elem(rows + 7 * a.E, oi) = u.z;
+      lane_elem(rows + 10 * a.E, oi) = u.w;
+    }
+    if constexpr (LAG) {   // zeros past the class's own
+      if (13 + c < a.D) lane_elem(rows + 13 * a.E, oc) = f[0];
+      if (17 + c < a.D) lane_elem(rows + 17 * a.E, oc) = f[1];
+    }
+  };
+  int until = ckpt_every;   // control steps to the next checkpoint
+  // fi, fo: lag states before and after control step t
+  auto finish = [&](int t, const float (&fi)[2], const float (&fo)[2]) {
+    const float4 u = out[t & 1][lane];
+    const int st = MODE != kRollAdjoint ? status[t & 1][lane] : 0;
+    last = st;
+    const bool was = (st & 1) != 0;
+    const float f[2] = {was ? ff[0] : fo[0], was ? ff[1] : fo[1]};
+    if (a.traj) store(a.traj + (int64_t)t * a.D * a.E, u, f);
+    if constexpr (MODE == kRollAdjoint) {
+      if (--until == 0) {
+        ckpt += a.D * a.E;
+        until = ckpt_every;
+        if (t + 1 < n) store(ckpt, u, f);
+      }
+    }
+    if (a.partials) {
+      int ok = isfinite(u.y) && isfinite(f[0]) && isfinite(f[1]) &&
+               (c == 0 || (isfinite(u.x) && isfinite(u.z) && isfinite(u.w)));
+      ok &= qperm<MG_QP(1, 0, 3, 2)>(ok);
+      ok &= qperm<MG_QP(2, 3, 0, 1)>(ok);
+      const double s = quad_stats(c, M, u.x, u.z, u.w, tg, active, active && ok && !was);
+      if (lane < 4) a.partials[((int64_t)t * a.nblk_total + blockIdx.x) * 4 + lane] = s;
+    }
+    if constexpr (MODE == kRollEach) {
+      if (!was && (st & 2)) {   // frozen from here on at the step's input
+        ff[0] = fi[0];
+        ff[1] = fi[1];
+      }
+    }
+  };
+  if constexpr (MODE == kRollAdjoint) store(ckpt, make_float4(x.p, x.q, x.v, x.w), x.f);
+  prepare(0);
+  for (int t = 0; t < n; ++t) {
+    lds_barrier();
+    if (t > 0) finish(t - 1, f0, f1);
+    if (t + 1 < n) prepare(t + 1);
+  }
+  lds_barrier();
+  finish(n - 1, f1, x.f);
+  if constexpr (LAG) {
+    if (!active || (MODE == kRollLaunch && (last & 2))) return;
+    const float f[2] = {last ? ff[0] : x.f[0], last ? ff[1] : x.f[1]};
+    quad_store_pair(fs, a.state + 13 * a.Ep, f);
+  }
+}
+
+template <int MODE>
+static void launch_roll(const ClassSegs& q, const StepArgs& a, bool lag, float* ckpt,
+                        int32_t ckpt_every, hipStream_t s) {
+  const dim3 grid((unsigned)q.blk_end[q.n - 1]), block(2 * kQuadBlock);
+  if (lag)
+    hipLaunchKernelGGL((k_roll_quad<true, MODE>), grid, block, 0, s, a, q, ckpt, ckpt_every);
+  else
+    hipLaunchKernelGGL((k_roll_quad<false, MODE>), grid, block, 0, s, a, q, ckpt, ckpt_every);
 }
 
 hipError_t launch_step_quad(const ClassSegs& q, const StepArgs& a, bool lag, bool each_step,
@@ -500,14 +640,22 @@ hipError_t launch_step_quad(const ClassSegs& q, const StepArgs& a, bool lag, boo
   if (nblk == 0) return hipSuccess;
   if (a.Ep > kQuadMaxEnvs || a.E > kQuadMaxEnvs) return hipErrorInvalidValue;
   const dim3 grid((unsigned)nblk), block(kQuadBlock);
-  if (lag && each_step)
-    hipLaunchKernelGGL((k_step_quad<true, true>), grid, block, 0, s, a, q);
+  // (frozen at the launch's input and at the control step's are the same for one)
+  if (a.n_ctrl > 1 && each_step)
+    launch_roll<kRollEach>(q, a, lag, nullptr, 1, s);
+  else if (a.n_ctrl > 1)
+    launch_roll<kRollLaunch>(q, a, lag, nullptr, 1, s);
   else if (lag)
-    hipLaunchKernelGGL((k_step_quad<true, false>), grid, block, 0, s, a, q);
-  else if (each_step)
-    hipLaunchKernelGGL((k_step_quad<false, true>), grid, block, 0, s, a, q);
+    hipLaunchKernelGGL((k_step_quad<true>), grid, block, 0, s, a, q);
   else
-    hipLaunchKernelGGL((k_step_quad<false, false>), grid, block, 0, s, a, q);
+    hipLaunchKernelGGL((k_step_quad<false>), grid, block, 0, s, a, q);
+  return hipGetLastError();
+}
+
+hipError_t launch_forward_quad(const ClassSegs& q, const StepArgs& a, bool lag, float* ckpt,
+                               int32_t ckpt_every, hipStream_t s) {
+  if (a.Ep > kQuadMaxEnvs || a.E > kQuadMaxEnvs) return hipErrorInvalidValue;
+  launch_roll<kRollAdjoint>(q, a, lag, ckpt, ckpt_every, s);
   return hipGetLastError();
 }
 

@@ -309,12 +309,15 @@ constexpr int64_t kQuadMaxEnvs = (int64_t)1 << 20;
 // else at the launch's input.
 hipError_t launch_step_quad(const ClassSegs& q, const StepArgs& a, bool lag, bool each_step,
                             hipStream_t s);
+// The adjoint's forward: as above, but no env is frozen, and the state before
+// every ckpt_every-th control step is stored in ckpt.
+hipError_t launch_forward_quad(const ClassSegs& q, const StepArgs& a, bool lag, float* ckpt,
+                               int32_t ckpt_every, hipStream_t s);
 
 // The adjoint's kernels with one env per quad of lanes, all classes in one
-// launch (kernels_adjoint_quad.hip; seg_start, seg_len and zb of AdjArgs unused):
-// the forward, the recomputation of every segment's sub-step inputs into the
+// launch (kernels_adjoint_quad.hip; seg_start, seg_len and zb of AdjArgs unused;
+// the forward is launch_forward_quad): the recomputation of every segment's sub-step inputs into the
 // whole-rollout segbuf, and the reverse sweep (a.recomputed 1 or 2).
-hipError_t launch_adj_quad_fwd(const ClassSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
 hipError_t launch_adj_quad_recompute(const ClassSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
 hipError_t launch_adj_quad_bwd(const ClassSegs& q, const AdjArgs& a, bool lag, hipStream_t s);
 

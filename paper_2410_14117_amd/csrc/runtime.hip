@@ -1092,7 +1092,12 @@ mg_status mg_adj_forward(mg_sim* s, const float* actions, int32_t T, int32_t ckp
   a.ckpt = ckpt;
   a.traj = traj;
   if (s->quad_on) {
-    MG_HIP(s, launch_adj_quad_fwd(s->quad, a, s->any_lag, s->stream));
+    StepArgs f = step_args(s);
+    f.actions = actions;
+    f.traj = traj;
+    f.n_ctrl = T;
+    f.substeps = s->substeps;
+    MG_HIP(s, launch_forward_quad(s->quad, f, s->any_lag, ckpt, ckpt_every, s->stream));
     return MG_OK;
   }
   for (int k = 0; k < s->n_classes; ++k) {
