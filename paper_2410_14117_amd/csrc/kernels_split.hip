@@ -14,8 +14,9 @@
 // with the command held over a control step, so its wrench B (f - f_cmd) is
 // formed once per control step and carried, and the lag states are set to
 // their end-of-control-step value f_cmd + kappa^S (f - f_cmd) at its start:
-// nothing in a sub-step depends on the thrusters, so one kernel serves every
-// class and one launch all of them.
+// nothing in a sub-step depends on the thrusters, so one launch serves all
+// classes (N is the most thrusters of any; the others' throttles past their own
+// are zeros, as are their columns of B).
 //
 // One env per lane, or per quad of lanes (fossen_quad.h) for launches of at
 // most one wave per SIMD, which last as long as one env's chain.
@@ -49,28 +50,24 @@ __device__ __forceinline__ RigidInv rigid_inverse(const float* params, int64_t E
   return I;
 }
 
-// Throttles past the class's are zero and so are their columns of B, so the
-// eight-thruster code gives the class's own results.
-__device__ __forceinline__ void load_throttles(int n, const float* af, int64_t E, uint32_t co,
-                                               float (&act)[kMaxThr]) {
-#pragma unroll
-  for (int i = 0; i < kMaxThr; ++i) act[i] = i < n ? lane_elem(af + i * E, co) : 0.0f;
-}
-
 }  // namespace
 
 // VALU-bound: 131 instructions per sub-step (211 with 8 thrusters before the lag
-// wrench was carried) and 300-400 per control step.  Three waves per SIMD; held
-// to four it spills inside the loop (4-20 times slower).  Lagged Heavies, 10
-// control steps of 16 sub-steps, before and now: 32 768 envs 74 -> 68 us, 131 072
-// 109 -> 99 us, 524 288 400 -> 358 us.
-template <bool LAG>
-__global__ void __launch_bounds__(kBlock)
-k_split(const SplitArgs a, const ClassSegs segs) {
-  constexpr int D = LAG ? 13 + kMaxThr : 13;
+// wrench was carried); 105 VGPRs, four waves per SIMD.  The class constants are
+// scalars, read anew at each control step: through a plain pointer they were
+// vector loads, waited for at each control step, and cost 54 more registers.
+// Lagged Heavies, 10 control steps of 16 sub-steps with trajectory, with a launch
+// per class and the lag states stepped, and now: 32 768 envs 74 -> 57 us, 131 072
+// 109 -> 81, 524 288 400 -> 294.
+template <int N, bool LAG>
+__global__ void __launch_bounds__(kBlock) k_split(const SplitArgs a, const ClassSegs segs) {
+  constexpr int D = Dims<N, LAG>::D;
   int block;
   const int k = block_class(segs, blockIdx.x, block);
-  const ClassConst* __restrict__ cc = segs.cc + k;
+  const ClassConst* ccp = segs.cc + k;
+  const int n = scalar_class_const(ccp).n_thr;
+  const bool lag = LAG && scalar_class_const(ccp).lag;
+  const int Dc = 13 + (lag ? n : 0);     // this class's rows
   const int64_t local = (int64_t)block * kBlock + threadIdx.x;
   if (local >= segs.len[k]) return;
   if (!MG_CHECK(a, segs.start[k] + segs.len[k] <= a.Ep, kDbgSegment)) return;
@@ -79,34 +76,39 @@ k_split(const SplitArgs a, const ClassSegs segs) {
   const int64_t c = a.perm ? (int64_t)lane_elem(a.perm, jo) : j;
   if (!MG_CHECK(a, c >= 0 && c < a.dbg.cols, kDbgColumn)) return;
   const uint32_t co = (uint32_t)c * 4u;
-  const int Dc = 13 + (cc->lag ? cc->n_thr : 0);     // this class's rows
   float x[D], acc[6], ma[6];
 #pragma unroll
-  for (int i = 0; i < D; ++i) x[i] = i < 13 || i < Dc ? lane_elem(a.state + i * a.Ep, jo) : 0.0f;
+  for (int i = 0; i < D; ++i)
+    x[i] = lane_elem(i < 13 || i < Dc ? a.state + i * a.Ep : a.state, jo);
 #pragma unroll
   for (int i = 0; i < 6; ++i) {
     acc[i] = lane_elem(a.acc + i * a.Ep, jo);
     ma[i] = lane_elem(a.params + (4 + i) * a.Ep, jo);
   }
   const EnvConst P = load_env_const_off(a.derived, a.Ep, jo);
-  const RigidInv I = rigid_inverse(a.params, a.Ep, jo, a.nominal[k].zg);
-  const float dt = to_vgpr(a.dt), hdt = to_vgpr(0.5f * a.dt), kappa = to_vgpr(cc->kappa);
   // each control step's throttles are loaded one step ahead: loads and stores
   // complete in order, so a load behind the trajectory's stores would wait for
   // them at every control step
   const int64_t frame = (int64_t)a.n_max * a.E;
-  float nxt[kMaxThr];
-  load_throttles(cc->n_thr, a.actions, a.E, co, nxt);
+  float nxt[N];
+  load_throttles<N>(n, a.actions, a.E, co, nxt);
+  const RigidInv I = rigid_inverse(a.params, a.Ep, jo, a.nominal[k].zg);
+  const float dt = to_vgpr(a.dt), hdt = to_vgpr(0.5f * a.dt);
+  const float kappa = to_vgpr(scalar_class_const(ccp).kappa);
+#pragma unroll
+  for (int i = 13; i < D; ++i) x[i] = i < Dc ? x[i] : 0.0f;
   for (int t = 0; t < a.n_ctrl; ++t) {
-    float fcmd[kMaxThr], gcmd[6], dg[6];
-    thrust_command<kMaxThr>(*cc, nxt, fcmd);
-    command_wrench<kMaxThr>(*cc, fcmd, gcmd);
+    const ClassConst cc = scalar_class_const(pin_sgpr(ccp));
+    float fcmd[N], gcmd[6], dg[6];
+    mask_throttles<N>(n, nxt);
+    thrust_command<N>(cc, nxt, fcmd);
+    command_wrench<N>(cc, fcmd, gcmd);
     if (t + 1 < a.n_ctrl)
-      load_throttles(cc->n_thr, a.actions + (int64_t)(t + 1) * frame, a.E, co, nxt);
+      load_throttles<N>(n, pin_sgpr(a.actions + (int64_t)(t + 1) * frame), pin_sgpr(a.E), co, nxt);
 #pragma unroll
     for (int i = 0; i < 6; ++i) dg[i] = 0.0f;
     if constexpr (LAG) {
-      if (cc->lag) begin_control_step<kMaxThr, true>(*cc, x, fcmd, dg, cc->kappa_s);
+      if (lag) begin_control_step<N, true>(cc, x, fcmd, dg, cc.kappa_s);
     }
     for (int s = 0; s < a.substeps; ++s) {
       float tau[6], kin[7], r[6], mom[6];
@@ -139,11 +141,18 @@ k_split(const SplitArgs a, const ClassSegs segs) {
       for (int i = 3; i < 7; ++i) x[i] *= inv;
     }
     if (a.traj) {
-      float* tf = a.traj + (int64_t)t * a.D * a.E;
+      float* tf = pin_sgpr(a.traj + (int64_t)t * a.D * a.E);
+      const int64_t ld = pin_sgpr(a.E);
 #pragma unroll
-      for (int i = 0; i < D; ++i)
-        if (i < a.D) lane_elem(tf + i * a.E, co) = x[i];
-      for (int i = D; i < a.D; ++i) lane_elem(tf + i * a.E, co) = 0.0f;
+      for (int i = 0; i < 13; ++i) lane_elem(tf + i * ld, co) = x[i];
+      if (D == a.D) {
+#pragma unroll
+        for (int i = 13; i < D; ++i) lane_elem(tf + i * ld, co) = x[i];
+      } else {   // the classes with most thrusters have no lag
+#pragma unroll
+        for (int i = 13; i < D; ++i)
+          if (i < a.D) lane_elem(tf + i * ld, co) = x[i];
+      }
     }
   }
 #pragma unroll
@@ -156,7 +165,7 @@ k_split(const SplitArgs a, const ClassSegs segs) {
 #pragma clang fp contract(off)
 
 // The same with one env per quad of lanes, bitwise: launches of at most one
-// wave per SIMD (16 384 envs: 71 -> 43 us, 1000 envs: 69 -> 36 us as above; at
+// wave per SIMD (16 384 envs: 71 -> 38 us, 1000 envs: 69 -> 32 us as above; at
 // two waves per SIMD it would be level with one env per lane).
 template <bool LAG>
 __global__ void __launch_bounds__(kQuadBlock) k_split_quad(const SplitArgs a,
@@ -269,10 +278,20 @@ hipError_t launch_split(const ClassSegs& segs, const SplitArgs& a, bool lag, boo
     hipLaunchKernelGGL((k_split_quad<true>), grid, dim3(kQuadBlock), 0, s, a, segs);
   else if (quad)
     hipLaunchKernelGGL((k_split_quad<false>), grid, dim3(kQuadBlock), 0, s, a, segs);
-  else if (lag)
-    hipLaunchKernelGGL((k_split<true>), grid, dim3(kBlock), 0, s, a, segs);
-  else
-    hipLaunchKernelGGL((k_split<false>), grid, dim3(kBlock), 0, s, a, segs);
+  if (quad) return hipGetLastError();
+#define MG_CASE(n)                                                                     \
+  case n:                                                                              \
+    if (lag)                                                                           \
+      hipLaunchKernelGGL((k_split<n, true>), grid, dim3(kBlock), 0, s, a, segs);       \
+    else                                                                               \
+      hipLaunchKernelGGL((k_split<n, false>), grid, dim3(kBlock), 0, s, a, segs);      \
+    break;
+  switch (a.n_max) {
+    MG_CASE(1) MG_CASE(2) MG_CASE(3) MG_CASE(4) MG_CASE(5) MG_CASE(6) MG_CASE(7) MG_CASE(8)
+    default:
+      return hipErrorInvalidValue;
+  }
+#undef MG_CASE
   return hipGetLastError();
 }
 
