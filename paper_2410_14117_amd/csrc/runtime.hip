@@ -316,6 +316,28 @@ mg_status enqueue_quad(mg_sim* s, const float* actions, int32_t n_ctrl, const fl
   return MG_OK;
 }
 
+// Whether a call takes all classes in one launch (enqueue_lanes).  A long call on
+// a large sim of several classes takes a launch per class instead, the classes
+// side by side on their streams: each class's own thruster count is then the
+// kernel's, and one class's last round of blocks is filled up by the other's.
+// us a control step on 2^20 envs of two classes, one launch -> a launch per class:
+//   rollouts of 24, 16 sub-steps, with statistics   155 -> 150, lagged 168 -> 163
+//                                 with trajectory   166 -> 151, lagged 176 -> 169
+//   the same with 4 sub-steps, statistics            52 ->  57, lagged  58 ->  62
+//   lag-free steps of 24, 16 / 4 sub-steps          149 -> 141, 42.5 -> 39.5
+//   lagged steps of 24, 16 sub-steps                153 -> 158
+// Rollouts of 6 are level (within 3 %), single control steps faster in one launch
+// (180 against 187).  On 2^18 envs one launch is mostly ahead (rollouts of 24, 4
+// sub-steps 14.6 against 16) but 16 lag-free sub-steps with statistics are not
+// (40.8 against 39.2); classes of 98 % and 2 % prefer it there by 6 %.
+bool one_launch(const mg_sim* s, int32_t n_ctrl, bool each_step) {
+  constexpr int32_t kBlocksPerCu = 8, kSubsteps = 16, kRollCtrl = 16, kStepCtrl = 6;
+  if (!s->lanes_on) return false;
+  if (s->n_classes == 1 || s->nblk_total < kBlocksPerCu * s->n_cu) return true;
+  if (each_step) return s->substeps < kSubsteps || n_ctrl < kRollCtrl;
+  return s->any_lag || n_ctrl < kStepCtrl;
+}
+
 // n_ctrl control steps of every class in one launch, one env per lane, frozen as
 // one launch per control step would (each_step) or as one launch.
 mg_status enqueue_lanes(mg_sim* s, const float* actions, int32_t n_ctrl, const float* targets,
@@ -448,7 +470,7 @@ mg_status step_common(mg_sim* s, const float* actions, int32_t n_ctrl, const flo
     return enqueue_quad(s, actions, n_ctrl, targets, traj, stats, false);
   }
   if (stats && (st = ensure_partials(s, n_ctrl, s->nblk_total))) return st;
-  if (s->lanes_on && !plain)
+  if (!plain && one_launch(s, n_ctrl, false))
     return enqueue_lanes(s, actions, n_ctrl, targets, traj, stats, false);
   return enqueue_steps(s, s->stream, actions, n_ctrl, targets, traj, stats, plain, false);
 }
@@ -1041,7 +1063,8 @@ mg_status mg_rollout(mg_sim* s, const float* actions, int32_t T, const float* ta
     return enqueue_quad(s, actions, T, targets, traj, stats, true);
   }
   if (stats && (st = ensure_partials(s, T, s->nblk_total))) return st;
-  if (s->lanes_on && !plain) return enqueue_lanes(s, actions, T, targets, traj, stats, true);
+  if (!plain && one_launch(s, T, true))
+    return enqueue_lanes(s, actions, T, targets, traj, stats, true);
   GraphKey key{T, plain ? 1 : 0, actions, targets, traj, stats};
   auto it = s->graphs.find(key);
   if (it == s->graphs.end()) {

@@ -24,7 +24,8 @@ LAG_HEAVY = vehicle_variant(BLUEROV2_HEAVY, thr_map=1, thr_tau=0.05)
 LAG_BLUE = vehicle_variant(BLUEROV2, thr_map=1, thr_tau=0.05)
 THREE = dict(BLUEROV2, thr_pos=BLUEROV2["thr_pos"][:3], thr_dir=BLUEROV2["thr_dir"][:3])
 FLEETS = {"heavy": [LAG_HEAVY], "bluerov2": [BLUEROV2], "three": [THREE],
-          "mixed": [LAG_BLUE, LAG_HEAVY], "lag_and_not": [LAG_HEAVY, BLUEROV2]}
+          "mixed": [LAG_BLUE, LAG_HEAVY], "plain_mixed": [BLUEROV2, BLUEROV2_HEAVY],
+          "lag_and_not": [LAG_HEAVY, BLUEROV2]}
 
 
 @pytest.fixture(scope="module")
@@ -199,6 +200,43 @@ def test_rollout_of_all_classes_in_one_launch(mgmod, fleet, E):
         np.testing.assert_array_equal(u, w)
     assert sorted(np.flatnonzero(out[0][3])) == sorted({7, 100, 300, E - 1})
     assert list(out[0][1][:, 3]) == [2, 3, 3, 4]
+
+
+@pytest.mark.parametrize("fleet,S,mode,T,piece", [
+    ("mixed", 16, "rollout", 16, 8), ("plain_mixed", 16, "rollout", 17, 15),
+    ("plain_mixed", 2, "step", 6, 3),
+])
+def test_launch_per_class_equals_one_launch(mgmod, fleet, S, mode, T, piece):
+    """A call long enough for a launch per class on a large sim equals the same control steps
+    in shorter calls, which take all classes in one launch, bitwise; in rollouts with envs
+    that go non-finite part-way.  The call is made twice from the same start (a rollout's
+    second one is a replay)."""
+    classes, E = FLEETS[fleet], 2048 * 256 + 3
+    assert torch.cuda.get_device_properties(0).multi_processor_count <= 256
+    cls, x0, _, mult = _inputs(classes, E, 1, 71)
+    gen = torch.Generator(device="cuda").manual_seed(72)
+    act = torch.rand(T, 8, E, device="cuda", generator=gen) * 2.4 - 1.2
+    if mode == "rollout":
+        act[0, 0, 7] = act[piece, 1, 100] = act[T - 1, 0, E - 1] = float("nan")
+    say("launch per class", fleet, mode)
+    sim = mgmod.Sim(classes, E, 0.005, S, env_class=cls)
+    fn = sim.rollout if mode == "rollout" else sim.step
+    x0, mult = dev(x0), dev(mult)
+
+    def run(n, traj, stats):
+        sim.reset(state=x0, param_mult=mult)
+        traj.fill_(-1.0)
+        for t in range(0, T, n):
+            fn(act[t:t + n], traj=traj[t:t + n], stats=stats[t:t + n])
+        return [v.clone() for v in (traj, stats, sim.get_state(), sim.get_flags())]
+
+    bufs = (torch.empty(T, x0.shape[0], E, device="cuda"),
+            torch.empty(T, 4, dtype=torch.float64, device="cuda"))
+    want = run(piece, *bufs)
+    for _ in range(2):
+        for name, u, w in zip(("traj", "stats", "state", "flags"), run(T, *bufs), want):
+            assert torch.equal(u.view(torch.uint8), w.view(torch.uint8)), name
+    sim.close()
 
 
 @pytest.mark.parametrize("fleet,task,m,sizes", [
