@@ -387,8 +387,8 @@ def bench_serving(torch, mg, duration_s=30.0, fifo_plain=False, seed=5005, warmu
 def bench_task(torch, sim, act, x0, n_b, n_h, n_steps=60):
     """Gym-style circle tracking on the benchmark's envs: 4 look-ahead points in the
     observation (30 rows), episodes of 100 control steps with automatic reset, the error of
-    Eq. (4) and the done flags; n_steps task steps (one launch per class each, issued from
-    Python) against as many single-control-step mg_step calls issued the same way (the
+    Eq. (4) and the done flags; n_steps task steps (one launch for all classes each, issued
+    from Python) against as many single-control-step mg_step calls issued the same way (the
     states drift apart between the passes; both advance the same envs by one control step
     per call)."""
     E, dev = sim.n_envs, x0.device
@@ -437,8 +437,8 @@ def bench_task(torch, sim, act, x0, n_b, n_h, n_steps=60):
             "epilogue_overhead": task_ms / step_ms - 1.0,
             "env_task_steps_per_s": E / (task_ms * 1e-3),
             "env_steps_per_s": E * S / (task_ms * 1e-3),
-            "roofline": {"bound": "alu", "kernel": "k_task<6|8,lag>: the fused control step and "
-                                                   "the task epilogue, both class launches",
+            "roofline": {"bound": "alu", "kernel": "k_task<8,lag>: the fused control step and "
+                                                   "the task epilogue, both classes",
                          "achieved": flops / (task_ms * 1e-3) / 1e12,
                          "peak": PEAK_FP32_VALU / 1e12, "unit": "TFLOP/s",
                          "frac": flops / (task_ms * 1e-3) / PEAK_FP32_VALU,
@@ -555,7 +555,7 @@ def bench_split(torch, mg, classes, cls, act, x0, mult, n_ctrl=50):
     stream = torch.cuda.current_stream()
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     out = {"workload": f"{E} envs (the benchmark's mix), {n_ctrl} control steps of 16 x 5 ms "
-                       "in one launch per class"}
+                       "in one launch"}
     for label, factor in (("presets", 1.0), ("added_mass_x0.4", 0.4)):
         cl = [copy.deepcopy(v) for v in classes]
         for v in cl:
@@ -577,7 +577,7 @@ def bench_split(torch, mg, classes, cls, act, x0, mult, n_ctrl=50):
                                n_h * split_substep_flops(8, True, 16))
         res = {"env_steps_per_s": E * n_ctrl * 16 / (ms * 1e-3),
                "blown_share": float(blown.float().mean()),
-               "roofline": {"bound": "alu", "kernel": "k_split<6|8,lag>, both class launches",
+               "roofline": {"bound": "alu", "kernel": "k_split<8,lag>, both classes",
                             "achieved": flops / (ms * 1e-3) / 1e12,
                             "peak": PEAK_FP32_VALU / 1e12, "unit": "TFLOP/s",
                             "frac": flops / (ms * 1e-3) / PEAK_FP32_VALU,

@@ -241,7 +241,8 @@ mg_status mg_step_plain(mg_sim* sim, const float* actions, int32_t n_ctrl, const
  * throttles (Eq. (3)) given up front, each of `substeps` sub-steps (Sec. II):
  * T control steps in one launch, with the results of T mg_step calls.  With
  * plain != 0 (T * substeps launches per class), or where some classes have a
- * thruster lag and some have none (T launches per class), the launches are
+ * thruster lag and some have none, or on large sims of several classes with
+ * both T and substeps >= 16 (T launches per class), the launches are
  * replayed from a HIP graph that is captured on first use and cached for this
  * exact argument tuple (at most 64 tuples per sim; the 65th empties the cache,
  * after waiting for the sim's stream).  Arguments as mg_step with n_ctrl = T. */
