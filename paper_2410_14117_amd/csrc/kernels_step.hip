@@ -161,9 +161,12 @@ __global__ void __launch_bounds__(kBlock) MG_STEP_ATTR k_step(const StepArgs a, 
 // pins): held in scalar registers across the control steps they spill, which
 // took 20 us of a control step of 2^20 envs.  168 VGPRs, no spills.  Per control
 // step, before (a launch per class and control step, forked and joined or
-// replayed from a graph) and now: 10^5 envs of two classes, 4 sub-steps, one call
-// per control step 43.7 -> 12.2 us, rollouts 17.1 -> 7.9; 2^20 envs, 16 sub-steps
-// 180 -> 174 and 175 -> 155; 2^20 envs of one class, rollouts 158 -> 154.  A
+// replayed from a graph) and with all in one launch, lagged envs, alternating
+// runs: two classes, one call per control step with statistics, 131072 envs of 4
+// sub-steps 48 -> 17.0 us, 2^20 of 16 187 -> 180; rollouts of 20, 4 sub-steps,
+// 131072 envs 14.0 -> 9.4, 2^20 68 -> 63; 16 sub-steps, 131072 envs 26.6 -> 24.7,
+// 2^20 168 -> 176 (such calls keep a launch per class); one class, 2^20 envs, 4
+// sub-steps 74 -> 62, 16 sub-steps 176 -> 175.  A
 // single class's mg_step stays with k_step, which is 2-8 % faster there.
 template <int N, bool LAG>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
