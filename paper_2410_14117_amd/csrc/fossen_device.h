@@ -262,12 +262,22 @@ __device__ __forceinline__ ClassConst scalar_class_const(const ClassConst* p) {
   return __builtin_bit_cast(ClassConst, v);
 }
 
+// A value every lane of the wave agrees on, uniform also to the compiler.
+__host__ __device__ __forceinline__ int wave_uniform(int v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  return __builtin_amdgcn_readfirstlane(v);
+#else
+  return v;
+#endif
+}
+
 // The class of block b in a launch over all of them, and its index within it.
-__device__ __forceinline__ int block_class(const ClassSegs& segs, int b, int& block) {
+// Past the last block: the last class, beyond its envs.
+__host__ __device__ __forceinline__ int block_class(const ClassSegs& segs, int b, int& block) {
   int k = 0, first = 0;
   while (k + 1 < segs.n && b >= segs.blk_end[k]) first = segs.blk_end[k++];
-  block = b - __builtin_amdgcn_readfirstlane(first);
-  return __builtin_amdgcn_readfirstlane(k);   // uniform, also to the compiler
+  block = b - wave_uniform(first);
+  return wave_uniform(k);
 }
 
 // The throttles of a class of n <= N thrusters; rows past n hold some other

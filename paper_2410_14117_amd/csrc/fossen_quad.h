@@ -69,6 +69,32 @@ __device__ __forceinline__ QuadLane quad_lane(int lane) {
   return L;
 }
 
+// The env of a lane's quad: its class and internal column.  A quad with no env
+// (past its class's envs, or in a block past the last) loads column 0, which
+// every sim has, and stores nothing; the first column of its class need not
+// exist, since a declared class may have no envs.
+struct QuadEnv {
+  int cls;
+  bool active;   // all four lanes of a quad alike
+  uint32_t j;
+};
+template <class ARGS>
+__host__ __device__ __forceinline__ QuadEnv quad_env(const ARGS& a, const ClassSegs& segs, int b,
+                                                     int lane) {
+  QuadEnv e;
+  int block;
+  e.cls = block_class(segs, b, block);
+  const int64_t start = segs.start[e.cls], len = segs.len[e.cls];
+  const int64_t local = (int64_t)block * kQuadEnvs + (lane >> 2);
+  e.active = local < len && MG_CHECK(a, start + len <= a.Ep, kDbgSegment);
+  e.j = e.active ? (uint32_t)(start + local) : 0u;
+  if (!MG_CHECK(a, (int64_t)e.j < a.Ep, kDbgInternal)) {   // also of quads with no env
+    e.active = false;
+    e.j = 0u;
+  }
+  return e;
+}
+
 // The state of one env: lane c's components.
 struct QuadState {
   float p, q, v, w;   // position, quaternion, linear and angular velocity

@@ -25,21 +25,19 @@ struct QuadPlace {
   QuadPair jf, of, oa;  // lag states in internal and caller rows, throttles
 };
 
-// b: the block of kQuadEnvs envs
+// b: the block of kQuadEnvs envs (one past the last in the surplus half of a
+// paired sweep's last block)
 __device__ __forceinline__ QuadPlace quad_place(const ClassSegs& segs, const AdjArgs& a, int b) {
   QuadPlace p;
-  int block;
-  const int k = block_class(segs, b, block);
-  p.cls = k;
   const int lane = threadIdx.x & (kQuadBlock - 1);
+  const QuadEnv e = quad_env(a, segs, b, lane);
+  const int k = e.cls;
+  p.cls = k;
   p.c = lane & 3;
   const int ci = p.c > 1 ? p.c - 1 : 0;
-  const int64_t local = (int64_t)block * kQuadEnvs + (lane >> 2);
-  p.active = local < segs.len[k] &&
-             MG_CHECK(a, segs.start[k] + segs.len[k] <= a.Ep, kDbgSegment);
-  p.j4 = (uint32_t)(segs.start[k] + (p.active ? local : 0)) * 4u;
-  const int64_t col =
-      p.active ? (a.perm ? (int64_t)lane_elem(a.perm, p.j4) : (int64_t)(p.j4 / 4u)) : 0;
+  p.active = e.active;
+  p.j4 = e.j * 4u;
+  const int64_t col = p.active ? (a.perm ? (int64_t)lane_elem(a.perm, p.j4) : (int64_t)e.j) : 0;
   p.active = p.active && MG_CHECK(a, col >= 0 && col < a.dbg.cols, kDbgColumn);
   p.c4 = p.active ? (uint32_t)col * 4u : 0u;
   const uint32_t s4 = (uint32_t)a.Ep * 4u, e4 = (uint32_t)a.E * 4u;

@@ -170,17 +170,15 @@ __global__ void __launch_bounds__(kBlock) k_split(const SplitArgs a, const Class
 template <bool LAG>
 __global__ void __launch_bounds__(kQuadBlock) k_split_quad(const SplitArgs a,
                                                            const ClassSegs segs) {
-  int block;
-  const int k = block_class(segs, blockIdx.x, block);
+  // the four lanes of a quad share every condition below
+  const QuadEnv env = quad_env(a, segs, blockIdx.x, threadIdx.x);
+  const int k = env.cls;
   const ClassConst* __restrict__ cc = segs.cc + k;
   const QuadLane L = quad_lane(threadIdx.x);
   const int c = L.c, ci = c > 1 ? c - 1 : 0;
-  // the four lanes of a quad share every condition below
-  const int64_t local = (int64_t)block * kQuadEnvs + (threadIdx.x >> 2);
-  bool active = local < segs.len[k] &&
-                MG_CHECK(a, segs.start[k] + segs.len[k] <= a.Ep, kDbgSegment);
-  const uint32_t j4 = (uint32_t)(segs.start[k] + (active ? local : 0)) * 4u;
-  const int64_t col = active ? (a.perm ? (int64_t)lane_elem(a.perm, j4) : (int64_t)(j4 / 4u)) : 0;
+  bool active = env.active;
+  const uint32_t j4 = env.j * 4u;
+  const int64_t col = active ? (a.perm ? (int64_t)lane_elem(a.perm, j4) : (int64_t)env.j) : 0;
   active = active && MG_CHECK(a, col >= 0 && col < a.dbg.cols, kDbgColumn);
   const uint32_t c4 = active ? (uint32_t)col * 4u : 0u;
   const uint32_t s4 = (uint32_t)a.Ep * 4u, e4 = (uint32_t)a.E * 4u;

@@ -366,18 +366,15 @@ hipError_t launch_step_classes(const ClassSegs& segs, const StepArgs& a, bool la
 // one control step
 template <bool LAG>
 __global__ void __launch_bounds__(kQuadBlock) k_step_quad(const StepArgs a, const ClassSegs segs) {
-  int block;
-  const int k = block_class(segs, blockIdx.x, block);
-  const ClassConst* __restrict__ cc = segs.cc + k;
-  const int64_t seg_start = segs.start[k], seg_len = segs.len[k];
   const int lane = threadIdx.x;
-  const QuadLane L = quad_lane(lane);
-  const int c = L.c, ci = c > 1 ? c - 1 : 0;
   // the four lanes of a quad share every condition below, so a DPP exchange
   // never reads a lane that is switched off
-  const int64_t local = (int64_t)block * kQuadEnvs + (lane >> 2);
-  bool active = local < seg_len && MG_CHECK(a, seg_start + seg_len <= a.Ep, kDbgSegment);
-  const uint32_t j = (uint32_t)(seg_start + (active ? local : 0));
+  const QuadEnv env = quad_env(a, segs, blockIdx.x, lane);
+  const ClassConst* __restrict__ cc = segs.cc + env.cls;
+  const QuadLane L = quad_lane(lane);
+  const int c = L.c, ci = c > 1 ? c - 1 : 0;
+  bool active = env.active;
+  const uint32_t j = env.j;
   const uint32_t j4 = j * 4u;
   int64_t col = active ? (a.perm ? (int64_t)lane_elem(a.perm, j4) : (int64_t)j) : 0;
   active = active && MG_CHECK(a, col >= 0 && col < a.dbg.cols, kDbgColumn);
@@ -467,16 +464,13 @@ __global__ void __launch_bounds__(2 * kQuadBlock) k_roll_quad(const StepArgs a,
   __shared__ int status[2][kQuadBlock];   // 1: frozen before it, 2: non-finite after it
   const int lane = threadIdx.x & (kQuadBlock - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kQuadBlock);
-  int block;
-  const int k = block_class(segs, blockIdx.x, block);
-  const ClassConst* __restrict__ cc = segs.cc + k;
+  // the four lanes of a quad share every condition below
+  const QuadEnv env = quad_env(a, segs, blockIdx.x, lane);
+  const ClassConst* __restrict__ cc = segs.cc + env.cls;
   const QuadLane L = quad_lane(lane);
   const int c = L.c, ci = c > 1 ? c - 1 : 0;
-  // the four lanes of a quad share every condition below
-  const int64_t local = (int64_t)block * kQuadEnvs + (lane >> 2);
-  bool active = local < segs.len[k] &&
-                MG_CHECK(a, segs.start[k] + segs.len[k] <= a.Ep, kDbgSegment);
-  const uint32_t j = (uint32_t)(segs.start[k] + (active ? local : 0)), j4 = j * 4u;
+  bool active = env.active;
+  const uint32_t j = env.j, j4 = j * 4u;
   const int64_t col = active ? (a.perm ? (int64_t)lane_elem(a.perm, j4) : (int64_t)j) : 0;
   active = active && MG_CHECK(a, col >= 0 && col < a.dbg.cols, kDbgColumn);
   const uint32_t c4 = active ? (uint32_t)col * 4u : 0u;

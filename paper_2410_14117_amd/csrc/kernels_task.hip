@@ -233,17 +233,15 @@ k_task(const TaskArgs a, const ClassSegs segs, const TaskConst tc) {
 template <bool LAG>
 __global__ void __launch_bounds__(kQuadBlock) k_task_quad(const TaskArgs a, const ClassSegs segs,
                                                           const TaskConst tc) {
-  int block;
-  const int cls = block_class(segs, blockIdx.x, block);
+  // the four lanes of a quad share every condition below, but for lane 0's
+  // restart of the parameters
+  const QuadEnv env = quad_env(a, segs, blockIdx.x, threadIdx.x);
+  const int cls = env.cls;
   const ClassConst* __restrict__ cc = segs.cc + cls;
   const QuadLane L = quad_lane(threadIdx.x);
   const int c = L.c, ci = c > 1 ? c - 1 : 0;
-  // the four lanes of a quad share every condition below, but for lane 0's
-  // restart of the parameters
-  const int64_t local = (int64_t)block * kQuadEnvs + (threadIdx.x >> 2);
-  bool active = local < segs.len[cls] &&
-                MG_CHECK(a, segs.start[cls] + segs.len[cls] <= a.Ep, kDbgSegment);
-  const uint32_t j = (uint32_t)(segs.start[cls] + (active ? local : 0)), j4 = j * 4u;
+  bool active = env.active;
+  const uint32_t j = env.j, j4 = j * 4u;
   const int64_t col = active ? (a.perm ? (int64_t)lane_elem(a.perm, j4) : (int64_t)j) : 0;
   active = active && MG_CHECK(a, col >= 0 && col < a.dbg.cols, kDbgColumn);
   const uint32_t c4 = active ? (uint32_t)col * 4u : 0u;
