@@ -462,6 +462,8 @@ __global__ void __launch_bounds__(2 * kQuadBlock) k_roll_quad(const StepArgs a,
   __shared__ float4 cmd[2][kQuadBlock];   // command wrench and lag wrench of a control step
   __shared__ float4 out[2][kQuadBlock];   // position, quaternion, velocities after it
   __shared__ int status[2][kQuadBlock];   // 1: frozen before it, 2: non-finite after it
+  __shared__ int lag_ok[2][kQuadBlock];   // the lane's thruster states are finite after it
+  constexpr bool kLagOk = LAG && MODE != kRollAdjoint;
   const int lane = threadIdx.x & (kQuadBlock - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kQuadBlock);
   // the four lanes of a quad share every condition below
@@ -494,6 +496,8 @@ __global__ void __launch_bounds__(2 * kQuadBlock) k_roll_quad(const StepArgs a,
     for (int t = 0; t < n; ++t) {
       lds_barrier();
       const float4 u = cmd[t & 1][lane];
+      int f_ok = 1;
+      if constexpr (kLagOk) f_ok = lag_ok[t & 1][lane];
       const QuadState x0 = x;
       const int was = frozen ? 1 : 0;
       if (!frozen) {
@@ -504,10 +508,10 @@ __global__ void __launch_bounds__(2 * kQuadBlock) k_roll_quad(const StepArgs a,
       }
       out[t & 1][lane] = make_float4(x.p, x.q, x.v, x.w);
       if constexpr (MODE != kRollAdjoint) {
-        // a thruster state that is not finite has made the velocities so
         int ok = 1;
         if (MODE == kRollEach || t == n - 1) {
-          ok = isfinite(x.q) && (c == 0 || (isfinite(x.p) && isfinite(x.v) && isfinite(x.w)));
+          ok = f_ok && isfinite(x.q) &&
+               (c == 0 || (isfinite(x.p) && isfinite(x.v) && isfinite(x.w)));
           ok &= qperm<MG_QP(1, 0, 3, 2)>(ok);
           ok &= qperm<MG_QP(2, 3, 0, 1)>(ok);
         }
@@ -560,6 +564,11 @@ __global__ void __launch_bounds__(2 * kQuadBlock) k_roll_quad(const StepArgs a,
     float gl, ga, dl, da;
     quad_command<LAG>(th, act, th.rho_s, x, gl, ga, dl, da);
     cmd[t & 1][lane] = make_float4(gl, ga, dl, da);
+    // (an env frozen part-way has its flag already; one frozen from the start
+    // keeps its thruster states)
+    if constexpr (kLagOk)
+      lag_ok[t & 1][lane] = frozen ? isfinite(ff[0]) && isfinite(ff[1])
+                                   : isfinite(x.f[0]) && isfinite(x.f[1]);
   };
   auto store = [&](float* rows, const float4& u, const float (&f)[2]) {
     if (!active) return;

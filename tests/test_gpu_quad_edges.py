@@ -1,5 +1,6 @@
 """GPU checks of the kernels with one env per quad of lanes where a fleet, a vehicle or a call
-is out of the ordinary: a declared class without envs behind an odd number of groups of 16."""
+is out of the ordinary: a declared class without envs behind an odd number of groups of 16, and
+thruster states that are not finite where the velocities are."""
 import numpy as np
 import pytest
 
@@ -52,3 +53,41 @@ def test_adjoint_of_odd_groups_with_an_empty_class(mgmod, E, where):
             assert (u[..., 13:, :] == 0).all(), i
             u = u[..., :13, :]
         np.testing.assert_array_equal(u, w, err_msg=str(i))
+
+
+@pytest.mark.parametrize("T", [8, 10])
+@pytest.mark.parametrize("mode", ["step", "rollout", "steps"])
+def test_thruster_states_that_overflow_freeze_their_env(mgmod, mode, T):
+    """A thruster without effect (its direction is zero) whose lag is unstable at this time step
+    overflows in the eighth control step while the velocities stay finite; an env that is not
+    steppable holds a NaN thruster state.  State, flags, counts and trajectory with one env per
+    quad of lanes are those with one env per lane, bitwise."""
+    heavy = vehicle_variant(BLUEROV2_HEAVY, thr_tau=0.0005)
+    heavy["thr_dir"] = list(heavy["thr_dir"][:7]) + [(0.0, 0.0, 0.0)]
+    big, E = 20000, 40
+    x0, mult = random_states(big, 21, 91), param_multipliers(big, 0.2, 92)
+    x0[13:] = 0
+    act = np.zeros((T, 8, big), np.float32)
+    act[:, 7, 3] = act[:, 7, 18] = 0.5
+    mult[4:7, 5], x0[14, 5] = -9.0, np.nan
+    res = []
+    for n in (E, big):
+        say("overflowing thruster states", mode, T, n)
+        sim = mgmod.Sim(heavy, n, 0.005, 2)
+        sim.reset(state=dev(x0[:, :n]), param_mult=dev(mult[:, :n]))
+        a, traj = dev(act[:, :, :n]), torch.full((T, 21, n), -1.0, device="cuda")
+        stats = torch.empty((T, 4), dtype=torch.float64, device="cuda")
+        if mode == "steps":
+            for t in range(T):
+                sim.step(a[t:t + 1], traj=traj[t:t + 1], stats=stats[t:t + 1])
+        else:
+            getattr(sim, mode)(a, traj=traj, stats=stats)
+        res.append([host(v) for v in (traj, sim.get_state(), sim.get_flags())] +
+                   [host(stats)[:, 3]])
+        sim.close()
+    small, ref = res
+    for name, u, w in zip(("traj", "state", "flags"), small, ref):
+        np.testing.assert_array_equal(u, w[..., :E], err_msg=name)
+    np.testing.assert_array_equal(small[3], ref[3])
+    assert list(np.flatnonzero(ref[2])) == [3, 5, 18] and list(ref[2][[3, 5, 18]]) == [1, 3, 1]
+    assert list(ref[3][:8]) == [1] * 7 + [3]
