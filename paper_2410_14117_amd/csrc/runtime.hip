@@ -294,7 +294,8 @@ StepArgs step_args(mg_sim* s) {
 // n_ctrl control steps of every class with one env per quad of lanes, frozen
 // as one launch per control step would (each_step) or as one launch.  With
 // statistics the per-wave partials of at most kQuadStatSteps control steps are
-// held at a time (each_step only: with one launch for all of them, all).
+// held at a time (each_step only: with one launch for all of them, all; see
+// quad_step).
 constexpr int32_t kQuadStatSteps = 128;
 mg_status enqueue_quad(mg_sim* s, const float* actions, int32_t n_ctrl, const float* targets,
                        float* traj, double* stats, bool each_step) {
@@ -314,6 +315,17 @@ mg_status enqueue_quad(mg_sim* s, const float* actions, int32_t n_ctrl, const fl
                                       s->stream));
   }
   return MG_OK;
+}
+
+// Whether an mg_step of n_ctrl control steps takes one env per quad of lanes.  Its
+// statistics need a partial for every 16 envs and control step (one env per lane:
+// for every 256), all of them at once, since an env is frozen at the state it had
+// before the whole call; calls whose partials would take more than kQuadStatBytes
+// (16 384 envs: 2048 control steps) take one env per lane.
+constexpr size_t kQuadStatBytes = (size_t)64 << 20;
+bool quad_step(const mg_sim* s, int32_t n_ctrl, bool stats) {
+  const size_t bytes = (size_t)n_ctrl * s->quad.blk_end[s->n_classes - 1] * 4 * sizeof(double);
+  return s->quad_on && (!stats || bytes <= kQuadStatBytes);
 }
 
 // Whether a call takes all classes in one launch (enqueue_lanes).  A long call on
@@ -465,7 +477,7 @@ mg_status step_common(mg_sim* s, const float* actions, int32_t n_ctrl, const flo
   if (!actions) return fail(s, MG_ERR_INVALID, "actions is NULL");
   if (n_ctrl < 1) return fail(s, MG_ERR_INVALID, "n_ctrl must be >= 1");
   DeviceGuard g(s->device);
-  if (s->quad_on && !plain) {
+  if (!plain && quad_step(s, n_ctrl, stats != nullptr)) {
     if (stats && (st = ensure_partials(s, n_ctrl, s->quad.blk_end[s->n_classes - 1]))) return st;
     return enqueue_quad(s, actions, n_ctrl, targets, traj, stats, false);
   }

@@ -1,6 +1,7 @@
 """GPU checks of the kernels with one env per quad of lanes where a fleet, a vehicle or a call
-is out of the ordinary: a declared class without envs behind an odd number of groups of 16, and
-thruster states that are not finite where the velocities are."""
+is out of the ordinary: a declared class without envs behind an odd number of groups of 16,
+thruster states that are not finite where the velocities are, and the statistics of very long
+calls."""
 import numpy as np
 import pytest
 
@@ -91,3 +92,36 @@ def test_thruster_states_that_overflow_freeze_their_env(mgmod, mode, T):
     np.testing.assert_array_equal(small[3], ref[3])
     assert list(np.flatnonzero(ref[2])) == [3, 5, 18] and list(ref[2][[3, 5, 18]]) == [1, 3, 1]
     assert list(ref[3][:8]) == [1] * 7 + [3]
+
+
+def test_statistics_of_a_long_call_take_bounded_memory(mgmod):
+    """4096 control steps of 16 384 envs with statistics in one call: the device memory the sim
+    takes for them stays below 64 MiB (as FP64 partials of every 16 envs they would be 128 MiB),
+    and the call's results are those of two calls of half the length."""
+    E, T = 16384, 4096
+    one = dict(BLUEROV2, thr_pos=BLUEROV2["thr_pos"][:1], thr_dir=BLUEROV2["thr_dir"][:1])
+    x0 = dev(random_states(E, 13, 101))
+    act = torch.zeros((T, 1, E), device="cuda")
+    act[::3] = 0.25
+    say("statistics of a long call")
+    res = []
+    for n in (T, T // 2):
+        sim = mgmod.Sim(one, E, 0.01, 1)
+        sim.reset(state=x0)
+        sim.step(act[:1])               # the code is loaded
+        sim.reset(state=x0)
+        stats = torch.zeros((T, 4), dtype=torch.float64, device="cuda")
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        for t in range(0, T, n):
+            sim.step(act[t:t + n], stats=stats[t:t + n])
+        torch.cuda.synchronize()
+        took = free - torch.cuda.mem_get_info()[0]
+        print("control steps a call", n, "MiB taken", took / 2**20)
+        assert took <= 64 << 20
+        res.append((host(sim.get_state()), host(stats)))
+        assert not host(sim.get_flags()).any()
+        sim.close()
+    np.testing.assert_array_equal(res[0][0], res[1][0])
+    # FP64 sums of the same values in another order
+    np.testing.assert_allclose(res[0][1], res[1][1], rtol=1e-12)
