@@ -390,11 +390,12 @@ __device__ __forceinline__ void quad_momentum(const QuadMass& M, float v, float 
 }
 
 // begin_control_step: the command wrench (gl, ga), the lag wrench (dl, da) and
-// the lag states at their end-of-control-step value, f_cmd + decay (f - f_cmd).
-template <bool LAG>
+// the lag states at their end-of-control-step value, f_cmd + decay (f - f_cmd);
+// SCALED: f_cmd + decay 2^e (f - f_cmd).
+template <bool LAG, bool SCALED = false>
 __device__ __forceinline__ void quad_command(const QuadThr& t, const float (&act)[2], float decay,
                                              QuadState& x, float& gl, float& ga, float& dl,
-                                             float& da) {
+                                             float& da, int e = 0) {
   float fcmd[2];
   quad_thrust(t, act, fcmd);
   quad_wrench(t, fcmd, gl, ga);
@@ -403,8 +404,8 @@ __device__ __forceinline__ void quad_command(const QuadThr& t, const float (&act
     if (t.lag) {
       const float df[2] = {x.f[0] - fcmd[0], x.f[1] - fcmd[1]};
       quad_wrench(t, df, dl, da);
-      x.f[0] = fmaf(decay, df[0], fcmd[0]);
-      x.f[1] = fmaf(decay, df[1], fcmd[1]);
+      x.f[0] = fmaf(decay, SCALED ? ldexpf(df[0], e) : df[0], fcmd[0]);
+      x.f[1] = fmaf(decay, SCALED ? ldexpf(df[1], e) : df[1], fcmd[1]);
     }
   }
 }

@@ -13,7 +13,8 @@
 // The lag step maps f - f_cmd to kappa (f - f_cmd), kappa = 1 - dt / tau_thr,
 // with the command held over a control step, so its wrench B (f - f_cmd) is
 // formed once per control step and carried, and the lag states are set to
-// their end-of-control-step value f_cmd + kappa^S (f - f_cmd) at its start:
+// their end-of-control-step value f_cmd + kappa^S (f - f_cmd) at its start (kappa^S
+// scaled where it is beyond FP32, so that a thruster at rest stays there):
 // nothing in a sub-step depends on the thrusters, so one launch serves all
 // classes (N is the most thrusters of any; the others' throttles past their own
 // are zeros, as are their columns of B).
@@ -108,7 +109,12 @@ __global__ void __launch_bounds__(kBlock) k_split(const SplitArgs a, const Class
 #pragma unroll
     for (int i = 0; i < 6; ++i) dg[i] = 0.0f;
     if constexpr (LAG) {
-      if (lag) begin_control_step<N, true>(cc, x, fcmd, dg, cc.kappa_s);
+      if (lag) {
+        lag_wrench<N>(cc, x, fcmd, dg);
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+          x[13 + i] = fma_t(cc.kappa_s, ldexpf(x[13 + i] - fcmd[i], cc.kappa_e), fcmd[i]);
+      }
     }
     for (int s = 0; s < a.substeps; ++s) {
       float tau[6], kin[7], r[6], mom[6];
@@ -216,7 +222,7 @@ __global__ void __launch_bounds__(kQuadBlock) k_split_quad(const SplitArgs a,
     quad_mask_pair(thr_in, act);
     if (t + 1 < a.n_ctrl) quad_load_pair(thr_in, a.actions + (int64_t)(t + 1) * frame, nxt);
     float gl, ga, dl, da;
-    quad_command<LAG>(th, act, cc->kappa_s, x, gl, ga, dl, da);
+    quad_command<LAG, true>(th, act, cc->kappa_s, x, gl, ga, dl, da, cc->kappa_e);
     for (int s = 0; s < a.substeps; ++s) {
       const float tl = LAG ? gl + dl : gl, ta = LAG ? ga + da : ga;
       if constexpr (LAG) {

@@ -48,8 +48,10 @@ struct ClassConst {
   int32_t lag;
   float rho_s;           // rho^S for the owner's S sub-steps per control step
   // the same for the split scheme's semi-implicit Euler step of the lag: one
-  // sub-step maps f - f_cmd to kappa (f - f_cmd), kappa = 1 - z
+  // sub-step maps f - f_cmd to kappa (f - f_cmd), kappa = 1 - z, and S of them to
+  // kappa_s 2^kappa_e (f - f_cmd); kappa_e is 0 unless kappa^S is beyond FP32
   float kappa, kappa_s;
+  int32_t kappa_e;
 };
 
 // Class constants for sub-steps of dt, S sub-steps per control step.  The

@@ -149,7 +149,18 @@ ClassConst mg::make_class_const(const mg_vehicle& v, double dt, int substeps) {
   c.rho = (float)rho;
   c.rho_s = (float)std::pow(rho, (double)substeps);
   c.kappa = (float)(1.0 - z);
-  c.kappa_s = (float)std::pow(1.0 - z, (double)substeps);
+  const double kappa_s = std::pow(1.0 - z, (double)substeps);
+  c.kappa_s = (float)kappa_s;
+  if (!std::isfinite(c.kappa_s)) {
+    // an unstable lag, over many sub-steps: thrusters at their commands stay there,
+    // and others are finite as long as kappa^S (f - f_cmd) is.  Beyond 2^1024 any
+    // f - f_cmd but zero overflows.
+    int e = 1024;
+    const double m = std::isfinite(kappa_s) ? std::frexp(kappa_s, &e)
+                                            : std::copysign(0.5, kappa_s);
+    c.kappa_s = (float)(2.0 * m);
+    c.kappa_e = e - 1;
+  }
   c.n_thr = v.n_thr;
   c.thr_map = v.thr_map;
   c.lag = v.thr_tau > 0.0 ? 1 : 0;

@@ -1,13 +1,13 @@
 """GPU checks of the kernels with one env per quad of lanes where a fleet, a vehicle or a call
 is out of the ordinary: a declared class without envs behind an odd number of groups of 16,
-thruster states that are not finite where the velocities are, and the statistics of very long
-calls."""
+thruster states that are not finite where the velocities are, the statistics of very long
+calls, and thruster lags that the split scheme's time step makes unstable."""
 import numpy as np
 import pytest
 
 torch = pytest.importorskip("torch")
 
-from tests.gpu_util import dev, host, say                                      # noqa: E402
+from tests.gpu_util import dev, host, rel_err, say                             # noqa: E402
 from workloads import (BLUEROV2, BLUEROV2_HEAVY, actions, param_multipliers,   # noqa: E402
                        random_states, vehicle_variant)
 
@@ -125,3 +125,34 @@ def test_statistics_of_a_long_call_take_bounded_memory(mgmod):
     np.testing.assert_array_equal(res[0][0], res[1][0])
     # FP64 sums of the same values in another order
     np.testing.assert_allclose(res[0][1], res[1][1], rtol=1e-12)
+
+
+@pytest.mark.parametrize("E", [40, 20000])
+def test_split_lag_factor_beyond_fp32(mgmod, oracle, E):
+    """Split steps of 41 sub-steps whose lag maps f - f_cmd to -9 (f - f_cmd): over a control
+    step that is 1.3e39, more than FP32 holds.  Thrusters at rest under zero throttles stay at
+    rest, and 1e-30 N of a thruster without effect becomes -1.3e9 N, as when the lag is stepped.
+    Against the oracle within the 1e-4 that 80 sub-steps of the scheme are held to."""
+    vs = [vehicle_variant(v, thr_tau=0.0005, added_mass=[0.4 * m for m in v["added_mass"]])
+          for v in (BLUEROV2, BLUEROV2_HEAVY)]
+    vs[1]["thr_dir"] = list(vs[1]["thr_dir"][:7]) + [(0.0, 0.0, 0.0)]
+    cls = (np.arange(E) % 3 == 0).astype(np.int32)
+    x0, mult = random_states(E, 21, 111), param_multipliers(E, 0.2, 112)
+    x0[13:] = 0
+    x0[20, 3] = 1e-30
+    act = np.zeros((2, 8, E), np.float32)
+    say("split, lag factor beyond FP32", E)
+    sim = mgmod.Sim(vs, E, 0.005, 41, env_class=cls)
+    sim.reset(state=dev(x0), param_mult=dev(mult))
+    traj = torch.full((2, 21, E), -1.0, device="cuda")
+    sim.step_split(dev(act), traj=traj)
+    got, xT = host(traj), host(sim.get_state())
+    sim.close()
+    n = min(E, 64)
+    ref = oracle.split_rollout(vs, x0[:, :n], act[:, :, :n], 41, 0.005, env_class=cls[:n],
+                               mult=mult[:, :n], want_traj=True)["traj"]
+    assert rel_err(got[0, :, :n], ref[0]) <= 1e-4
+    assert ref[0, 20, 3] < -1e9
+    rest = np.arange(n) != 3
+    assert rel_err(got[1][:, :n][:, rest], ref[1][:, rest]) <= 1e-4
+    np.testing.assert_array_equal(xT, got[1])
