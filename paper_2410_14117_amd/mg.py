@@ -303,7 +303,10 @@ class Sim:
 
     def _bind_stream(self):
         # the current device's current stream, as torch.cuda.current_stream() gives it,
-        # without the Stream object: 0.2 instead of 2.9 us of a call's 4-9
+        # without the Stream object: 0.3 instead of 2.8 us of a call's 4-9; torch's own check
+        # refuses a forked child of a process that has initialised the GPU
+        if not _torch.cuda.is_initialized():
+            _torch.cuda.init()
         c = _torch._C
         self._check(_lib.mg_set_stream(self._h, c._cuda_getCurrentRawStream(c._cuda_getDevice())))
 
