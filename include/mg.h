@@ -203,11 +203,15 @@ mg_status mg_get_flags(mg_sim* sim, int32_t* out, int32_t out_on_device);
 int32_t mg_debug_build(void);
 mg_status mg_debug_word(mg_sim* sim, uint32_t* word, int32_t clear);
 
-/* Advances every env by n_ctrl control steps in ONE fused launch (one per class
- * where some classes have a thruster lag and some have none):
- * each control step reads one throttle frame, holds it for `substeps` RK4
- * sub-steps, and the state stays in registers across all n_ctrl * substeps
- * sub-steps (Sec. II: several sub-simulation steps per simulation step).
+/* Advances every env by n_ctrl control steps in ONE fused launch for all classes,
+ * or in one launch per class, the classes side by side on helper streams: where
+ * some classes have a thruster lag and some have none, and where that is faster
+ * (sims of several classes and more than two blocks of 256 envs per compute unit,
+ * in calls of about 2^22 env control steps or more; from 2^19 on with many sub-steps
+ * and no lag).  The results are the same.  Each control step reads one throttle
+ * frame, holds it for `substeps` RK4 sub-steps, and the state stays in registers
+ * across all n_ctrl * substeps sub-steps (Sec. II: several sub-simulation steps per
+ * simulation step).
  *   actions  device [n_ctrl][N_max][E] throttles (rows >= a class's n_thr are ignored)
  *   targets  device [3][E] station-keeping targets for the statistics, or NULL (origin)
  *   traj     device [n_ctrl][D][E] state after each control step, or NULL
@@ -239,13 +243,14 @@ mg_status mg_step_plain(mg_sim* sim, const float* actions, int32_t n_ctrl, const
                         float* traj, double* stats);
 /* A sequence of T Gym-style steps (Sec. III) of every env with its
  * throttles (Eq. (3)) given up front, each of `substeps` sub-steps (Sec. II):
- * T control steps in one launch, with the results of T mg_step calls.  With
- * plain != 0 (T * substeps launches per class), or where some classes have a
- * thruster lag and some have none, or on large sims of several classes with
- * both T and substeps >= 16 (T launches per class), the launches are
- * replayed from a HIP graph that is captured on first use and cached for this
- * exact argument tuple (at most 64 tuples per sim; the 65th empties the cache,
- * after waiting for the sim's stream).  Arguments as mg_step with n_ctrl = T. */
+ * T control steps in one launch, with the results of T mg_step calls, or, where
+ * that is faster (sims of several classes and more than two blocks of 256 envs per
+ * compute unit, more than 8 sub-steps, long calls), in T launches per class.
+ * With plain != 0 (T * substeps launches per class), or where some classes have a
+ * thruster lag and some have none (T launches per class), the launches are replayed
+ * from a HIP graph that is captured on first use and cached for this exact argument
+ * tuple (at most 64 tuples per sim; the 65th empties the cache, after waiting for
+ * the sim's stream).  Arguments as mg_step with n_ctrl = T. */
 mg_status mg_rollout(mg_sim* sim, const float* actions, int32_t T, const float* targets,
                      float* traj, double* stats, int32_t plain);
 /* Reads back eta and nu of Eq. (1) (Sec. II) with the thruster states: copies

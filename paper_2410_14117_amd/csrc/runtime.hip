@@ -99,6 +99,8 @@ struct mg_sim {
   // all classes in one launch, one env per lane (steps and rollouts: if all
   // classes have a lag or none has)
   bool lanes_on = true;
+  bool lopsided = false;       // one class has more than three quarters of the envs
+  int32_t nblk_largest = 0;    // blocks of the largest class, one env per lane
   ClassSegs lanes{};
 
   float* state = nullptr;      // [D][Ep]
@@ -339,26 +341,50 @@ bool quad_step(const mg_sim* s, int32_t n_ctrl, bool stats) {
   return s->quad_on && (!stats || bytes <= kQuadStatBytes);
 }
 
-// Whether a call takes all classes in one launch (enqueue_lanes).  A long call on
-// a large sim of several classes takes a launch per class instead, the classes
-// side by side on their streams: each class's own thruster count is then the
-// kernel's, and one class's last round of blocks is filled up by the other's.
-// us a control step on 2^20 envs of two classes, one launch -> a launch per class:
-//   rollouts of 24, 16 sub-steps, with statistics   155 -> 150, lagged 168 -> 163
-//                                 with trajectory   166 -> 151, lagged 176 -> 169
-//   the same with 4 sub-steps, statistics            52 ->  57, lagged  58 ->  62
-//   lag-free steps of 24, 16 / 4 sub-steps          149 -> 141, 42.5 -> 39.5
-//   lagged steps of 24, 16 sub-steps                153 -> 158
-// Rollouts of 6 are level (within 3 %), single control steps faster in one launch
-// (180 against 187).  On 2^18 envs one launch is mostly ahead (rollouts of 24, 4
-// sub-steps 14.6 against 16) but 16 lag-free sub-steps with statistics are not
-// (40.8 against 39.2); classes of 98 % and 2 % prefer it there by 6 %.
-bool one_launch(const mg_sim* s, int32_t n_ctrl, bool each_step) {
-  constexpr int32_t kBlocksPerCu = 8, kSubsteps = 16, kRollCtrl = 16, kStepCtrl = 6;
+// Whether a call takes all classes in one launch (enqueue_lanes) or a launch per
+// class, the classes side by side on their streams.  A launch per class pays a fork
+// and a join a call; one launch pays for every class's throttles at the largest
+// thruster count at each control step, and, in a rollout, for its blocks' even
+// spread over the CUs: it lasts as long as the fullest CU's, where the classes'
+// chains of launches share the chip anew at each step.  Ratios are one launch / a
+// launch per class (rollouts: replayed from a graph; as issued here, 7 us a call
+// more), two halves unless stated, over 163 840 to 2^20 envs:
+//  - at most two blocks to a CU: one launch (131 072 envs and fewer 0.15-1.01);
+//  - rollouts of 8 or fewer sub-steps: one launch, which keeps the state and the
+//    constants in registers (mean 0.52 at 1 sub-step, 0.58 at 2, 0.79 at 4, 0.91 at
+//    8, where single sizes reach 1.13);
+//  - rollouts of 16 sub-steps: from 6 control steps on 1.03-1.22 at 2.5 and 3.5
+//    blocks to a CU, 0.95-1.09 at 3 to 8, 0.96-1.06 there beyond 16 control steps;
+//    shorter ones without a lag 0.96-1.17, with one 0.93-1.09; with a lag and 8
+//    blocks to a CU or more 0.94-1.02 up to 16 control steps.  Where one class has
+//    nearly all envs, its chain alone sets the time of a launch per class, whose
+//    blocks are as unevenly spread: 0.78-1.00 unless the other classes' blocks fill
+//    another round of the CUs (131 072 envs, 2 % in the other class, 2 blocks to a
+//    CU and one more: 1.02-1.12);
+//  - steps: the cost of one launch grows with the envs' control steps and that of
+//    the fork does not.  They cross at about 2^22 env control steps, at 2^21 without
+//    a lag from 4 sub-steps on and 2^20 from 16 on, at half of these where one class
+//    has nearly all envs, and where a last round of the CUs is nearly empty (131 072
+//    interleaved envs, 514 blocks: 1.05 at 0.8 x 2^20); far beyond, one launch takes
+//    1.03-1.20.  With a lag and 8 or more sub-steps one launch stays ahead
+//    (0.93-1.01), and so it does when it writes the trajectory with fewer than 4
+//    (0.80-0.99), whose stores its loads never wait for.
+bool one_launch(const mg_sim* s, int32_t n_ctrl, bool each_step, bool traj) {
   if (!s->lanes_on) return false;
-  if (s->n_classes == 1 || s->nblk_total < kBlocksPerCu * s->n_cu) return true;
-  if (each_step) return s->substeps < kSubsteps || n_ctrl < kRollCtrl;
-  return s->any_lag || n_ctrl < kStepCtrl;
+  if (s->n_classes == 1 || s->nblk_total <= 2 * s->n_cu) return true;
+  const int32_t S = s->substeps;
+  auto rounds = [&](int32_t blocks) { return (blocks + s->n_cu - 1) / s->n_cu; };
+  if (each_step) {
+    if (S <= 8 || n_ctrl < (s->any_lag ? 6 : 3)) return true;
+    const bool large = s->nblk_total >= 8 * s->n_cu;
+    if (large && n_ctrl > 16) return false;
+    if (s->lopsided) return rounds(s->nblk_total) * 4 <= rounds(s->nblk_largest) * 5;
+    return s->any_lag && large;
+  }
+  if ((s->any_lag && S >= 8) || (traj && S < 4)) return true;
+  const bool uneven = rounds(s->nblk_total) * s->n_cu > s->nblk_total * 5 / 4;
+  const int log2 = 22 - s->lopsided - uneven - (s->any_lag ? 0 : (S >= 4) + (S >= 16));
+  return s->E * n_ctrl <= (int64_t)1 << log2;
 }
 
 // n_ctrl control steps of every class in one launch, one env per lane, frozen as
@@ -400,30 +426,23 @@ mg_status enqueue_steps(mg_sim* s, hipStream_t st, const float* actions, int32_t
     MG_HIP(s, hipEventRecord(s->ev_fork[k - 1], st));
     MG_HIP(s, hipStreamWaitEvent(s->aux[k - 1], s->ev_fork[k - 1], 0));
   }
-  for (int k = 0; k < s->n_classes; ++k) {
-    hipStream_t ks = k == 0 ? st : s->aux[k - 1];
-    a.seg_start = s->seg_start[k];
-    a.seg_len = s->seg_len[k];
-    a.blk_off = s->seg_blk_off[k];
-    if (!plain && !one_launch_per_ctrl) {
-      a.actions = actions;
-      a.traj = traj;
-      a.partials = stats ? s->partials : nullptr;
-      a.n_ctrl = n_ctrl;
-      a.substeps = s->substeps;
-      MG_HIP(s, launch_step(s->cc[k], a, ks));
-      continue;
-    }
-    const int32_t n_sub = plain ? s->substeps : 1;
-    for (int32_t t = 0; t < n_ctrl; ++t) {
-      for (int32_t sub = 0; sub < n_sub; ++sub) {
-        const bool last = sub == n_sub - 1;
-        a.actions = actions + t * frame;
-        a.traj = (traj && last) ? traj + t * tframe : nullptr;
-        a.partials = (stats && last) ? s->partials + t * pframe : nullptr;
-        a.n_ctrl = 1;
-        a.substeps = plain ? 1 : s->substeps;
-        MG_HIP(s, launch_step(s->cc[k], a, ks));
+  // control step by control step, so that the classes advance together also while
+  // the launches are being issued
+  const bool together = !plain && !one_launch_per_ctrl;
+  const int32_t n_sub = plain ? s->substeps : 1;
+  a.n_ctrl = together ? n_ctrl : 1;
+  a.substeps = plain ? 1 : s->substeps;
+  for (int32_t t = 0; t < n_ctrl; t += a.n_ctrl) {
+    a.actions = actions + t * frame;
+    for (int32_t sub = 0; sub < n_sub; ++sub) {
+      const bool last = sub == n_sub - 1;
+      a.traj = (traj && last) ? traj + t * tframe : nullptr;
+      a.partials = (stats && last) ? s->partials + t * pframe : nullptr;
+      for (int k = 0; k < s->n_classes; ++k) {
+        a.seg_start = s->seg_start[k];
+        a.seg_len = s->seg_len[k];
+        a.blk_off = s->seg_blk_off[k];
+        MG_HIP(s, launch_step(s->cc[k], a, k == 0 ? st : s->aux[k - 1]));
       }
     }
   }
@@ -493,7 +512,7 @@ mg_status step_common(mg_sim* s, const float* actions, int32_t n_ctrl, const flo
     return enqueue_quad(s, actions, n_ctrl, targets, traj, stats, false);
   }
   if (stats && (st = ensure_partials(s, n_ctrl, s->nblk_total))) return st;
-  if (!plain && one_launch(s, n_ctrl, false))
+  if (!plain && one_launch(s, n_ctrl, false, traj != nullptr))
     return enqueue_lanes(s, actions, n_ctrl, targets, traj, stats, false);
   return enqueue_steps(s, s->stream, actions, n_ctrl, targets, traj, stats, plain, false);
 }
@@ -731,6 +750,9 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
   }
   for (int k = 0; k < cfg->n_classes; ++k)
     s->lanes_on = s->lanes_on && (s->cc[k].lag != 0) == s->any_lag;
+  const int64_t largest = *std::max_element(count.begin(), count.end());
+  s->lopsided = largest > E / 4 * 3;
+  s->nblk_largest = (int32_t)((largest + kBlock - 1) / kBlock);
   s->lanes = s->quad;
   for (int k = 0; k < cfg->n_classes; ++k)
     s->lanes.blk_end[k] = k + 1 < cfg->n_classes ? s->seg_blk_off[k + 1] : blk;
@@ -1086,8 +1108,13 @@ mg_status mg_rollout(mg_sim* s, const float* actions, int32_t T, const float* ta
     return enqueue_quad(s, actions, T, targets, traj, stats, true);
   }
   if (stats && (st = ensure_partials(s, T, s->nblk_total))) return st;
-  if (!plain && one_launch(s, T, true))
+  if (!plain && one_launch(s, T, true, traj != nullptr))
     return enqueue_lanes(s, actions, T, targets, traj, stats, true);
+  // classes alike that are faster side by side: launches of 30 us and more are issued
+  // sooner than they end, and new buffers need no capture (2^18 envs, 16 control
+  // steps: 677 us a call issued, 680 replayed; a first call 0.8 against 1.1 ms)
+  if (!plain && s->lanes_on)
+    return enqueue_steps(s, s->stream, actions, T, targets, traj, stats, false, true);
   GraphKey key{T, plain ? 1 : 0, actions, targets, traj, stats};
   auto it = s->graphs.find(key);
   if (it == s->graphs.end()) {

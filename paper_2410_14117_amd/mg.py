@@ -420,7 +420,8 @@ class Sim:
         return out
 
     def step(self, actions, targets=None, traj=None, stats=None, plain=False):
-        """actions [n_ctrl][N_max][E]: n_ctrl control steps fused in one launch."""
+        """actions [n_ctrl][N_max][E]: n_ctrl control steps fused in one launch, or in one per
+        class (see mg_step)."""
         n_ctrl = int(actions.shape[0])
         a, tg, tr, st = self._step_args(actions, n_ctrl, targets, traj, stats)
         self._bind_stream()
@@ -428,8 +429,9 @@ class Sim:
         self._check(fn(self._h, a, n_ctrl, tg, tr, st))
 
     def rollout(self, actions, targets=None, traj=None, stats=None, plain=False):
-        """actions [T][N_max][E]: T control steps in one launch (plain: one launch per sub-step,
-        replayed from a cached HIP graph; see mg_rollout)."""
+        """actions [T][N_max][E]: T control steps in one launch, or in one per class and control
+        step (plain: one per class and sub-step, replayed from a cached HIP graph); see
+        mg_rollout."""
         T = int(actions.shape[0])
         a, tg, tr, st = self._step_args(actions, T, targets, traj, stats)
         self._bind_stream()
