@@ -66,6 +66,26 @@ __device__ __forceinline__ float theta_bar_get(const ThetaBarLds& t, int k) {
   return *(volatile float*)(t.ma.p + k * kBlock);
 }
 
+// Nothing is scheduled across it: the stage VJPs, which hold the most values of a
+// sub-step, each begin where the one before has ended.  Without it the compiler
+// interleaves them (one wave per SIMD, 20 000 lag-free Heavies, 8 control steps of 4
+// sub-steps: backward 113 against 106 us) and, in the two-wave sweeps, spills for it.
+__host__ __device__ __forceinline__ void sched_fence() {
+#ifdef __HIP_DEVICE_COMPILE__
+  __builtin_amdgcn_sched_barrier(0);
+#endif
+}
+
+// A factor the compiler takes for another value than it has been: products with it
+// are formed again instead of being kept.
+template <class T>
+__host__ __device__ __forceinline__ T formed_again(T v) {
+#ifdef __HIP_DEVICE_COMPILE__
+  asm volatile("" : "+s"(v));
+#endif
+  return v;
+}
+
 // dL/d(x, tau, theta) of xd = rhs_core(x, tau) given xdb = dL/dxd.
 // Writes xb (rows 3..12; the position rows receive nothing) and taub and
 // accumulates into thb.
@@ -81,7 +101,12 @@ __device__ __forceinline__ float theta_bar_get(const ThetaBarLds& t, int k) {
 //   t' = q_w g_p + g_p x q_v,  E = d_L + 2 d_Q |nu|
 //   q_v' = -w g_q0 + w x g_qv + t x g_p + 2 v x t' + (rows of k)
 //   q_w' = w . g_qv + t . g_p + 2 (q_x k'_y - q_y k'_x)
-template <class T, class TB>
+//
+// TIGHT (the two-wave recomputing sweeps, which spill): its parts in turn, in an
+// order that ends each value's life early.  With the wrenches formed again (below),
+// 150 000 lagged Heavies, 8 control steps of 2 sub-steps, 304 -> 238 us recomputed
+// first and 288 -> 285 us segment by segment; without a lag 189 -> 184 and 198 -> 194.
+template <bool TIGHT = false, class T, class TB>
 __host__ __device__ __forceinline__ void rhs_core_vjp(const T* x, const EnvConstT<T>& P,
                                                       const T (&tau)[6], const T* xdb, T* xb,
                                                       T (&taub)[6], TB& thb) {
@@ -129,6 +154,7 @@ __host__ __device__ __forceinline__ void rhs_core_vjp(const T* x, const EnvConst
   thb.hz -= k[1] * m[0];
   thb.hz += k[0] * m[1];
   T ab[3], bb[3], tb2[3], kb2[3], vb[3], wb[3], qb[3], s[3];
+  if constexpr (TIGHT) sched_fence();
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
@@ -140,34 +166,42 @@ __host__ __device__ __forceinline__ void rhs_core_vjp(const T* x, const EnvConst
     thb.dq[3 + i] += eba * abs_t(w[i]);
     const T el = fma_t(P.dq[i], abs_t(v[i]), fma_t(P.dq[i], abs_t(v[i]), P.dl[i]));
     const T ea = fma_t(P.dq[3 + i], abs_t(w[i]), fma_t(P.dq[3 + i], abs_t(w[i]), P.dl[3 + i]));
-    // [a; b] = M nu
-    ab[i] = fma_t(-v[i2], m[i1], fma_t(v[i1], m[i2], fma_t(-w[i2], f[i1], mul_nc(w[i1], f[i2]))));
-    bb[i] = fma_t(-w[i2], m[i1], mul_nc(w[i1], m[i2]));
     vb[i] = fma_t(-a[i1], m[i2], fma_t(a[i2], m[i1], fma_t(-el, f[i], gp[i])));
     wb[i] = fma_t(-b[i1], m[i2], fma_t(b[i2], m[i1],
             fma_t(-a[i1], f[i2], fma_t(a[i2], f[i1], mul_nc(-ea, m[i])))));
-    // quaternion rows (xd[3..6] = q (x) (0, w)) and t
+  }
+  if constexpr (TIGHT) sched_fence();
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
+    // quaternion rows (xd[3..6] = q (x) (0, w)), [a; b] = M nu, k = R^T e3
     wb[i] = fma_t(-gv[i2], q[i1], fma_t(gv[i1], q[i2], fma_t(qw, gv[i], fma_t(-q[i], gw, wb[i]))));
-    const T tb = fma_t(-gp[i2], q[i1], fma_t(gp[i1], q[i2], mul_nc(qw, gp[i])));
-    tb2[i] = tb + tb;
+    ab[i] = fma_t(-v[i2], m[i1], fma_t(v[i1], m[i2], fma_t(-w[i2], f[i1], mul_nc(w[i1], f[i2]))));
+    bb[i] = fma_t(-w[i2], m[i1], mul_nc(w[i1], m[i2]));
+    thb.ma[i] += v[i] * ab[i];
+    thb.ma[3 + i] += w[i] * bb[i];
     const T kb = mul_nc(P.wmb, f[i]);
     const T kbi = i == 0 ? fma_t(P.hz, m[1], kb) : (i == 1 ? fma_t(-P.hz, m[0], kb) : kb);
     kb2[i] = kbi + kbi;
-    qb[i] = fma_t(-w[i2], gv[i1], fma_t(w[i1], gv[i2], mul_nc(-w[i], gw)));
-    qb[i] = fma_t(-t[i2], gp[i1], fma_t(t[i1], gp[i2], qb[i]));
-    s[i] = fma_t(t[i], gp[i], mul_nc(w[i], gv[i]));
   }
-#pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    thb.ma[i] += v[i] * ab[i];
-    thb.ma[3 + i] += w[i] * bb[i];
-  }
+  if constexpr (TIGHT) sched_fence();
   vb[0] = fma_t(P.Muq, bb[1], fma_t(P.Muu, ab[0], vb[0]));
   vb[1] = fma_t(P.Mvp, bb[0], fma_t(P.Mvv, ab[1], vb[1]));
   vb[2] = fma_t(P.Mww, ab[2], vb[2]);
   wb[0] = fma_t(P.Mvp, ab[1], fma_t(P.Mpp, bb[0], wb[0]));
   wb[1] = fma_t(P.Muq, ab[0], fma_t(P.Mqq, bb[1], wb[1]));
   wb[2] = fma_t(P.Mrr, bb[2], wb[2]);
+  if constexpr (TIGHT) sched_fence();
+#pragma unroll
+  for (int i = 0; i < 3; ++i) {
+    const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
+    const T tb = fma_t(-gp[i2], q[i1], fma_t(gp[i1], q[i2], mul_nc(qw, gp[i])));
+    tb2[i] = tb + tb;
+    qb[i] = fma_t(-w[i2], gv[i1], fma_t(w[i1], gv[i2], mul_nc(-w[i], gw)));
+    qb[i] = fma_t(-t[i2], gp[i1], fma_t(t[i1], gp[i2], qb[i]));
+    s[i] = fma_t(t[i], gp[i], mul_nc(w[i], gv[i]));
+  }
+  if constexpr (TIGHT) sched_fence();
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
     const int i1 = (i + 1) % 3, i2 = (i + 2) % 3;
@@ -191,8 +225,11 @@ __host__ __device__ __forceinline__ void rhs_core_vjp(const T* x, const EnvConst
 
 // Reverse of rk4_substep: y is the sub-step input (D rows), lam holds dL/d(output)
 // on entry and dL/dy on exit; dL/d f_cmd and dL/d (B f_cmd) accumulate into fcb and
-// gcb, parameter adjoints into thb.
-template <int N, bool LAG, class T, class TB>
+// gcb, parameter adjoints into thb.  TIGHT: the stage wrenches are formed again
+// for the stage VJPs, so that neither they nor the residuals with them are held from
+// the forward recomputation on (130 more VALU instructions, 9-22 fewer spilled
+// registers).
+template <int N, bool LAG, bool TIGHT = false, class T, class TB>
 __host__ __device__ __forceinline__ void rk4_substep_vjp(const T* y, const EnvConstT<T>& P,
                                                          const ClassConst& cc,
                                                          const T (&fcmd)[N], const T (&gcmd)[6],
@@ -263,6 +300,15 @@ __host__ __device__ __forceinline__ void rk4_substep_vjp(const T* y, const EnvCo
   // combination z' = y + fac(h6) (k1 + 2 k2 + 2 k3 + k4), then the stages in
   // reverse; the position rows of Xb stay zero
   T yb[13], kb[13], Xb[13], tb1[6], tb2[6], tb3[6], tb4[6];
+  auto begin_stage = [&](T sigma, T (&tau)[6]) {
+    if constexpr (LAG && TIGHT) {
+      const T sg = formed_again(sigma);
+#pragma unroll
+      for (int j = 0; j < 6; ++j) tau[j] = fma_t(sg, dg[j], gcmd[j]);
+    }
+    theta_bar_fence(thb);
+    sched_fence();
+  };
   auto scale = [&](T weight) {   // kb = weight fac(h6) zb
 #pragma unroll
     for (int i = 0; i < 13; ++i) kb[i] = mul_nc(weight * fac(i, h6), zb[i]);
@@ -277,20 +323,20 @@ __host__ __device__ __forceinline__ void rk4_substep_vjp(const T* y, const EnvCo
 #pragma unroll
   for (int i = 0; i < 13; ++i) yb[i] = zb[i];
   scale(T(1));
-  theta_bar_fence(thb);
-  rhs_core_vjp(X4, P, tau4, kb, Xb, tb4, thb);          // X4 = y + fac(dt) k3
+  begin_stage(T(cc.sigma4), tau4);
+  rhs_core_vjp<TIGHT>(X4, P, tau4, kb, Xb, tb4, thb);   // X4 = y + fac(dt) k3
   scale(T(2));
   add_stage(dt);
-  theta_bar_fence(thb);
-  rhs_core_vjp(X3, P, tau3, kb, Xb, tb3, thb);          // X3 = y + fac(h2) k2
+  begin_stage(T(cc.sigma3), tau3);
+  rhs_core_vjp<TIGHT>(X3, P, tau3, kb, Xb, tb3, thb);   // X3 = y + fac(h2) k2
   scale(T(2));
   add_stage(h2);
-  theta_bar_fence(thb);
-  rhs_core_vjp(X2, P, tau2, kb, Xb, tb2, thb);          // X2 = y + fac(h2) k1
+  begin_stage(T(cc.sigma2), tau2);
+  rhs_core_vjp<TIGHT>(X2, P, tau2, kb, Xb, tb2, thb);   // X2 = y + fac(h2) k1
   scale(T(1));
   add_stage(h2);
-  theta_bar_fence(thb);
-  rhs_core_vjp(y, P, tau1, kb, Xb, tb1, thb);           // X1 = y
+  begin_stage(T(1), tau1);
+  rhs_core_vjp<TIGHT>(y, P, tau1, kb, Xb, tb1, thb);    // X1 = y
 #pragma unroll
   for (int i = 0; i < 3; ++i) lam[i] = yb[i];
 #pragma unroll
@@ -548,7 +594,7 @@ __host__ __device__ __forceinline__ void adj_bwd_env(const AdjArgs& a, const Cla
           for (int s = S - 1; s >= 0; --s) {
             float y[D];
             load_input(t, s, base, y);
-            rk4_substep_vjp<N, LAG>(y, P, cc, fcmd, gcmd, a.dt, lam, fcb, gcb, thb);
+            rk4_substep_vjp<N, LAG, true>(y, P, cc, fcmd, gcmd, a.dt, lam, fcb, gcb, thb);
           }
         }
         throttle_vjp<N>(cc, act, fcb, gcb, ab);
