@@ -7,7 +7,7 @@
 // don't-care values in the 3-vectors that no other lane reads.
 //
 // A reverse sub-step is 1700-1850 VALU instructions with one env per lane (the
-// chain that a launch of few waves waits for) and about 830 here, 360 of them in
+// chain that a launch of few waves waits for) and 660-740 here, 345 of them in
 // the chain of state adjoints: a cross product is two FMAs for its three
 // components, and each rotated operand is one DPP move shared by all the
 // products that read it.

@@ -271,8 +271,8 @@ k_adj_quad_bwd(const AdjArgs a, const ClassSegs segs) {
 // LDS holds float4 columns of 64 lanes: the chain's input (16 values of each
 // stage, q and 1/|q|) twice, what the parameters read of the stages (5 of each)
 // three times, and of the chain (4 of each) twice: 57 KiB, two blocks to a CU.
-// 441 instructions in wave 0's phase against 900 of the one-wave sweep's
-// sub-step, 400-500 in wave 1's, 250-300 in wave 2's.
+// 445 instructions in wave 0's phase, of them 345 VALU for a sub-step, against 710-980
+// of the one-wave sweep (660-740 VALU), 370-450 in wave 1's, 200-300 in wave 2's.
 constexpr int kTrioIn = 17, kTrioTheta = 5, kTrioOut = 4;   // columns
 constexpr int kTrioColumns = 2 * kTrioIn + 3 * kTrioTheta + 2 * kTrioOut;
 

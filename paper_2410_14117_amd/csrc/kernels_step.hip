@@ -159,8 +159,11 @@ __global__ void __launch_bounds__(kBlock) MG_STEP_ATTR k_step(const StepArgs a, 
 // (a.each).  All classes have a lag or none has; N is the most thrusters of any.
 // The class constants and the row pointers are formed anew at each use (the
 // pins): held in scalar registers across the control steps they spill, which
-// took 20 us of a control step of 2^20 envs.  168 VGPRs, no spills.  Per control
-// step, before (a launch per class and control step, forked and joined or
+// took 20 us of a control step of 2^20 envs.  168 VGPRs, none spilled; of the
+// scalar registers 57 (8 lagged thrusters; 40 without a lag) still go to vector
+// lanes, none in the sub-step loop: with the largest class's thrusters it makes a
+// control step cost about 95 VALU and 185 scalar instructions more than k_step's.
+// Which calls it is used for: one_launch (runtime.hip).  Per control step, before (a launch per class and control step, forked and joined or
 // replayed from a graph) and with all in one launch, lagged envs, alternating
 // runs: two classes, one call per control step with statistics, 131072 envs of 4
 // sub-steps 48 -> 17.0 us, 2^20 of 16 187 -> 180; rollouts of 20, 4 sub-steps,

@@ -37,7 +37,7 @@ enum DerivedRow : int {
 struct ClassConst {
   float B[6][kMaxThr];   // allocation matrix
   float f_max;
-  float inv_tau;         // 1 / thruster lag (0 if none)
+  float inv_tau;         // 1 / thruster lag (0 if none); read by no kernel
   // Classical RK4 applied to the linear lag f' = (f_cmd - f) / tau with the
   // command held: with z = dt / tau the stage values are
   //   f_cmd + sigma_i (f - f_cmd),  sigma = 1, 1 - z/2, 1 - z/2 + z^2/4, 1 - z + z^2/2 - z^3/4
