@@ -426,25 +426,32 @@ mg_status enqueue_steps(mg_sim* s, hipStream_t st, const float* actions, int32_t
     MG_HIP(s, hipEventRecord(s->ev_fork[k - 1], st));
     MG_HIP(s, hipStreamWaitEvent(s->aux[k - 1], s->ev_fork[k - 1], 0));
   }
-  // control step by control step, so that the classes advance together also while
-  // the launches are being issued
-  const bool together = !plain && !one_launch_per_ctrl;
   const int32_t n_sub = plain ? s->substeps : 1;
-  a.n_ctrl = together ? n_ctrl : 1;
+  a.n_ctrl = !plain && !one_launch_per_ctrl ? n_ctrl : 1;
   a.substeps = plain ? 1 : s->substeps;
-  for (int32_t t = 0; t < n_ctrl; t += a.n_ctrl) {
+  auto launch = [&](int k, int32_t t) {   // class k from control step t
+    a.seg_start = s->seg_start[k];
+    a.seg_len = s->seg_len[k];
+    a.blk_off = s->seg_blk_off[k];
     a.actions = actions + t * frame;
-    for (int32_t sub = 0; sub < n_sub; ++sub) {
+    hipError_t e = hipSuccess;
+    for (int32_t sub = 0; sub < n_sub && e == hipSuccess; ++sub) {
       const bool last = sub == n_sub - 1;
       a.traj = (traj && last) ? traj + t * tframe : nullptr;
       a.partials = (stats && last) ? s->partials + t * pframe : nullptr;
-      for (int k = 0; k < s->n_classes; ++k) {
-        a.seg_start = s->seg_start[k];
-        a.seg_len = s->seg_len[k];
-        a.blk_off = s->seg_blk_off[k];
-        MG_HIP(s, launch_step(s->cc[k], a, k == 0 ? st : s->aux[k - 1]));
-      }
+      e = launch_step(s->cc[k], a, k == 0 ? st : s->aux[k - 1]);
     }
+    return e;
+  };
+  if (!plain && one_launch_per_ctrl) {
+    // the classes advance together also while the launches are being issued
+    for (int32_t t = 0; t < n_ctrl; ++t)
+      for (int k = 0; k < s->n_classes; ++k) MG_HIP(s, launch(k, t));
+  } else {
+    // one stream after the other, which takes the host less (16 classes, 16
+    // sub-steps a call: 950 us against 1150)
+    for (int k = 0; k < s->n_classes; ++k)
+      for (int32_t t = 0; t < n_ctrl; t += a.n_ctrl) MG_HIP(s, launch(k, t));
   }
   for (int k = 1; k < s->n_classes; ++k) {
     MG_HIP(s, hipEventRecord(s->ev_join[k - 1], s->aux[k - 1]));
