@@ -350,6 +350,7 @@ hipError_t launch_gather_out(const float* in, int64_t Ep, float* out, int64_t E,
                              const int32_t* iperm, hipStream_t s);
 // out[r][j] = in[r][perm[j]] (caller -> internal order), padding lanes untouched
 hipError_t launch_scatter_in(const float* in, int64_t E, float* out, int64_t Ep, int32_t rows,
-                             const int32_t* perm, int64_t n_internal, hipStream_t s);
+                             const int32_t* perm, int64_t n_internal, int32_t n_classes,
+                             hipStream_t s);
 
 }  // namespace mg
