@@ -280,6 +280,38 @@ __host__ __device__ __forceinline__ int block_class(const ClassSegs& segs, int b
   return wave_uniform(k);
 }
 
+// What a kernel over all classes, or over the only one (its constants kernel
+// arguments, all its thrusters N), needs of a block's class.
+template <class SEGS>
+struct BlockClass;
+template <>
+struct BlockClass<ClassSegs> {
+  static constexpr bool kOne = false;
+  const ClassConst* ccp;
+  int k, block;
+  int64_t start, len;
+  __device__ __forceinline__ BlockClass(const ClassSegs& segs, int b) {
+    k = block_class(segs, b, block);
+    ccp = segs.cc + k;
+    start = segs.start[k];
+    len = segs.len[k];
+  }
+  __device__ __forceinline__ ClassConst constants() const {
+    return scalar_class_const(pin_sgpr(ccp));
+  }
+};
+template <>
+struct BlockClass<OneClass> {
+  static constexpr bool kOne = true;
+  static constexpr int k = 0;
+  const OneClass& one;
+  int block;
+  int64_t start, len;
+  __device__ __forceinline__ BlockClass(const OneClass& o, int b)
+      : one(o), block(b), start(o.start), len(o.len) {}
+  __device__ __forceinline__ const ClassConst& constants() const { return one.cc; }
+};
+
 // The throttles of a class of n <= N thrusters; rows past n hold some other
 // throttle until mask_throttles makes them zeros.  With their columns of B,
 // which are zero too, N-thruster code then gives that class's results.  Two

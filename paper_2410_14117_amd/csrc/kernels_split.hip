@@ -60,19 +60,23 @@ __device__ __forceinline__ RigidInv rigid_inverse(const float* params, int64_t E
 // Lagged Heavies, 10 control steps of 16 sub-steps with trajectory, with a launch
 // per class and the lag states stepped, and now: 32 768 envs 74 -> 57 us, 131 072
 // 109 -> 81, 524 288 400 -> 294.
-template <int N, bool LAG>
-__global__ void __launch_bounds__(kBlock) k_split(const SplitArgs a, const ClassSegs segs) {
+// A sim of one class takes its constants from the kernel's arguments (OneClass); read
+// through memory, short calls of few sub-steps took up to 25 % longer.
+template <int N, bool LAG, class SEGS>
+__global__ void __launch_bounds__(kBlock) k_split(const SplitArgs a, const SEGS segs) {
   constexpr int D = Dims<N, LAG>::D;
-  int block;
-  const int k = block_class(segs, blockIdx.x, block);
-  const ClassConst* ccp = segs.cc + k;
-  const int n = scalar_class_const(ccp).n_thr;
-  const bool lag = LAG && scalar_class_const(ccp).lag;
-  const int Dc = 13 + (lag ? n : 0);     // this class's rows
-  const int64_t local = (int64_t)block * kBlock + threadIdx.x;
-  if (local >= segs.len[k]) return;
-  if (!MG_CHECK(a, segs.start[k] + segs.len[k] <= a.Ep, kDbgSegment)) return;
-  const int64_t j = segs.start[k] + local;
+  const BlockClass<SEGS> cls(segs, blockIdx.x);
+  int n = N, Dc = D;                     // this class's thrusters and rows
+  bool lag = LAG;
+  if constexpr (!cls.kOne) {
+    n = cls.constants().n_thr;
+    lag = LAG && cls.constants().lag;
+    Dc = 13 + (lag ? n : 0);
+  }
+  const int64_t local = (int64_t)cls.block * kBlock + threadIdx.x;
+  if (local >= cls.len) return;
+  if (!MG_CHECK(a, cls.start + cls.len <= a.Ep, kDbgSegment)) return;
+  const int64_t j = cls.start + local;
   const uint32_t jo = (uint32_t)j * 4u;
   const int64_t c = a.perm ? (int64_t)lane_elem(a.perm, jo) : j;
   if (!MG_CHECK(a, c >= 0 && c < a.dbg.cols, kDbgColumn)) return;
@@ -93,13 +97,13 @@ __global__ void __launch_bounds__(kBlock) k_split(const SplitArgs a, const Class
   const int64_t frame = (int64_t)a.n_max * a.E;
   float nxt[N];
   load_throttles<N>(n, a.actions, a.E, co, nxt);
-  const RigidInv I = rigid_inverse(a.params, a.Ep, jo, a.nominal[k].zg);
+  const RigidInv I = rigid_inverse(a.params, a.Ep, jo, a.nominal[cls.k].zg);
   const float dt = to_vgpr(a.dt), hdt = to_vgpr(0.5f * a.dt);
-  const float kappa = to_vgpr(scalar_class_const(ccp).kappa);
+  const float kappa = to_vgpr(cls.constants().kappa);
 #pragma unroll
   for (int i = 13; i < D; ++i) x[i] = i < Dc ? x[i] : 0.0f;
   for (int t = 0; t < a.n_ctrl; ++t) {
-    const ClassConst cc = scalar_class_const(pin_sgpr(ccp));
+    const ClassConst cc = cls.constants();
     float fcmd[N], gcmd[6], dg[6];
     mask_throttles<N>(n, nxt);
     thrust_command<N>(cc, nxt, fcmd);
@@ -270,8 +274,8 @@ __global__ void __launch_bounds__(kQuadBlock) k_split_quad(const SplitArgs a,
 
 #pragma clang fp contract(fast)
 
-hipError_t launch_split(const ClassSegs& segs, const SplitArgs& a, bool lag, bool quad,
-                        hipStream_t s) {
+hipError_t launch_split(const ClassSegs& segs, const ClassConst& cc, const SplitArgs& a, bool lag,
+                        bool quad, hipStream_t s) {
   const int nblk = segs.blk_end[segs.n - 1];
   if (nblk == 0) return hipSuccess;
   // 32-bit lane offsets: one row, or (quad) every row at once
@@ -283,12 +287,21 @@ hipError_t launch_split(const ClassSegs& segs, const SplitArgs& a, bool lag, boo
   else if (quad)
     hipLaunchKernelGGL((k_split_quad<false>), grid, dim3(kQuadBlock), 0, s, a, segs);
   if (quad) return hipGetLastError();
-#define MG_CASE(n)                                                                     \
-  case n:                                                                              \
-    if (lag)                                                                           \
-      hipLaunchKernelGGL((k_split<n, true>), grid, dim3(kBlock), 0, s, a, segs);       \
-    else                                                                               \
-      hipLaunchKernelGGL((k_split<n, false>), grid, dim3(kBlock), 0, s, a, segs);      \
+  const dim3 block(kBlock);
+  const OneClass one{cc, segs.start[0], segs.len[0]};
+#define MG_LAUNCH(N, lagged)                                                                  \
+  do {                                                                                        \
+    if (segs.n == 1)                                                                          \
+      hipLaunchKernelGGL((k_split<N, lagged, OneClass>), grid, block, 0, s, a, one);          \
+    else                                                                                      \
+      hipLaunchKernelGGL((k_split<N, lagged, ClassSegs>), grid, block, 0, s, a, segs);        \
+  } while (0)
+#define MG_CASE(n)       \
+  case n:                \
+    if (lag)             \
+      MG_LAUNCH(n, true); \
+    else                 \
+      MG_LAUNCH(n, false); \
     break;
   switch (a.n_max) {
     MG_CASE(1) MG_CASE(2) MG_CASE(3) MG_CASE(4) MG_CASE(5) MG_CASE(6) MG_CASE(7) MG_CASE(8)
@@ -296,6 +309,7 @@ hipError_t launch_split(const ClassSegs& segs, const SplitArgs& a, bool lag, boo
       return hipErrorInvalidValue;
   }
 #undef MG_CASE
+#undef MG_LAUNCH
   return hipGetLastError();
 }
 

@@ -129,26 +129,28 @@ __device__ __forceinline__ void curve_sincos(const TaskConst& tc, double t, doub
 // for all classes instead of one each, forked and joined through events: 7 task
 // steps of 57 059 interleaved envs with reset and read-back 436 -> 167 us, 9 of
 // 214 719 703 -> 555 us, 2 of 2^20 with 16 sub-steps 620 -> 610 us.
-template <int N, bool LAG>
+// A sim of one class takes its constants from the kernel's arguments (OneClass): read
+// through memory, and with the selects for smaller classes, a task step of 20 000 to
+// 300 000 envs took 4-16 % longer, an observation 3-18 %.
+template <int N, bool LAG, class SEGS>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
-k_task(const TaskArgs a, const ClassSegs segs, const TaskConst tc) {
+k_task(const TaskArgs a, const SEGS segs, const TaskConst tc) {
   constexpr int D = Dims<N, LAG>::D;
-  int block;
-  const int cls = block_class(segs, blockIdx.x, block);
-  const ClassConst* ccp = segs.cc + cls;
-  const int64_t local = (int64_t)block * kBlock + threadIdx.x;
-  if (local >= segs.len[cls]) return;
-  if (!MG_CHECK(a, segs.start[cls] + segs.len[cls] <= a.Ep, kDbgSegment)) return;
-  const int64_t j = segs.start[cls] + local;
+  const BlockClass<SEGS> cls(segs, blockIdx.x);
+  const int64_t local = (int64_t)cls.block * kBlock + threadIdx.x;
+  if (local >= cls.len) return;
+  if (!MG_CHECK(a, cls.start + cls.len <= a.Ep, kDbgSegment)) return;
+  const int64_t j = cls.start + local;
   const uint32_t jo = (uint32_t)j * 4u;
   const int64_t c = a.perm ? (int64_t)lane_elem(a.perm, jo) : j;
   if (!MG_CHECK(a, c >= 0 && c < a.dbg.cols, kDbgColumn)) return;
   const uint32_t co = (uint32_t)c * 4u;
   float x[D];
-  int Dc;   // the class's rows
-  {
-    const ClassConst cc = scalar_class_const(ccp);
-    Dc = 13 + (LAG && cc.lag ? cc.n_thr : 0);
+  int n = N, Dc = D;   // the class's thrusters and rows
+  if constexpr (!cls.kOne) {
+    const ClassConst cc = cls.constants();
+    n = cc.n_thr;
+    Dc = 13 + (LAG && cc.lag ? n : 0);
   }
 #pragma unroll
   for (int i = 0; i < D; ++i)
@@ -156,12 +158,12 @@ k_task(const TaskArgs a, const ClassSegs segs, const TaskConst tc) {
   int32_t k = lane_elem(a.task_k, jo);
   if (a.actions) {
     const EnvConst P = load_env_const_off(a.derived, a.Ep, jo);
-    const ClassConst cc = scalar_class_const(pin_sgpr(ccp));
+    const ClassConst cc = cls.constants();
     float act[N], fcmd[N], gcmd[6];
-    load_throttles<N>(cc.n_thr, a.actions, a.E, co, act);
+    load_throttles<N>(n, a.actions, a.E, co, act);
     const StepConstT<float> sc = make_step_const(cc, a.dt);
     const HalfInvT<float> A = half_step_inverse(P, sc.h2);
-    mask_throttles<N>(cc.n_thr, act);
+    mask_throttles<N>(n, act);
     thrust_command<N>(cc, act, fcmd);
     command_wrench<N>(cc, fcmd, gcmd);
     // rows past the class's: at their commands, so that they have no lag wrench
@@ -204,7 +206,7 @@ k_task(const TaskArgs a, const ClassSegs segs, const TaskConst tc) {
       curve_sincos(tc, 0.0, phase, sn, cs);
       uint8_t fl = (uint8_t)(a.flags[j] & kFlagNotSPD);
       if (a.reset_mult)
-        fl = set_env_params(a.nominal[cls], a.reset_mult + c, a.E, false, a.params, a.derived,
+        fl = set_env_params(a.nominal[cls.k], a.reset_mult + c, a.E, false, a.params, a.derived,
                             a.Ep, j) ? 0 : kFlagNotSPD;
       a.flags[j] = fl;
     }
@@ -358,8 +360,8 @@ __global__ void __launch_bounds__(kQuadBlock) k_task_quad(const TaskArgs a, cons
   }
 }
 
-hipError_t launch_task(const ClassSegs& segs, const TaskConst& tc, const TaskArgs& a, bool lag,
-                       bool quad, hipStream_t s) {
+hipError_t launch_task(const ClassSegs& segs, const ClassConst& cc, const TaskConst& tc,
+                       const TaskArgs& a, bool lag, bool quad, hipStream_t s) {
   const int nblk = segs.blk_end[segs.n - 1];
   if (nblk == 0) return hipSuccess;
   // 32-bit lane offsets: one row, or (quad) every row at once
@@ -373,12 +375,20 @@ hipError_t launch_task(const ClassSegs& segs, const TaskConst& tc, const TaskArg
       hipLaunchKernelGGL((k_task_quad<false>), grid, dim3(kQuadBlock), 0, s, a, segs, tc);
     return hipGetLastError();
   }
-#define MG_CASE(n)                                                              \
-  case n:                                                                       \
-    if (lag)                                                                    \
-      hipLaunchKernelGGL((k_task<n, true>), grid, block, 0, s, a, segs, tc);    \
-    else                                                                        \
-      hipLaunchKernelGGL((k_task<n, false>), grid, block, 0, s, a, segs, tc);   \
+  const OneClass one{cc, segs.start[0], segs.len[0]};
+#define MG_LAUNCH(N, lagged)                                                                  \
+  do {                                                                                        \
+    if (segs.n == 1)                                                                          \
+      hipLaunchKernelGGL((k_task<N, lagged, OneClass>), grid, block, 0, s, a, one, tc);       \
+    else                                                                                      \
+      hipLaunchKernelGGL((k_task<N, lagged, ClassSegs>), grid, block, 0, s, a, segs, tc);     \
+  } while (0)
+#define MG_CASE(n)       \
+  case n:                \
+    if (lag)             \
+      MG_LAUNCH(n, true); \
+    else                 \
+      MG_LAUNCH(n, false); \
     break;
   switch (a.n_max) {
     MG_CASE(1) MG_CASE(2) MG_CASE(3) MG_CASE(4) MG_CASE(5) MG_CASE(6) MG_CASE(7) MG_CASE(8)
@@ -386,6 +396,7 @@ hipError_t launch_task(const ClassSegs& segs, const TaskConst& tc, const TaskArg
       return hipErrorInvalidValue;
   }
 #undef MG_CASE
+#undef MG_LAUNCH
   return hipGetLastError();
 }
 

@@ -117,6 +117,12 @@ struct ClassSegs {
   float zb[MG_MAX_CLASSES];    // z_b of the class (dL/dB through h_z)
 };
 
+// The same of a sim of one class, whose constants are then kernel arguments.
+struct OneClass {
+  ClassConst cc;
+  int64_t start, len;
+};
+
 struct StepArgs {
   float* state;                // internal [D][Ep]
   uint8_t* flags;              // internal [Ep] status flags (read, set when an env freezes)
@@ -335,12 +341,12 @@ hipError_t launch_step_classes(const ClassSegs& segs, const StepArgs& a, bool la
 hipError_t launch_stats_finalize(const double* partials, int32_t nblk, int32_t n_ctrl,
                                  double* stats, hipStream_t s);
 hipError_t launch_reset(const ResetArgs& a, hipStream_t s);
-// all classes in one launch, one env per lane or (quad) per quad of lanes
-hipError_t launch_task(const ClassSegs& segs, const TaskConst& tc, const TaskArgs& a, bool lag,
-                       bool quad, hipStream_t s);
-// all classes in one launch, one env per lane or (quad) per quad of lanes
-hipError_t launch_split(const ClassSegs& segs, const SplitArgs& a, bool lag, bool quad,
-                        hipStream_t s);
+// all classes in one launch, one env per lane or (quad) per quad of lanes; cc: the first
+// class's constants
+hipError_t launch_task(const ClassSegs& segs, const ClassConst& cc, const TaskConst& tc,
+                       const TaskArgs& a, bool lag, bool quad, hipStream_t s);
+hipError_t launch_split(const ClassSegs& segs, const ClassConst& cc, const SplitArgs& a, bool lag,
+                        bool quad, hipStream_t s);
 // status flags to caller order int32 [E]; flags &= mask for n envs
 hipError_t launch_flags_out(const uint8_t* flags, int32_t* out, int64_t E, const int32_t* perm,
                             int64_t n_internal, hipStream_t s);

@@ -657,8 +657,8 @@ mg_status enqueue_task(mg_sim* s, const float* actions, float* obs, float* err, 
   a.reset_state = reset_state;
   a.reset_mult = reset_mult;
   a.nominal = s->nominal_dev;
-  MG_HIP(s, launch_task(s->quad_on ? s->quad : s->lanes, s->task, a, s->any_lag, s->quad_on,
-                        s->stream));
+  MG_HIP(s, launch_task(s->quad_on ? s->quad : s->lanes, s->cc[0], s->task, a, s->any_lag,
+                        s->quad_on, s->stream));
   return MG_OK;
 }
 
@@ -1031,7 +1031,8 @@ mg_status mg_step_split(mg_sim* s, const float* actions, int32_t n_ctrl, float* 
   a.traj = traj;
   a.dt = (float)s->dt;
   a.nominal = s->nominal_dev;
-  MG_HIP(s, launch_split(s->quad_on ? s->quad : s->lanes, a, s->any_lag, s->quad_on, s->stream));
+  MG_HIP(s, launch_split(s->quad_on ? s->quad : s->lanes, s->cc[0], a, s->any_lag, s->quad_on,
+                         s->stream));
   return MG_OK;
 }
 
