@@ -280,6 +280,13 @@ __host__ __device__ __forceinline__ int block_class(const ClassSegs& segs, int b
   return wave_uniform(k);
 }
 
+// The block that the launch's i-th block is.
+__device__ __forceinline__ int launch_block(const ClassSegs& segs, int i) {
+  if (!segs.order) return i;
+  return ((const __attribute__((address_space(4))) int32_t*)(reinterpret_cast<uint64_t>(
+      segs.order)))[i];
+}
+
 // What a kernel over all classes, or over the only one (its constants kernel
 // arguments, all its thrusters N), needs of a block's class.
 template <class SEGS>
@@ -291,7 +298,7 @@ struct BlockClass<ClassSegs> {
   int k, block;
   int64_t start, len;
   __device__ __forceinline__ BlockClass(const ClassSegs& segs, int b) {
-    k = block_class(segs, b, block);
+    k = block_class(segs, launch_block(segs, b), block);
     ccp = segs.cc + k;
     start = segs.start[k];
     len = segs.len[k];

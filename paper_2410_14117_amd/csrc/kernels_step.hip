@@ -176,7 +176,8 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3))
 k_step_classes(const StepArgs a, const ClassSegs segs) {
   constexpr int D = Dims<N, LAG>::D;
   int block;
-  const int k = block_class(segs, blockIdx.x, block);
+  const int canonical = launch_block(segs, blockIdx.x);   // the statistics' partials are its
+  const int k = block_class(segs, canonical, block);
   const ClassConst* ccp = segs.cc + k;
   auto class_const = [&]() { return scalar_class_const(pin_sgpr(ccp)); };
   const int64_t seg_start = segs.start[k], seg_len = segs.len[k];
@@ -293,7 +294,7 @@ k_step_classes(const StepArgs a, const ClassSegs segs) {
     }
     if (a.partials)
       block_stats(s_dist, m_dist, s_ke, n_bad,
-                  a.partials + ((int64_t)t * a.nblk_total + blockIdx.x) * 4);
+                  a.partials + ((int64_t)t * a.nblk_total + canonical) * 4);
   }
   if (!active) return;
   if (!a.each && all_finite()) {

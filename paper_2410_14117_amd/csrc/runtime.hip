@@ -111,6 +111,7 @@ struct mg_sim {
   uint8_t* class_of = nullptr; // [Ep]
   uint8_t* flags = nullptr;    // [Ep] status flags (kFlagNonFinite, kFlagNotSPD)
   ClassNominal* nominal_dev = nullptr;
+  int32_t* block_order = nullptr;    // lanes.order
   ClassConst* cc_dev = nullptr;      // device copy of cc, behind nominal_dev's entries
   double* partials = nullptr;
   size_t partials_cap = 0;     // doubles
@@ -270,6 +271,28 @@ mg_status validate_vehicle(const mg_vehicle& v, int idx, std::string& why, bool&
   return MG_OK;
 }
 
+// ClassSegs::order: chunks of eight blocks of the classes, spread evenly over the
+// launch.
+std::vector<int32_t> interleaved_blocks(const ClassSegs& segs) {
+  constexpr int32_t kChunk = 8;
+  struct Chunk {
+    double at;   // its middle, as a share of its class's blocks
+    int32_t first, end;
+  };
+  std::vector<Chunk> chunks;
+  for (int k = 0, first = 0; k < segs.n; first = segs.blk_end[k++]) {
+    const double n = segs.blk_end[k] - first;
+    for (int32_t b = first; b < segs.blk_end[k]; b += kChunk)
+      chunks.push_back({(b - first + 0.5 * kChunk) / n, b, std::min(b + kChunk, segs.blk_end[k])});
+  }
+  std::stable_sort(chunks.begin(), chunks.end(),
+                   [](const Chunk& a, const Chunk& b) { return a.at < b.at; });
+  std::vector<int32_t> order;
+  for (const Chunk& c : chunks)
+    for (int32_t b = c.first; b < c.end; ++b) order.push_back(b);
+  return order;
+}
+
 mg_status ensure_partials(mg_sim* s, int32_t n_ctrl, int32_t nblk) {
   const size_t need = (size_t)std::max(n_ctrl, 1) * (size_t)nblk * 4;
   if (need <= s->partials_cap) return MG_OK;
@@ -368,7 +391,10 @@ bool quad_step(const mg_sim* s, int32_t n_ctrl, bool stats) {
 //    interleaved envs, 514 blocks: 1.05 at 0.8 x 2^20); far beyond, one launch takes
 //    1.03-1.20.  With a lag and 8 or more sub-steps one launch stays ahead
 //    (0.93-1.01), and so it does when it writes the trajectory with fewer than 4
-//    (0.80-0.99), whose stores its loads never wait for.
+//    (0.80-0.99), whose stores its loads never wait for, or, of interleaved classes,
+//    with fewer than 16, whose lines the classes' blocks write together
+//    (ClassSegs::order; 2^20 envs, 8 steps of 4 sub-steps: 2 classes 666 against 850
+//    us, 8 classes 1212 against 3004).
 bool one_launch(const mg_sim* s, int32_t n_ctrl, bool each_step, bool traj) {
   if (!s->lanes_on) return false;
   if (s->n_classes == 1 || s->nblk_total <= 2 * s->n_cu) return true;
@@ -381,7 +407,7 @@ bool one_launch(const mg_sim* s, int32_t n_ctrl, bool each_step, bool traj) {
     if (s->lopsided) return rounds(s->nblk_total) * 4 <= rounds(s->nblk_largest) * 5;
     return s->any_lag && large;
   }
-  if ((s->any_lag && S >= 8) || (traj && S < 4)) return true;
+  if ((s->any_lag && S >= 8) || (traj && S < (s->lanes.order ? 16 : 4))) return true;
   const bool uneven = rounds(s->nblk_total) * s->n_cu > s->nblk_total * 5 / 4;
   const int log2 = 22 - s->lopsided - uneven - (s->any_lag ? 0 : (S >= 4) + (S >= 16));
   return s->E * n_ctrl <= (int64_t)1 << log2;
@@ -845,6 +871,19 @@ mg_status mg_create(const mg_config* cfg, mg_sim** out) {
   s->cc_dev = reinterpret_cast<ClassConst*>(reinterpret_cast<char*>(s->nominal_dev) +
                                             nominal_bytes);
   s->quad.cc = s->lanes.cc = s->cc_dev;
+  if (!in_order && !s->quad_on) {
+    const std::vector<int32_t> order = interleaved_blocks(s->lanes);
+    if (hipMalloc(&s->block_order, order.size() * sizeof(int32_t)) != hipSuccess) {
+      (void)hipGetLastError();
+      return bail(MG_ERR_OOM, "out of device memory in mg_create");
+    }
+    if (hipMemcpy(s->block_order, order.data(), order.size() * sizeof(int32_t),
+                  hipMemcpyHostToDevice) != hipSuccess) {
+      (void)hipGetLastError();
+      return bail(MG_ERR_DEVICE, "device initialisation failed in mg_create");
+    }
+    s->lanes.order = s->block_order;
+  }
   // the debug build's failed-check word; MG_DEBUG_SHRINK=k (read here, debug
   // build only) makes the kernels treat caller columns >= E - k as out of
   // bounds, so that a test can see the checks fire while every access stays in
@@ -900,7 +939,7 @@ void mg_destroy(mg_sim* s) {
     for (hipEvent_t e : s->ev_fork) (void)hipEventDestroy(e);
     for (hipEvent_t e : s->ev_join) (void)hipEventDestroy(e);
     void* bufs[] = {s->state, s->params, s->derived, s->perm, s->iperm, s->class_of, s->flags,
-                    s->nominal_dev, s->partials, s->staging, s->segbuf, s->task_f, s->task_k,
+                    s->nominal_dev, s->block_order, s->partials, s->staging, s->segbuf, s->task_f, s->task_k,
                     s->split_acc, s->dbg.word};
     for (void* b : bufs)
       if (b) (void)hipFree(b);

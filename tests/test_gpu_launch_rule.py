@@ -22,7 +22,8 @@ LIN = [BLUEROV2, BLUEROV2_HEAVY]
     (LAG, 0.02, 131072, 16, "rollout", 6, 3, False),    # the small class in a third round
     (LIN, 0.02, 524291, 16, "rollout", 18, 9, False),   # one class has nearly all
     (LAG, 0.5, 524291, 2, "step", 10, 5, False),        # 2^22 env control steps
-    (LIN, 0.5, 524291, 4, "step", 6, 3, True),          # 2^21
+    (LIN, 0.5, 524291, 4, "step", 6, 3, False),         # 2^21
+    (LIN, 0.5, 524291, 16, "step", 3, 1, True),         # 2^20, trajectory of interleaved classes
     (LIN, 0.02, 140001, 16, "step", 6, 3, True),        # 2^19
 ])
 def test_a_call_equals_its_pieces(classes, share, E, S, mode, T, piece, with_traj):
