@@ -280,11 +280,10 @@ __host__ __device__ __forceinline__ int block_class(const ClassSegs& segs, int b
   return wave_uniform(k);
 }
 
-// The block that the launch's i-th block is.
-__device__ __forceinline__ int launch_block(const ClassSegs& segs, int i) {
-  if (!segs.order) return i;
-  return ((const __attribute__((address_space(4))) int32_t*)(reinterpret_cast<uint64_t>(
-      segs.order)))[i];
+// The block that the launch's i-th block is (order: ClassSegs::order).
+__device__ __forceinline__ int launch_block(const int32_t* order, int i) {
+  if (!order) return i;
+  return ((const __attribute__((address_space(4))) int32_t*)(reinterpret_cast<uint64_t>(order)))[i];
 }
 
 // What a kernel over all classes, or over the only one (its constants kernel
@@ -298,11 +297,14 @@ struct BlockClass<ClassSegs> {
   int k, block;
   int64_t start, len;
   __device__ __forceinline__ BlockClass(const ClassSegs& segs, int b) {
-    k = block_class(segs, launch_block(segs, b), block);
+    k = block_class(segs, launch_block(segs.order, b), block);
     ccp = segs.cc + k;
     start = segs.start[k];
     len = segs.len[k];
   }
+  // at the start, where what is read can be shared, and anew at each later use
+  // (nothing held in scalar registers between)
+  __device__ __forceinline__ ClassConst first_constants() const { return scalar_class_const(ccp); }
   __device__ __forceinline__ ClassConst constants() const {
     return scalar_class_const(pin_sgpr(ccp));
   }
@@ -316,6 +318,7 @@ struct BlockClass<OneClass> {
   int64_t start, len;
   __device__ __forceinline__ BlockClass(const OneClass& o, int b)
       : one(o), block(b), start(o.start), len(o.len) {}
+  __device__ __forceinline__ const ClassConst& first_constants() const { return one.cc; }
   __device__ __forceinline__ const ClassConst& constants() const { return one.cc; }
 };
 

@@ -69,8 +69,8 @@ __global__ void __launch_bounds__(kBlock) k_split(const SplitArgs a, const SEGS 
   int n = N, Dc = D;                     // this class's thrusters and rows
   bool lag = LAG;
   if constexpr (!cls.kOne) {
-    n = cls.constants().n_thr;
-    lag = LAG && cls.constants().lag;
+    n = cls.first_constants().n_thr;
+    lag = LAG && cls.first_constants().lag;
     Dc = 13 + (lag ? n : 0);
   }
   const int64_t local = (int64_t)cls.block * kBlock + threadIdx.x;
@@ -99,7 +99,7 @@ __global__ void __launch_bounds__(kBlock) k_split(const SplitArgs a, const SEGS 
   load_throttles<N>(n, a.actions, a.E, co, nxt);
   const RigidInv I = rigid_inverse(a.params, a.Ep, jo, a.nominal[cls.k].zg);
   const float dt = to_vgpr(a.dt), hdt = to_vgpr(0.5f * a.dt);
-  const float kappa = to_vgpr(cls.constants().kappa);
+  const float kappa = to_vgpr(cls.first_constants().kappa);
 #pragma unroll
   for (int i = 13; i < D; ++i) x[i] = i < Dc ? x[i] : 0.0f;
   for (int t = 0; t < a.n_ctrl; ++t) {

@@ -163,21 +163,24 @@ __global__ void __launch_bounds__(kBlock) MG_STEP_ATTR k_step(const StepArgs a, 
 // scalar registers 57 (8 lagged thrusters; 40 without a lag) still go to vector
 // lanes, none in the sub-step loop: with the largest class's thrusters it makes a
 // control step cost about 95 VALU and 185 scalar instructions more than k_step's.
-// Which calls it is used for: one_launch (runtime.hip).  Per control step, before (a launch per class and control step, forked and joined or
-// replayed from a graph) and with all in one launch, lagged envs, alternating
-// runs: two classes, one call per control step with statistics, 131072 envs of 4
-// sub-steps 48 -> 17.0 us, 2^20 of 16 187 -> 180; rollouts of 20, 4 sub-steps,
-// 131072 envs 14.0 -> 9.4, 2^20 68 -> 63; 16 sub-steps, 131072 envs 26.6 -> 24.7,
-// 2^20 168 -> 176 (such calls keep a launch per class); one class, 2^20 envs, 4
-// sub-steps 74 -> 62, 16 sub-steps 176 -> 175.  A
-// single class's mg_step stays with k_step, which is 2-8 % faster there.
-template <int N, bool LAG>
+// ORDER: the launch's blocks in the order segs.order gives (ClassSegs), in kernels
+// of their own: the order's look-up in every launch took six more spilled scalar
+// registers, and 6 control steps of 16 sub-steps of 2^20 envs of two classes in
+// halves 1139 us against 1097 (1054 both, with the kernels apart, on another card).
+// Which calls it is used for: one_launch (runtime.hip).  Per control step, before
+// (a launch per class and control step, forked and joined or replayed from a graph)
+// and with all in one launch, lagged envs, alternating runs: two classes, one call
+// per control step with statistics, 131072 envs of 4 sub-steps 48 -> 17.0 us, 2^20
+// of 16 187 -> 180; rollouts of 20, 4 sub-steps, 131072 envs 14.0 -> 9.4, 2^20 68
+// -> 63; 16 sub-steps, 131072 envs 26.6 -> 24.7, 2^20 168 -> 176 (such calls keep a
+// launch per class); one class, 2^20 envs, 4 sub-steps 74 -> 62, 16 sub-steps 176 ->
+// 175.  A single class's mg_step stays with k_step, which is 2-8 % faster there.
+template <int N, bool LAG, bool ORDER>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
 k_step_classes(const StepArgs a, const ClassSegs segs) {
   constexpr int D = Dims<N, LAG>::D;
   int block;
-  const int canonical = launch_block(segs, blockIdx.x);   // the statistics' partials are its
-  const int k = block_class(segs, canonical, block);
+  const int k = block_class(segs, ORDER ? launch_block(segs.order, blockIdx.x) : blockIdx.x, block);
   const ClassConst* ccp = segs.cc + k;
   auto class_const = [&]() { return scalar_class_const(pin_sgpr(ccp)); };
   const int64_t seg_start = segs.start[k], seg_len = segs.len[k];
@@ -294,7 +297,9 @@ k_step_classes(const StepArgs a, const ClassSegs segs) {
     }
     if (a.partials)
       block_stats(s_dist, m_dist, s_ke, n_bad,
-                  a.partials + ((int64_t)t * a.nblk_total + canonical) * 4);
+                  a.partials + ((int64_t)t * a.nblk_total +
+                                (ORDER ? launch_block(pin_sgpr(segs.order), blockIdx.x)
+                                       : blockIdx.x)) * 4);
   }
   if (!active) return;
   if (!a.each && all_finite()) {
@@ -345,12 +350,18 @@ hipError_t launch_step_classes(const ClassSegs& segs, const StepArgs& a, bool la
   if (a.Ep > ((int64_t)1 << 30) || a.E > ((int64_t)1 << 30)) return hipErrorInvalidValue;
   if (a.D != 13 + (lag ? a.n_max : 0)) return hipErrorInvalidValue;
   const dim3 grid((unsigned)nblk), block(kBlock);
+#define MG_LAUNCH(N, LAG)                                                               \
+  if (segs.order)                                                                       \
+    hipLaunchKernelGGL((k_step_classes<N, LAG, true>), grid, block, 0, s, a, segs);     \
+  else                                                                                  \
+    hipLaunchKernelGGL((k_step_classes<N, LAG, false>), grid, block, 0, s, a, segs);
 #define MG_CASE(n)                                                                      \
   case n:                                                                               \
-    if (lag)                                                                            \
-      hipLaunchKernelGGL((k_step_classes<n, true>), grid, block, 0, s, a, segs);        \
-    else                                                                                \
-      hipLaunchKernelGGL((k_step_classes<n, false>), grid, block, 0, s, a, segs);       \
+    if (lag) {                                                                          \
+      MG_LAUNCH(n, true)                                                                \
+    } else {                                                                            \
+      MG_LAUNCH(n, false)                                                               \
+    }                                                                                   \
     break;
   switch (a.n_max) {
     MG_CASE(1) MG_CASE(2) MG_CASE(3) MG_CASE(4) MG_CASE(5) MG_CASE(6) MG_CASE(7) MG_CASE(8)
@@ -358,6 +369,7 @@ hipError_t launch_step_classes(const ClassSegs& segs, const StepArgs& a, bool la
       return hipErrorInvalidValue;
   }
 #undef MG_CASE
+#undef MG_LAUNCH
   return hipGetLastError();
 }
 

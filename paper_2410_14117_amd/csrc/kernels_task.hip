@@ -148,7 +148,7 @@ k_task(const TaskArgs a, const SEGS segs, const TaskConst tc) {
   float x[D];
   int n = N, Dc = D;   // the class's thrusters and rows
   if constexpr (!cls.kOne) {
-    const ClassConst cc = cls.constants();
+    const ClassConst cc = cls.first_constants();
     n = cc.n_thr;
     Dc = 13 + (LAG && cc.lag ? n : 0);
   }
