@@ -164,9 +164,10 @@ __global__ void __launch_bounds__(kBlock) MG_STEP_ATTR k_step(const StepArgs a, 
 // lanes, none in the sub-step loop: with the largest class's thrusters it makes a
 // control step cost about 95 VALU and 185 scalar instructions more than k_step's.
 // ORDER: the launch's blocks in the order segs.order gives (ClassSegs), in kernels
-// of their own: the order's look-up in every launch took six more spilled scalar
-// registers, and 6 control steps of 16 sub-steps of 2^20 envs of two classes in
-// halves 1139 us against 1097 (1054 both, with the kernels apart, on another card).
+// of their own: with the order looked up in every launch seven more scalar registers
+// were spilled, and 6 control steps of 16 sub-steps of 2^20 envs of two classes in
+// halves took 1139 us against 1097 without it (with the kernels apart, on another
+// card, 1054 against 1053).
 // Which calls it is used for: one_launch (runtime.hip).  Per control step, before
 // (a launch per class and control step, forked and joined or replayed from a graph)
 // and with all in one launch, lagged envs, alternating runs: two classes, one call
